@@ -317,12 +317,35 @@ __device__ __forceinline__ uint64_t sat_add(uint64_t a, uint64_t b) {
     return (s < a || s > (1ull << 63)) ? (1ull << 63) : s;
 }
 
-// kRowLanes lanes share a row of up to kLongRow entries; longer ones are taken by whole blocks.
-// Block b owns rows b, b + nb, ... (nb blocks), so that hubs, which cluster at small ids in
-// power-law graphs, land in different blocks.
+// The row kernels.  kRowLanes lanes share a row; a row's loads form a chain (its bounds, its
+// entries, what those point at), so a group of lanes works on kRowsAhead rows at once, each
+// stage's loads for all of them before the next stage's.  Four neighbouring rows lie in one
+// wave (they share cache lines), and consecutive fours go to different blocks, since hubs
+// cluster at small indices (sixteen neighbouring rows per wave: 312 -> 446 us for the rows).  A block collects its rows of more than kLongRow entries in LDS
+// and takes them with all its threads at the end; those past the list's end stay with their
+// group.  (BA(10^6, 5), weighted: one row per group at a time took 276 us for the sums and
+// 474 us for the rows.)
 constexpr int kRowLanes = 16;
-constexpr int kLongRow = 1024;
+constexpr int kRowsAhead = 4;
+constexpr int kLongRow = 256;
+constexpr int kLongList = 256;
 constexpr int kRowBlocks = 2048;   // largest grid of the row kernels (their partials are kept per block)
+
+// Calls body(u[]) for every kRowsAhead rows of this thread's group.
+template <class Body>
+__device__ __forceinline__ void for_rows(int32_t n, Body body) {
+    constexpr int kGroupsPerWave = kWave / kRowLanes;
+    const int64_t nb = gridDim.x;
+    const int64_t waves = nb * (kBlock / kWave);
+    const int64_t first = (threadIdx.x / kWave) * nb + blockIdx.x;
+    const int g = (threadIdx.x & (kWave - 1)) / kRowLanes;
+    for (int64_t c = first; c * kGroupsPerWave < n; c += kRowsAhead * waves) {
+        int64_t u[kRowsAhead];
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) u[q] = (c + q * waves) * kGroupsPerWave + g;
+        body(u);
+    }
+}
 
 struct RowPartial {
     uint64_t max_s, vol;
@@ -373,54 +396,92 @@ __device__ __forceinline__ RowPartial block_merge(RowPartial p, RowPartial* lds)
     return p;
 }
 
-// Weighted degree (fixed point) of every input row, the repeated-edge check (equal neighbours in
-// the sorted keys), and per-block partials of vol, the largest row and the largest degree.
+// Weighted degree (fixed point) of every input row, the entries' weights in row order (fill_rows
+// would gather them again: half of them are random lines), the repeated-edge check (equal
+// neighbours in the sorted keys), and per-block partials of vol, the largest row and the largest degree.
 template <class K>
 __global__ void __launch_bounds__(kBlock)
     row_sums(int32_t n, const K* __restrict__ keys, const int32_t* __restrict__ vals, const float* __restrict__ w,
-             const int32_t* __restrict__ rows, uint64_t* __restrict__ sfix, RowPartial* __restrict__ parts) {
+             const int32_t* __restrict__ rows, float* __restrict__ wrow, uint64_t* __restrict__ sfix,
+             RowPartial* __restrict__ parts) {
     __shared__ RowPartial lds[kBlock / kWave];
     __shared__ uint64_t lsum[kBlock / kWave];
+    __shared__ int32_t long_rows[kLongList];
+    __shared__ uint32_t nlong;
+    if (threadIdx.x == 0) nlong = 0;
+    __syncthreads();
     const int sub = threadIdx.x & (kRowLanes - 1);
-    const int64_t nb = gridDim.x;
-    constexpr int kGroups = kBlock / kRowLanes;
     RowPartial p{0, 0, 0x7FFFFFFF, 0, 0, 0};
     auto entry = [&](int32_t i) -> uint64_t {
         if (i > 0 && keys[i - 1] == keys[i]) p.err |= kErrDupEdge;
-        return w ? fixed_weight(w[vals[i] >> 1]) : (1ull << 24);
+        if (!w) return 1ull << 24;
+        const float x = w[vals[i] >> 1];
+        wrow[i] = x;
+        return fixed_weight(x);
     };
-    bool any_long = false;
-    for (int64_t u = blockIdx.x + (threadIdx.x / kRowLanes) * nb; u < n; u += kGroups * nb) {
-        const int32_t beg = rows[u], end = rows[u + 1];
-        if (end - beg > kLongRow) {
-            any_long = true;
-            continue;
-        }
-        uint64_t S = 0;
-        for (int32_t i = beg + sub; i < end; i += kRowLanes) S += entry(i);
+    for_rows(n, [&](const int64_t (&u)[kRowsAhead]) {
+        int32_t beg[kRowsAhead], end[kRowsAhead];
+        uint64_t S[kRowsAhead];
 #pragma unroll
-        for (int off = kRowLanes / 2; off > 0; off >>= 1) S += __shfl_xor(S, off, kWave);
-        if (sub == 0) {
-            sfix[u] = S;
-            take_row(p, S, static_cast<int32_t>(u), end - beg);
+        for (int q = 0; q < kRowsAhead; ++q) {
+            beg[q] = u[q] < n ? rows[u[q]] : 0;
+            end[q] = u[q] < n ? rows[u[q] + 1] : 0;
         }
-    }
-    if (__syncthreads_or(any_long)) {
-        for (int64_t u = blockIdx.x; u < n; u += nb) {
-            const int32_t beg = rows[u], end = rows[u + 1];
-            if (end - beg <= kLongRow) continue;
-            uint64_t S = 0;   // under 2^23 entries of less than 2^40 each per thread
-            for (int32_t i = beg + static_cast<int32_t>(threadIdx.x); i < end; i += kBlock) S += entry(i);
+        // the first kRowLanes entries of every row, stage by stage
+        K key[kRowsAhead], prev[kRowsAhead];
+        int32_t e[kRowsAhead];
 #pragma unroll
-            for (int off = kWave / 2; off > 0; off >>= 1) S = sat_add(S, __shfl_xor(S, off, kWave));
-            __syncthreads();
-            if ((threadIdx.x & (kWave - 1)) == 0) lsum[threadIdx.x / kWave] = S;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                for (int v = 1; v < kBlock / kWave; ++v) S = sat_add(S, lsum[v]);
-                sfix[u] = S;
-                take_row(p, S, static_cast<int32_t>(u), end - beg);
+        for (int q = 0; q < kRowsAhead; ++q) {
+            const int32_t i = beg[q] + sub;
+            const bool have = i < end[q];
+            key[q] = have ? keys[i] : K{1};
+            prev[q] = have && i > 0 ? keys[i - 1] : K{0};
+            e[q] = have && w ? vals[i] >> 1 : 0;
+            if (have && i > 0 && prev[q] == key[q]) p.err |= kErrDupEdge;
+        }
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) {
+            const bool have = beg[q] + sub < end[q];
+            const float x = have && w ? w[e[q]] : 1.0f;
+            if (have && w) wrow[beg[q] + sub] = x;
+            S[q] = have ? fixed_weight(x) : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) {
+            const int32_t deg = end[q] - beg[q];
+            if (deg > kLongRow) {
+                uint32_t slot = 0;
+                if (sub == 0) {
+                    slot = atomicAdd(&nlong, 1u);
+                    if (slot < kLongList) long_rows[slot] = static_cast<int32_t>(u[q]);
+                }
+                if (__shfl(slot, 0, kRowLanes) < kLongList) continue;
             }
+            for (int32_t i = beg[q] + sub + kRowLanes; i < end[q]; i += kRowLanes) S[q] = sat_add(S[q], entry(i));
+#pragma unroll
+            for (int off = kRowLanes / 2; off > 0; off >>= 1) S[q] = sat_add(S[q], __shfl_xor(S[q], off, kWave));
+            if (sub == 0 && u[q] < n) {
+                sfix[u[q]] = S[q];
+                take_row(p, S[q], static_cast<int32_t>(u[q]), deg);
+            }
+        }
+    });
+    __syncthreads();
+    const uint32_t nl = nlong < kLongList ? nlong : kLongList;
+    for (uint32_t j = 0; j < nl; ++j) {
+        const int32_t u = long_rows[j];
+        const int32_t beg = rows[u], end = rows[u + 1];
+        uint64_t S = 0;
+        for (int32_t i = beg + static_cast<int32_t>(threadIdx.x); i < end; i += kBlock) S = sat_add(S, entry(i));
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) S = sat_add(S, __shfl_xor(S, off, kWave));
+        __syncthreads();
+        if ((threadIdx.x & (kWave - 1)) == 0) lsum[threadIdx.x / kWave] = S;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int v = 1; v < kBlock / kWave; ++v) S = sat_add(S, lsum[v]);
+            sfix[u] = S;
+            take_row(p, S, u, end - beg);
         }
     }
     __syncthreads();
@@ -497,21 +558,23 @@ struct RowOut {
 template <class K>
 __global__ void __launch_bounds__(kBlock)
     fill_rows(int32_t n, int bits, const K* __restrict__ keys, const int32_t* __restrict__ vals,
-              const float* __restrict__ w, const int32_t* __restrict__ rows, const uint64_t* __restrict__ sfix,
+              const float* __restrict__ wrow, const int32_t* __restrict__ rows, const uint64_t* __restrict__ sfix,
               const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ node_id,
               const int32_t* __restrict__ node_index, RowOut out, double* __restrict__ strength,
               uint32_t* __restrict__ rec) {
     static_assert(kRowLanes == kRecWords, "one record word per lane of a row");
     __shared__ uint64_t lsum[kBlock / kWave];
+    __shared__ int32_t long_rows[kLongList];
+    __shared__ uint32_t nlong;
+    if (threadIdx.x == 0) nlong = 0;
+    __syncthreads();
     const int sub = threadIdx.x & (kRowLanes - 1);
-    const int64_t nb = gridDim.x;
-    constexpr int kGroups = kBlock / kRowLanes;
     const K mask = (static_cast<K>(1) << bits) - 1;
     // entry i of the sorted list -> entry o of the CSR; returns its fixed-point weight
     auto copy = [&](int64_t i, int64_t o, int32_t& c) -> uint64_t {
         c = node_index[static_cast<uint32_t>(keys[i] & mask)];
         const int32_t e = vals[i] >> 1;
-        const float x = w ? w[e] : 1.0f;
+        const float x = wrow ? wrow[i] : 1.0f;
         out.col[o] = c;
         out.edge_id[o] = e;
         out.weight[o] = x;
@@ -540,38 +603,77 @@ __global__ void __launch_bounds__(kBlock)
         rec[static_cast<int64_t>(kRecWords) * x + sub] = word;
         if (sub == 0) strength[x] = static_cast<double>(S) * (1.0 / 16777216.0);
     };
-    bool any_long = false;
-    for (int64_t x = blockIdx.x + (threadIdx.x / kRowLanes) * nb; x < n; x += kGroups * nb) {
-        const int32_t id = node_id[x];
-        const int32_t from = rows[id], beg = row_ptr[x], deg = row_ptr[x + 1] - beg;
-        if (deg > kLongRow) {
-            any_long = true;
-            continue;
+    for_rows(n, [&](const int64_t (&x)[kRowsAhead]) {
+        int32_t id[kRowsAhead], from[kRowsAhead], beg[kRowsAhead], deg[kRowsAhead];
+        uint64_t S[kRowsAhead];
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) {
+            id[q] = x[q] < n ? node_id[x[q]] : 0;
+            beg[q] = x[q] < n ? row_ptr[x[q]] : 0;
+            deg[q] = x[q] < n ? row_ptr[x[q] + 1] - beg[q] : 0;
         }
-        uint64_t carry = 0, cd0 = 0;
-        int32_t c0 = 0;
-        for (int32_t b0 = 0; b0 < deg; b0 += kRowLanes) {
-            const int32_t i = b0 + sub;
-            int32_t c = 0;
-            const uint64_t W = i < deg ? copy(static_cast<int64_t>(from) + i, static_cast<int64_t>(beg) + i, c) : 0ull;
-            uint64_t cd = 0;
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) {
+            from[q] = rows[id[q]];
+            S[q] = sfix[id[q]];
+        }
+        // the first kRowLanes entries of every row, stage by stage
+        int32_t c[kRowsAhead], e[kRowsAhead];
+        float wt[kRowsAhead];
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) {
+            const bool have = sub < deg[q];
+            const int64_t i = static_cast<int64_t>(from[q]) + sub;
+            c[q] = have ? static_cast<int32_t>(keys[i] & mask) : 0;
+            e[q] = have ? vals[i] >> 1 : 0;
+            wt[q] = have && wrow ? wrow[i] : 1.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) c[q] = node_index[c[q]];
+#pragma unroll
+        for (int q = 0; q < kRowsAhead; ++q) {
+            if (x[q] >= n) continue;
+            if (deg[q] > kLongRow) {
+                uint32_t slot = 0;
+                if (sub == 0) {
+                    slot = atomicAdd(&nlong, 1u);
+                    if (slot < kLongList) long_rows[slot] = static_cast<int32_t>(x[q]);
+                }
+                if (__shfl(slot, 0, kRowLanes) < kLongList) continue;
+            }
+            const bool have = sub < deg[q];
+            const int64_t o = static_cast<int64_t>(beg[q]) + sub;
+            if (have) {
+                out.col[o] = c[q];
+                out.edge_id[o] = e[q];
+                out.weight[o] = wt[q];
+            }
+            uint64_t cd = 0, carry = 0;
             if (out.cdf) {
-                cd = carry + lanes_incl_scan_u64<kRowLanes>(W, sub);
-                if (i < deg) out.cdf[beg + i] = cd;
+                cd = lanes_incl_scan_u64<kRowLanes>(have ? fixed_weight(wt[q]) : 0ull, sub);
+                if (have) out.cdf[o] = cd;
                 carry = __shfl(cd, kRowLanes - 1, kRowLanes);
             }
-            if (b0 == 0) {
-                c0 = c;
-                cd0 = cd;
+            put_record(x[q], beg[q], deg[q], id[q], c[q], cd, S[q]);
+            for (int32_t b0 = kRowLanes; b0 < deg[q]; b0 += kRowLanes) {
+                const int32_t i = b0 + sub;
+                int32_t cc = 0;
+                const uint64_t W = i < deg[q] ? copy(static_cast<int64_t>(from[q]) + i, static_cast<int64_t>(beg[q]) + i, cc)
+                                              : 0ull;
+                if (out.cdf) {
+                    const uint64_t y = carry + lanes_incl_scan_u64<kRowLanes>(W, sub);
+                    if (i < deg[q]) out.cdf[beg[q] + i] = y;
+                    carry = __shfl(y, kRowLanes - 1, kRowLanes);
+                }
             }
         }
-        put_record(x, beg, deg, id, c0, cd0, sfix[id]);
-    }
-    if (!__syncthreads_or(any_long)) return;
+    });
+    __syncthreads();
+    const uint32_t nl = nlong < kLongList ? nlong : kLongList;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    for (int64_t x = blockIdx.x; x < n; x += nb) {
+    for (uint32_t j = 0; j < nl; ++j) {
+        const int32_t x = long_rows[j];
         const int32_t beg = row_ptr[x], deg = row_ptr[x + 1] - beg;
-        if (deg <= kLongRow) continue;
         const int32_t id = node_id[x];
         const int32_t from = rows[id];
         uint64_t carry = 0;
@@ -619,6 +721,7 @@ struct BfsState {
     uint32_t lo, hi;  // the frontier of the level that the wide kernels expand
     int32_t level;    // its distance from the pivot
     int32_t done;     // no frontier left: further launches return at once
+    int32_t up;       // the level is expanded from the unreached nodes (bfs_up)
     uint32_t nlong;   // long frontier rows deferred to bfs_long this level
     int32_t long_rows[kBfsLongRows];
 };
@@ -641,15 +744,36 @@ __device__ __forceinline__ void bfs_flush(BfsBuffer& b, int lane, int32_t* __res
     b.count = 0;
 }
 
-// Expands entries k0 + lane of the row (k0 wave-uniform, entries from `end` on ignored): a
-// neighbour still unreached is claimed for the next level and buffered for the queue.
-__device__ __forceinline__ void bfs_expand(int32_t k0, int32_t end, int lane, int32_t level,
+// The last entries of a block's waves, with one atomic for the block (an atomic per wave on the one
+// tail took 150 us a level at 16384 waves).
+__device__ __forceinline__ void bfs_finish(const BfsBuffer& b, int lane, int32_t* __restrict__ order, BfsState* st) {
+    __shared__ uint32_t count[kBlock / kWave];
+    __shared__ uint32_t base;
+    const int wid = threadIdx.x / kWave;
+    if (lane == 0) count[wid] = static_cast<uint32_t>(b.count);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int w = 0; w < kBlock / kWave; ++w) {
+            const uint32_t c = count[w];
+            count[w] = total;
+            total += c;
+        }
+        base = total ? atomicAdd(&st->tail, total) : 0u;
+    }
+    __syncthreads();
+    const uint32_t at = base + count[wid];
+    for (int32_t i = lane; i < b.count; i += kWave) order[at + i] = b.buf[i];
+}
+
+// Visits entry k of a row (lanes with `have`; the whole wave calls): a neighbour still unreached
+// is claimed for the next level and buffered for the queue.
+__device__ __forceinline__ void bfs_expand(bool have, int32_t k, int lane, int32_t level,
                                            const int32_t* __restrict__ col, int32_t* __restrict__ dist,
                                            int32_t* __restrict__ order, BfsState* st, BfsBuffer& b) {
-    const int32_t k = k0 + lane;
     int32_t w = 0;
     bool found = false;
-    if (k < end) {
+    if (have) {
         w = col[k];
         found = dist[w] == -1 && atomicCAS(&dist[w], -1, level + 1) == -1;
     }
@@ -660,33 +784,121 @@ __device__ __forceinline__ void bfs_expand(int32_t k0, int32_t end, int lane, in
     b.count += __popcll(m);
 }
 
-// One wave per frontier node, lanes over its neighbours; rows longer than kBfsLongRow go to
-// bfs_long (up to kBfsLongRows of them), so a hub's row does not hold the level on one wave.
-__global__ void bfs_level(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+// A wave takes four frontier nodes at a time, sixteen lanes over the neighbours of each (most rows
+// are short: with a wave per node BA(10^6, 5)'s levels took 683 us); rows past
+// kBfsGroupRow are then taken by the whole wave, and rows longer than kBfsLongRow go to bfs_long
+// (up to kBfsLongRows of them), so a hub's row does not hold the level on one wave.
+constexpr int kBfsLanes = 16;
+constexpr int kBfsGroupRow = 128;
+
+// Once the frontier outweighs the unreached nodes (Beamer, Asanovic, Patterson, "Direction-
+// optimizing breadth-first search", SC 2012; their factor 14, on node counts), each unreached
+// node looks for a neighbour on the frontier instead: few probes per node and no
+// compare-and-swap per entry (a stale line of another XCD's L2 sends most of those out in vain).
+constexpr int64_t kBfsUpFactor = 14;
+constexpr int kBfsUpLanes = 8;
+
+__device__ __forceinline__ void bfs_up(int32_t n, int64_t wave, int64_t nw, int lane, int32_t level,
+                                       const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+                                       int32_t* __restrict__ dist, int32_t* __restrict__ order, BfsState* st,
+                                       BfsBuffer& b) {
+    constexpr int kRows = kWave / kBfsUpLanes;
+    const int sub = lane & (kBfsUpLanes - 1);
+    for (int64_t u0 = kRows * wave; u0 < n; u0 += kRows * nw) {
+        const int64_t u = u0 + lane / kBfsUpLanes;
+        int32_t beg = 0, end = 0;
+        if (u < n && dist[u] == -1) {
+            beg = row_ptr[u];
+            end = row_ptr[u + 1];
+        }
+        const bool short_row = end - beg <= kBfsGroupRow;
+        bool found = false;
+        int32_t k = beg, stop = short_row ? end : beg;
+        while (__any(k < stop)) {
+            const bool hit = k + sub < stop && dist[col[k + sub]] == level;
+            const uint64_t m = __ballot(hit);
+            if ((m >> (lane & ~(kBfsUpLanes - 1))) & ((1u << kBfsUpLanes) - 1u)) {
+                found = true;
+                stop = 0;
+            }
+            k += kBfsUpLanes;
+        }
+        uint64_t rest = __ballot(!short_row && sub == 0);
+        while (rest) {   // longer rows: the whole wave, or every wave (bfs_long)
+            const int src = __builtin_ctzll(rest);
+            rest &= rest - 1;
+            const int32_t rb = __shfl(beg, src, kWave), re = __shfl(end, src, kWave);
+            if (re - rb > kBfsLongRow) {
+                uint32_t slot = 0;
+                if (lane == src) {
+                    slot = atomicAdd(&st->nlong, 1u);
+                    if (slot < kBfsLongRows) st->long_rows[slot] = static_cast<int32_t>(u);
+                }
+                if (__shfl(slot, src, kWave) < kBfsLongRows) continue;
+            }
+            for (int32_t k0 = rb; k0 < re; k0 += kWave)
+                if (__any(k0 + lane < re && dist[col[k0 + lane]] == level)) {
+                    found = found || lane == src;
+                    break;
+                }
+        }
+        found = found && sub == 0;
+        if (found) dist[u] = level + 1;
+        const uint64_t m = __ballot(found);
+        if (m == 0) continue;
+        if (b.count > kBfsBuf - kWave) bfs_flush(b, lane, order, st);
+        if (found) b.buf[b.count + __popcll(m & ((1ull << lane) - 1))] = static_cast<int32_t>(u);
+        b.count += __popcll(m);
+    }
+}
+
+__global__ void bfs_level(int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                           int32_t* __restrict__ dist, int32_t* __restrict__ order, BfsState* st) {
     if (st->done) return;
     const uint32_t lo = st->lo, hi = st->hi;
     const int32_t level = st->level;
     const int lane = threadIdx.x & (kWave - 1);
+    constexpr int kRows = kWave / kBfsLanes;
     const int64_t wave = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) +
                          __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t nw = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
     __shared__ int32_t lds[kBlock / kWave][kBfsBuf];
     BfsBuffer b{lds[threadIdx.x / kWave], 0};
-    for (int64_t i = lo + wave; i < hi; i += nw) {
-        const int32_t u = order[i];
-        const int32_t beg = row_ptr[u], end = row_ptr[u + 1];
-        if (end - beg > kBfsLongRow) {
-            uint32_t slot = 0;
-            if (lane == 0) {
-                slot = atomicAdd(&st->nlong, 1u);
-                if (slot < kBfsLongRows) st->long_rows[slot] = u;
-            }
-            if (__shfl(slot, 0, kWave) < kBfsLongRows) continue;
-        }
-        for (int32_t k0 = beg; k0 < end; k0 += kWave) bfs_expand(k0, end, lane, level, col, dist, order, st, b);
+    if (st->up) {
+        bfs_up(n, wave, nw, lane, level, row_ptr, col, dist, order, st, b);
+        bfs_finish(b, lane, order, st);
+        return;
     }
-    bfs_flush(b, lane, order, st);
+    for (int64_t i0 = lo + kRows * wave; i0 < hi; i0 += kRows * nw) {
+        const int64_t i = i0 + lane / kBfsLanes;
+        int32_t u = 0, beg = 0, end = 0;
+        if (i < hi) {
+            u = order[i];
+            beg = row_ptr[u];
+            end = row_ptr[u + 1];
+        }
+        const bool short_row = end - beg <= kBfsGroupRow;
+        const int32_t stop = short_row ? end : beg;
+        for (int32_t k = beg + (lane & (kBfsLanes - 1)); __any(k < stop); k += kBfsLanes)
+            bfs_expand(k < stop, k, lane, level, col, dist, order, st, b);
+        uint64_t rest = __ballot(!short_row && (lane & (kBfsLanes - 1)) == 0);
+        while (rest) {
+            const int src = __builtin_ctzll(rest);
+            rest &= rest - 1;
+            const int32_t rb = __shfl(beg, src, kWave), re = __shfl(end, src, kWave);
+            if (re - rb > kBfsLongRow) {
+                uint32_t slot = 0;
+                if (lane == src) {
+                    slot = atomicAdd(&st->nlong, 1u);
+                    if (slot < kBfsLongRows) st->long_rows[slot] = u;
+                }
+                if (__shfl(slot, src, kWave) < kBfsLongRows) continue;
+            }
+            for (int32_t k0 = rb; k0 < re; k0 += kWave)
+                bfs_expand(k0 + lane < re, k0 + lane, lane, level, col, dist, order, st, b);
+        }
+    }
+    bfs_finish(b, lane, order, st);
 }
 
 // The level's long rows, every wave taking every nw-th 64-entry chunk of each.
@@ -704,14 +916,28 @@ __global__ void bfs_long(const int32_t* __restrict__ row_ptr, const int32_t* __r
     for (uint32_t j = 0; j < nl; ++j) {
         const int32_t u = st->long_rows[j];
         const int32_t beg = row_ptr[u], end = row_ptr[u + 1];
+        if (st->up) {
+            // u is unreached: one neighbour on the frontier is enough
+            bool hit = false;
+            for (int64_t k0 = beg + wave * kWave; !hit && k0 < end; k0 += nw * kWave)
+                hit = __any(k0 + lane < end && dist[col[k0 + lane]] == level);
+            const bool found = hit && lane == 0 && atomicCAS(&dist[u], -1, level + 1) == -1;
+            const uint64_t m = __ballot(found);
+            if (m == 0) continue;
+            if (b.count > kBfsBuf - kWave) bfs_flush(b, lane, order, st);
+            if (found) b.buf[b.count] = u;
+            b.count += 1;
+            continue;
+        }
         for (int64_t k0 = beg + wave * kWave; k0 < end; k0 += nw * kWave)
-            bfs_expand(static_cast<int32_t>(k0), end, lane, level, col, dist, order, st, b);
+            bfs_expand(k0 + lane < end, static_cast<int32_t>(k0) + lane, lane, level, col, dist, order, st, b);
     }
-    bfs_flush(b, lane, order, st);
+    bfs_finish(b, lane, order, st);
 }
 
 // Levels of up to kNarrowNodes nodes and kNarrowEdges entries in one block: eight lanes per row
-// of up to kNarrowRow entries, then one wave per longer row.  `first`: the search starts here;
+// of up to kNarrowRow entries, one wave per row of up to kNarrowThreads, and all threads for a
+// longer one.  `first`: the search starts here;
 // otherwise the wide kernels have just expanded [lo, hi).
 constexpr int kNarrowThreads = 1024;
 constexpr int kNarrowNodes = 2048;
@@ -719,7 +945,7 @@ constexpr int kNarrowEdges = 16384;
 constexpr int kNarrowRow = 64;
 
 __global__ void __launch_bounds__(kNarrowThreads)
-    bfs_narrow(bool first, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+    bfs_narrow(int32_t n, bool first, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                int32_t* __restrict__ dist, int32_t* __restrict__ order, BfsState* st, BuildScalars* sc) {
     __shared__ int32_t list[2][kNarrowNodes];
     __shared__ int2 row[kNarrowNodes];
@@ -736,6 +962,7 @@ __global__ void __launch_bounds__(kNarrowThreads)
         const uint32_t size = hi - lo;
         if (size > kNarrowNodes) break;
         uint32_t edges = 0;
+        bool wide = false;
         for (uint32_t i = t; i < size; i += kNarrowThreads) {
             const int32_t u = listed ? list[cur][i] : order[lo + i];
             const int2 r = make_int2(row_ptr[u], row_ptr[u + 1]);
@@ -743,11 +970,12 @@ __global__ void __launch_bounds__(kNarrowThreads)
             // each term at most 2 kNarrowEdges, so that the sum cannot wrap
             const uint32_t d = static_cast<uint32_t>(r.y - r.x);
             edges += d < 2u * kNarrowEdges ? d : 2u * kNarrowEdges;
+            wide = wide || d > kNarrowThreads;
         }
         edges = wave_sum(edges);
         if (lane == 0) wsum[wid] = edges;
         if (t == 0) found_count = 0;
-        __syncthreads();
+        const bool any_wide = __syncthreads_or(wide) != 0;
         edges = 0;
         for (int w = 0; w < kNarrowThreads / kWave; ++w) edges += wsum[w];
         if (edges > kNarrowEdges) break;
@@ -766,9 +994,15 @@ __global__ void __launch_bounds__(kNarrowThreads)
         }
         for (uint32_t i = wid; i < size; i += kNarrowThreads / kWave) {
             const int2 r = row[i];
-            if (r.y - r.x > kNarrowRow)
+            if (r.y - r.x > kNarrowRow && r.y - r.x <= kNarrowThreads)
                 for (int32_t k = r.x + lane; k < r.y; k += kWave) visit(k);
         }
+        if (any_wide)   // at most kNarrowEdges / kNarrowThreads such rows
+            for (uint32_t i = 0; i < size; ++i) {
+                const int2 r = row[i];
+                if (r.y - r.x > kNarrowThreads)
+                    for (int32_t k = r.x + t; k < r.y; k += kNarrowThreads) visit(k);
+            }
         __syncthreads();
         const uint32_t found = found_count;
         __syncthreads();   // found_count and wsum are rewritten by the next level
@@ -785,6 +1019,7 @@ __global__ void __launch_bounds__(kNarrowThreads)
         st->tail = hi;
         st->level = level;
         st->nlong = 0;
+        st->up = kBfsUpFactor * (hi - lo) > n - static_cast<int64_t>(hi) ? 1 : 0;
         st->done = done ? 1 : 0;
         sc->bfs_tail = hi;
         sc->bfs_done = done ? 1 : 0;
@@ -976,9 +1211,11 @@ int build_rows(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, con
     hipLaunchKernelGGL(entry_keys<K>, grid(m), dim3(kBlock), 0, s, m, src, dst, w, n, bits, keys, vals, L.scalars);
     RWC_CHECK(radix_sort(&keys, &keys_tmp, &vals, &vals_tmp, nnz, 2 * bits, L.hist, L.sums, s));
     hipLaunchKernelGGL(row_bounds<K>, grid(static_cast<int64_t>(n) + 1), dim3(kBlock), 0, s, n, nnz, bits, keys, L.rows);
+    float* wrow = w ? reinterpret_cast<float*>(keys_tmp) : nullptr;   // the sort's spare array
     const unsigned want = blocks_for(n, kBlock / kRowLanes);
     const unsigned gr = want < kRowBlocks ? want : kRowBlocks;
-    hipLaunchKernelGGL(row_sums<K>, dim3(gr), dim3(kBlock), 0, s, n, keys, vals, w, L.rows, L.sfix, L.parts);
+    hipLaunchKernelGGL(row_sums<K>, dim3(gr), dim3(kBlock), 0, s, n, keys, vals, w, L.rows, wrow, L.sfix,
+                       L.parts);
     hipLaunchKernelGGL(row_stats, dim3(1), dim3(kBlock), 0, s, static_cast<int>(gr), L.parts, L.scalars);
     RWC_CHECK(read_scalars(host));
     // faults of single edges are reported before those of rows
@@ -999,7 +1236,7 @@ int build_rows(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, con
                        L.node_index, L.rows, deg);
     RWC_CHECK(exclusive_scan(deg, static_cast<int64_t>(n) + 1, L.sums, s));
     const RowOut out{L.col, L.edge_id, L.weight, L.cdf};
-    hipLaunchKernelGGL(fill_rows<K>, dim3(gr), dim3(kBlock), 0, s, n, bits, keys, vals, w, L.rows, L.sfix, L.row_ptr,
+    hipLaunchKernelGGL(fill_rows<K>, dim3(gr), dim3(kBlock), 0, s, n, bits, keys, vals, wrow, L.rows, L.sfix, L.row_ptr,
                        L.node_id, L.node_index, out, L.strength, L.rec);
     RWC_HIP(hipGetLastError());
     return RWC_OK;
@@ -1069,19 +1306,20 @@ extern "C" int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src, const 
     // levels past the last return at once
     int32_t* dist = L.nvals_a;
     hipLaunchKernelGGL(bfs_init, grid(n), dim3(kBlock), 0, s, n, pivot_index, dist, L.bfs_order, L.component, L.bfs);
-    hipLaunchKernelGGL(bfs_narrow, dim3(1), dim3(kNarrowThreads), 0, s, true, L.row_ptr, L.col, dist, L.bfs_order,
+    hipLaunchKernelGGL(bfs_narrow, dim3(1), dim3(kNarrowThreads), 0, s, n, true, L.row_ptr, L.col, dist, L.bfs_order,
                        L.bfs, L.scalars);
     // every level of a graph within the narrow limits is narrow
     const bool all_narrow = n <= kNarrowNodes && nnz <= kNarrowEdges;
-    const unsigned gw = blocks_for(n, 64) < gs ? blocks_for(n, 64) : gs;   // 16 rows per wave and more
+    // 16 nodes per wave and more, and no more blocks than the device holds at once
+    const unsigned gw = blocks_for(n, 64) < 2048u ? blocks_for(n, 64) : 2048u;
     // small-world graphs have two to four wide levels; deep graphs with wide levels double the
     // number launched between two looks, up to 32
     int64_t launched = 0;
     for (int32_t steps = all_narrow ? 0 : 4;; steps = steps < 32 ? 2 * steps : 32) {
         for (int32_t c = 0; c < steps; ++c) {
-            hipLaunchKernelGGL(bfs_level, dim3(gw), dim3(kBlock), 0, s, L.row_ptr, L.col, dist, L.bfs_order, L.bfs);
+            hipLaunchKernelGGL(bfs_level, dim3(gw), dim3(kBlock), 0, s, n, L.row_ptr, L.col, dist, L.bfs_order, L.bfs);
             hipLaunchKernelGGL(bfs_long, dim3(gw), dim3(kBlock), 0, s, L.row_ptr, L.col, dist, L.bfs_order, L.bfs);
-            hipLaunchKernelGGL(bfs_narrow, dim3(1), dim3(kNarrowThreads), 0, s, false, L.row_ptr, L.col, dist,
+            hipLaunchKernelGGL(bfs_narrow, dim3(1), dim3(kNarrowThreads), 0, s, n, false, L.row_ptr, L.col, dist,
                                L.bfs_order, L.bfs, L.scalars);
         }
         RWC_CHECK(read_scalars(&host));
