@@ -163,7 +163,11 @@ int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src_dev, const int32_t
                                         more than 16 entries per node, and no graph has
                                         spread starts (same forest)                         */
 
-#define RWC_SAMPLE_NO_LDS_STATE 512u /* keep every graph's tree state in HBM.  Without it,
+#define RWC_SAMPLE_NO_LDS_STATE 512u /* keep every graph's tree state in HBM.  Without it, a
+                                        call that leaves the plan open (no walkers, trees in
+                                        flight or path ring asked for) on graphs of at most
+                                        30 000 nodes and pivot eccentricity up to 32 pops its
+                                        trees' cycles in LDS, a work-group per tree; else,
                                         a call whose graphs all use walker teams and all fit
                                         (64 / W trees of n 8-byte words in 48 KB of LDS; at
                                         most 2^24 samples) grows its trees in LDS instead:
@@ -240,7 +244,8 @@ typedef struct rwc_sample_outputs {
                                     (-1 none, 0 captured by this call, 1 a cached graph
                                     replayed), graphs with LDS-resident trees.  The walk
                                     kernel is 3 (4 with the path ring) when graph 0's trees
-                                    live in LDS                                           */
+                                    live in LDS, 5 when they are grown by cycle popping (the
+                                    walkers per tree are then not used)                     */
 } rwc_sample_outputs;
 
 /* Workspace for rwc_sample_forests with these graphs and parameters. */

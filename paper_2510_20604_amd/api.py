@@ -186,7 +186,7 @@ def sample_forests(graphs: Graph | Sequence[Graph], num_samples: int, seed: int,
     `starts` ("auto", "shared", "spread"), `bfs_starts` (None = automatic, True =
     breadth-first from the root, False = ascending ids) and `path_ring` (None = automatic) pick
     how walker teams schedule their walks, and lds_state=False keeps every tree's state in HBM
-    (by default small graphs grow their trees in LDS); the forest does not depend on them.  `roots` (ids,
+    (by default small graphs grow their trees in LDS, by popping cycles where the plan is open); the forest does not depend on them.  `roots` (ids,
     single graph) samples spanning forests rooted at that set instead of trees rooted at one
     node.  `out` (a dict returned by an earlier call) reuses its output tensors, so that a
     repeated call with capture=True replays the library's cached hipGraph.  The call is
@@ -248,9 +248,9 @@ def sample_forests(graphs: Graph | Sequence[Graph], num_samples: int, seed: int,
     res["roots"] = rt
     res["walkers_per_tree"], res["trees_in_flight"], res["batches"] = int(plan[0]), int(plan[1]), int(plan[2])
     kernels = (("wilson_walk", "wilson_team<false>", "wilson_team<true>", "wilson_team_lds<false>",
-                "wilson_team_lds<true>") if strata < 2 else
+                "wilson_team_lds<true>", "cycle_pop") if strata < 2 else
                ("wilson_walk_strata", "wilson_team_strata<false>", "wilson_team_strata<true>",
-                "wilson_team_lds_strata<false>", "wilson_team_lds_strata<true>"))
+                "wilson_team_lds_strata<false>", "wilson_team_lds_strata<true>", "cycle_pop_strata"))
     res["walk_kernel"] = kernels[int(plan[3])]
     res["lds_graphs"] = int(plan[7])
     res["starts"] = "spread" if plan[4] else "shared"

@@ -7,12 +7,14 @@
 // reduction pass folds the per-tree departure counts into the per-node totals, writes the
 // requested parent dumps and resets the slots for the next batch.
 //
-// Two kernels (walk.hpp).  wilson_walk: one lane grows one tree, running Algorithm 3's three loops --
+// Kernels (walk.hpp).  wilson_walk: one lane grows one tree, running Algorithm 3's three loops --
 // pick the next start node that is not yet in the tree, walk until the tree is hit, retrace
 // the loop-erased path -- as one flat state machine, so every iteration of the wave does one
 // step of some lane's work instead of parking lanes that finished a phase early.
 // wilson_team: W lanes of one wave grow one tree together (below); used for large graphs,
 // whose per-tree state limits how many trees can be in flight.
+// A third (pop.hpp, cycle_pop) pops every cycle of the current arrows at once, round by round,
+// in LDS: the automatic choice for small-world graphs of up to kPopMaxNodes nodes.
 //
 // RandomNeighbor(u) at the k-th departure from u in sample i of graph word g is
 // Philox4x32-10((k, u, i, g), seed).  A node's successive choices are therefore fixed in
@@ -30,6 +32,7 @@
 #include "roots.hpp"
 #include "device.hpp"
 #include "walk.hpp"
+#include "pop.hpp"
 
 namespace rwc {
 
@@ -65,6 +68,7 @@ bool spread_starts(const rwc_csr& g, uint32_t flags) {
 
 using LdsKernel = void (*)(const GraphArgs*, const Item*, int32_t, uint32_t*, int64_t, int64_t, uint64_t,
                            const int64_t*, uint64_t*, uint64_t*, int32_t*, DumpArgs, uint64_t*, uint64_t*, uint32_t*);
+using PopKernel = void (*)(PopArgs, DumpArgs);
 using WalkKernel = void (*)(const GraphArgs*, const Item*, int32_t, uint32_t*, int32_t, int64_t, int64_t, uint64_t,
                             uint64_t*, uint64_t*, uint32_t*);
 
@@ -199,6 +203,10 @@ struct Plan {
     int64_t lds_words = 0;            // dynamic LDS of the LDS-state kernel, in 8-byte words
     int32_t batches = 1;
     int32_t lds_graphs = 0;
+    bool pop = false;                 // every graph's trees are grown by cycle_pop
+    int64_t pop_slots = 0;            // cycle_pop: the most work-groups
+    int64_t pop_stride = 0;           // words of a work-group's count slot in HBM (0: counts in LDS)
+    int64_t pop_sums = 0;             // words of a work-group's visit sums in HBM (0: several graphs)
     bool team = false;                // some graph uses more than one walker per tree
     bool hbm_team = false;            // some graph with HBM state uses walker teams
 };
@@ -251,6 +259,40 @@ int auto_walkers(int64_t n) {
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+// Whether cycle_pop grows the call's trees: an automatic plan (no walkers, trees in flight or path
+// ring asked for, and LDS state allowed) on graphs whose arrows fit 15 bits and whose walks are
+// short.  Measured against walker teams: 1.2 to 5 times faster (walk and reduction, ms: ER(300, 8)
+// x 2000 trees 0.93 -> 0.24, ER(1000, 8) x 2000 2.03 -> 0.67, BA(2000, 4) x 500 0.45 -> 0.13,
+// BA(20 000, 5) x 2000 3.76 -> 1.81, x 20 000 28.4 -> 15.7).  Above kPopLdsCounts nodes a graph
+// without hubs (largest degree under sqrt n) has long arrow paths and many rounds, which only
+// pays while a compute unit has few trees (ER(12 000, 8) x 500 trees 14.4 -> 8.3 ms, but x 2000
+// 16.4 -> 17.4 and x 20 000 50.7 -> 120).  Meshes (the test for spread starts) stay with the walker teams: their trees take
+// thousands of rounds of one cycle each (20 000-node grid: 2 975 rounds on average).
+bool pops_cycles(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) {
+    if (p->walkers_per_tree != 0 || p->walkers_per_graph || p->trees_in_flight > 0) return false;
+    if (p->flags & (RWC_SAMPLE_NO_LDS_STATE | RWC_SAMPLE_PATH_RING)) return false;
+    if (p->num_samples > kLdsMaxSamples || p->num_samples * G > (int64_t{1} << 30)) return false;
+    const bool few = p->num_samples * G <= 4 * device_cu_count();
+    for (int32_t g = 0; g < G; ++g) {
+        if (graphs[g].n > kPopMaxNodes || graphs[g].bfs_depth > kLongWalkDepth) return false;
+        const bool hubs = static_cast<int64_t>(graphs[g].max_degree) * graphs[g].max_degree >= graphs[g].n;
+        if (graphs[g].n > kPopLdsCounts && !hubs && !few) return false;
+    }
+    return true;
+}
+
+// Threads of a cycle_pop work-group.  A round is a chain of barriers and LDS latencies, so while the
+// call leaves compute units idle a tree gets a thread per node (ER(1000, 8): 500 trees 0.35 ms,
+// 0.42 with two nodes per thread, 0.59 with four); larger calls gain from fewer waves per tree
+// (ER(1000, 8), 4000 trees: 0.98, 0.83 and 0.99 ms; BA(2000, 4), 20 000 trees: 1.69 with two,
+// 1.27 with four).
+int pop_threads(int32_t n, int64_t trees) {
+    const int per = trees <= 4 * device_cu_count() ? 1 : trees * n < 6400000 ? 2 : 4;
+    int T = kWave;
+    while (T < kPopMaxThreads && per * T < n) T *= 2;
+    return T;
+}
+
 int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan* plan) {
     plan->node_off.assign(G + 1, 0);
     plan->W.assign(G, 1);
@@ -271,8 +313,9 @@ int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan
     // also holds larger graphs the two launches cannot overlap and the LDS launch's tail idles
     // the device (256 mixed graphs: the batch autotuner picks HBM state), so a call uses LDS
     // state only when every graph's trees fit.
-    bool all_fit = !(p->flags & RWC_SAMPLE_NO_LDS_STATE) && l <= kLdsMaxSamples;
-    for (int32_t g = 0; g < G && all_fit; ++g) {
+    plan->pop = pops_cycles(graphs, G, p);
+    bool all_fit = plan->pop || (!(p->flags & RWC_SAMPLE_NO_LDS_STATE) && l <= kLdsMaxSamples);
+    for (int32_t g = 0; g < G && all_fit && !plan->pop; ++g) {
         const int Wg = p->walkers_per_graph ? p->walkers_per_graph[g]
                        : (p->walkers_per_tree > 0) ? p->walkers_per_tree : auto_walkers(graphs[g].n);
         all_fit = Wg > 1 && (kWave / Wg) * round_up(graphs[g].n, 8) * 8 <= kLdsStateBytes;
@@ -298,12 +341,22 @@ int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan
         if (all_fit) {
             plan->lds[g] = 1;
             plan->T[g] = 0;
-            plan->lds_words = std::max<int64_t>(plan->lds_words, S * plan->stride[g]);
             ++plan->lds_graphs;
+            if (plan->pop) {
+                plan->lds_words = std::max<int64_t>(plan->lds_words, (PopLayout(graphs[g].n).words() + 1) / 2);
+                if (n > kPopLdsCounts) plan->pop_stride = std::max(plan->pop_stride, plan->stride[g]);
+            } else {
+                plan->lds_words = std::max<int64_t>(plan->lds_words, S * plan->stride[g]);
+            }
             continue;
         }
         plan->hbm_team = plan->hbm_team || W > 1;
         state_words += T * plan->stride[g];
+    }
+    if (plan->pop) {
+        // eight work-groups of 256 threads, or two of kPopMaxThreads, fill a compute unit
+        plan->pop_slots = std::min<int64_t>(l * G, (plan->pop_stride > 0 ? 2 : 8) * device_cu_count());
+        plan->pop_sums = G == 1 ? plan->stride[0] : 0;
     }
     const int64_t budget = (p->trees_in_flight <= 0) ? default_state_budget() : 0;
     if (p->trees_in_flight <= 0 && state_words * 8 > budget) {
@@ -335,12 +388,15 @@ struct SampleLayout {
     uint32_t* rootmask;
     int64_t mask_words;
     uint32_t* cover;   // [n0] components holding a root (graphs of several components)
+    uint32_t* pop_counts;   // departure counts of cycle_pop's work-groups
+    uint64_t* pop_sums;     // their visit sums
     size_t total;
 };
 
 // Work items of one batch of HBM-state graphs (a block of S tree slots each), then of the
 // LDS-state graphs (a block of S samples each, all samples in one launch).
 int64_t max_items(int32_t G, const Plan& plan, int64_t l) {
+    if (plan.pop) return G;   // one per graph: its samples are counted by the kernel
     int64_t k = 0;
     for (int32_t g = 0; g < G; ++g)
         k += plan.lds[g] ? (l + plan.S[g] - 1) / plan.S[g] : (plan.T[g] + plan.S[g] - 1) / plan.S[g];
@@ -368,6 +424,8 @@ SampleLayout carve_sample(void* ws, int32_t G, const Plan& plan, int32_t n0, int
     L.mask_words = (static_cast<int64_t>(n0) + 31) / 32;
     L.rootmask = c.take<uint32_t>(L.mask_words);
     L.cover = c.take<uint32_t>(n0);
+    L.pop_counts = c.take<uint32_t>(static_cast<size_t>(plan.pop_slots) * plan.pop_stride);
+    L.pop_sums = c.take<uint64_t>(static_cast<size_t>(plan.pop_slots) * 2 * plan.pop_sums);
     L.total = c.used();
     return L;
 }
@@ -444,6 +502,9 @@ struct Setup {
     bool ring = false, lds_ring = false;
     WalkKernel walk = nullptr;
     LdsKernel walk_lds = nullptr;
+    PopKernel pop = nullptr;
+    int pop_block = 0;
+    int32_t pop_walk_share = 0;
     int grid_persistent = 0;
     int32_t nit_hbm = 0, nit_lds = 0, grid_lds = 0;
     size_t lds_bytes = 0;
@@ -530,7 +591,9 @@ int make_setup(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, voi
             for (int32_t s0 = 0; s0 < plan.T[g]; s0 += plan.S[g]) S->items.push_back(Item{g, s0});
     S->nit_hbm = static_cast<int32_t>(S->items.size());
     for (int32_t g : order)
-        if (plan.lds[g])
+        if (plan.pop)
+            S->items.push_back(Item{g, 0});
+        else if (plan.lds[g])
             for (int64_t s0 = 0; s0 < l; s0 += plan.S[g]) S->items.push_back(Item{g, static_cast<int32_t>(s0)});
     S->nit_lds = static_cast<int32_t>(S->items.size()) - S->nit_hbm;
     const bool hbm_team = plan.hbm_team || (plan.team && S->nit_hbm == 0);
@@ -549,7 +612,31 @@ int make_setup(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, voi
         if (per_cu < 1) per_cu = 1;
         S->grid_persistent = per_cu * device_cu_count();
     }
-    if (S->nit_lds > 0) {
+    if (plan.pop) {
+        S->lds_bytes = static_cast<size_t>(plan.lds_words) * 8;
+        int32_t nmax = 0;
+        for (int32_t g = 0; g < G; ++g) nmax = std::max(nmax, graphs[g].n);
+        S->pop_block = pop_threads(nmax, p->num_samples * G);
+        if (nmax <= 2 * S->pop_block)
+            S->pop = strat ? cycle_pop_strata<2> : cycle_pop<2>;
+        else if (nmax <= 4 * S->pop_block)
+            S->pop = strat ? cycle_pop_strata<4> : cycle_pop<4>;
+        else if (nmax <= 8 * S->pop_block)
+            S->pop = strat ? cycle_pop_strata<8> : cycle_pop<8>;
+        else if (nmax <= 16 * S->pop_block)
+            S->pop = strat ? cycle_pop_strata<16> : cycle_pop<16>;
+        else
+            S->pop = strat ? cycle_pop_strata<32> : cycle_pop<32>;
+        // Following only the changed nodes' paths pays where a thread would double many nodes'
+        // arrows (BA(20 000, 5), 2000 trees: 4.07 -> 2.40 ms; BA(8000, 5): 1.21 -> 1.12 ms, but
+        // ER(8000, 8), whose paths are long: 7.7 -> 8.6 ms).
+        S->pop_walk_share = nmax > kPopLdsCounts ? 16 : 0;
+        int per_cu = 0;
+        RWC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, S->pop, S->pop_block, S->lds_bytes));
+        if (per_cu < 1) per_cu = 1;
+        int64_t grid = static_cast<int64_t>(per_cu) * device_cu_count();
+        S->grid_lds = static_cast<int32_t>(std::min(grid, plan.pop_slots));
+    } else if (S->nit_lds > 0) {
         if (strat)
             S->walk_lds = S->lds_ring ? static_cast<LdsKernel>(wilson_team_lds_strata<true>)
                                       : static_cast<LdsKernel>(wilson_team_lds_strata<false>);
@@ -738,12 +825,14 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
         if (nroots > 0 && graphs[0].components > 1)
             check_root_cover(graphs[0], p->roots, nroots, L.cover, L.rootmask, L.header, ls);
         if (p->root >= 0) hipLaunchKernelGGL(resolve_root, dim3(1), dim3(1), 0, ls, L.graphs, graphs[0].node_index, p->root);
-        hipLaunchKernelGGL(init_state, dim3(node_blocks), dim3(256), 0, ls, L.graphs, L.node_off, G, plan.total_nodes);
+        if (nit > 0)   // graphs with their trees in LDS have no slots to set up or to reduce
+            hipLaunchKernelGGL(init_state, dim3(node_blocks), dim3(256), 0, ls, L.graphs, L.node_off, G,
+                               plan.total_nodes);
         for (int32_t b = 0; b < plan.batches; ++b) {
             // every graph runs its samples [b*T_g, (b+1)*T_g); graphs with fewer batches idle
             if (out->timing_ms) RWC_HIP(hipEventRecord(timer.ev[0], ls));
             uint32_t* status = &L.header->status;
-            if (b == 0 && S.nit_lds > 0) {
+            if (b == 0 && (S.nit_lds > 0 || plan.pop)) {
                 // every tree of the LDS-state graphs, in one persistent launch
                 DumpArgs ldumps{};
                 if (plan.lds[0])
@@ -752,10 +841,24 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
                         ldumps.out[ldumps.count] = d;
                         ++ldumps.count;
                     }
-                hipLaunchKernelGGL(S.walk_lds, dim3(S.grid_lds), dim3(kWave), S.lds_bytes, ls, L.graphs,
-                                   L.items + S.nit_hbm, S.nit_lds, L.queue + 1, p->sample_begin, l, p->seed, L.node_off,
-                                   out->counts, out->counts_sq, out->parents, ldumps, out->tree_hash, out->total_steps,
-                                   status);
+                if (plan.pop) {
+                    const PopArgs args{L.graphs,      L.items,         G,          L.queue + 1,      p->sample_begin,
+                                       l,             p->seed,         L.node_off, L.pop_counts,     plan.pop_stride,
+                                       plan.pop_sums > 0 ? L.pop_sums : nullptr, plan.pop_sums,
+                                       out->counts,   out->counts_sq,  out->parents, out->tree_hash, out->total_steps,
+                                       status,        S.pop_walk_share};
+                    hipLaunchKernelGGL(S.pop, dim3(S.grid_lds), dim3(S.pop_block), S.lds_bytes, ls, args, ldumps);
+                    if (plan.pop_sums > 0)
+                        hipLaunchKernelGGL(pop_reduce,
+                                           dim3(blocks_for(graphs[0].n, 256), blocks_for(S.grid_lds, kPopSlots)), dim3(256),
+                                           0, ls, L.pop_sums, plan.pop_sums, S.grid_lds, graphs[0].n, graphs[0].node_id,
+                                           out->counts, out->counts_sq);
+                } else {
+                    hipLaunchKernelGGL(S.walk_lds, dim3(S.grid_lds), dim3(kWave), S.lds_bytes, ls, L.graphs,
+                                       L.items + S.nit_hbm, S.nit_lds, L.queue + 1, p->sample_begin, l, p->seed,
+                                       L.node_off, out->counts, out->counts_sq, out->parents, ldumps, out->tree_hash,
+                                       out->total_steps, status);
+                }
             }
             if (nit > 0 && persistent) {
                 hipLaunchKernelGGL(reset_queue, dim3(1), dim3(1), 0, ls, L.queue);
@@ -776,9 +879,10 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
                 }
             }
             if (out->timing_ms) RWC_HIP(hipEventRecord(timer.ev[1], ls));
-            hipLaunchKernelGGL(reduce_batch, dim3(node_blocks), dim3(256), 0, ls, L.graphs, L.node_off, G,
-                               plan.total_nodes, b, l, b + 1 < plan.batches, out->counts, out->counts_sq,
-                               out->parents, dumps);
+            if (nit > 0)
+                hipLaunchKernelGGL(reduce_batch, dim3(node_blocks), dim3(256), 0, ls, L.graphs, L.node_off, G,
+                                   plan.total_nodes, b, l, b + 1 < plan.batches, out->counts, out->counts_sq,
+                                   out->parents, dumps);
             if (out->timing_ms) {
                 RWC_HIP(hipEventRecord(timer.ev[2], ls));
                 RWC_HIP(hipEventSynchronize(timer.ev[2]));
@@ -852,7 +956,7 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
         out->plan[0] = plan.W[0];
         out->plan[1] = plan.T[0];
         out->plan[2] = plan.batches;
-        out->plan[3] = plan.lds[0] ? (S.lds_ring ? 4 : 3) : (!plan.team ? 0 : (S.ring ? 2 : 1));
+        out->plan[3] = plan.pop ? 5 : plan.lds[0] ? (S.lds_ring ? 4 : 3) : (!plan.team ? 0 : (S.ring ? 2 : 1));
         out->plan[4] = S.hg[0].spread;
         out->plan[5] = S.hg[0].order != nullptr ? 1 : 0;
         out->plan[6] = replayed;

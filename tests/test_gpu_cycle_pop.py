@@ -1,0 +1,96 @@
+"""The cycle-popping kernel (trees popped round by round in LDS) against the serial oracle, bit for
+bit: counts in LDS and in the workspace (above 8192 nodes), the last size it takes, work-group
+sizes, rounds that change more nodes than a list holds, deep rounds (two cliques joined by one
+edge), root sets, stratified entries, batches, and the calls that keep the walker teams."""
+import numpy as np
+import pytest
+
+import rwcgen as G
+from oracle import wilson as W
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2510_20604_amd")
+
+
+def _barbell(k):
+    a, b = np.triu_indices(k, 1)
+    src = np.concatenate([a, a + k, [0]])
+    dst = np.concatenate([b, b + k, [k]])
+    return G.graphs.EdgeList(2 * k, src.astype(np.int32), dst.astype(np.int32), None)
+
+
+def _graph(name):
+    if name == "barbell":
+        return _barbell(40)
+    if name == "pairs":      # a heavy edge inside every pair of leaves: over a quarter of the nodes on 2-cycles
+        k = 600
+        hub = np.zeros(k, np.int32)
+        a = (1 + 2 * np.arange(k)).astype(np.int32)
+        w = np.concatenate([np.full(k, 1.0), np.full(k, 9.0)]).astype(np.float32)
+        return G.graphs.EdgeList(2 * k + 1, np.concatenate([hub, a]), np.concatenate([a, a + 1]), w)
+    if name == "star":
+        return G.star_graph(700)
+    n = int(name[2:])
+    return G.erdos_renyi_lcc(n, 8, 5) if name[:2] == "er" else G.barabasi_albert(n, 3, 5)
+
+
+def _check(s, ref, l):
+    np.testing.assert_array_equal(P.as_uint64(s["counts"]), ref["visits"])
+    np.testing.assert_array_equal(P.as_uint64(s["counts_sq"]), ref["visits_sq"])
+    np.testing.assert_array_equal(P.as_uint64(s["tree_hash"][0]), ref["hash"])
+    np.testing.assert_array_equal(s["parents"].cpu().numpy(), ref["parents"][[0, l - 1]])
+    assert int(P.as_uint64(s["total_steps"])[0]) == int(ref["steps"].sum())
+
+
+@pytest.mark.parametrize("name,l,weighted,strata", [
+    ("er256", 90, True, 0), ("er257", 90, False, 0), ("er1000", 300, False, 0), ("ba1024", 40, True, 64), ("ba4097", 30, False, 0),
+    ("ba8192", 20, True, 0), ("ba8193", 20, False, 32), ("ba16385", 8, False, 0), ("ba30000", 6, True, 0), ("barbell", 40, False, 0),
+    ("pairs", 50, True, 0),
+    ("star", 30, False, 32)])
+def test_cycle_pop_is_bit_exact(name, l, weighted, strata):
+    g = _graph(name)
+    if weighted and g.w is None:
+        g = g.with_weights(G.uniform_weights(g.m, 0.5, 2.0, 9))
+    Gd = P.Graph(g.n, g.src, g.dst, g.w)
+    o = W.OracleCSR(g.n, g.src, g.dst, g.w)
+    ref = W.fastwalk_sample(o, o.pivot, 4001, 0, 2, l, want_parents=True, threads=8, strata=strata)
+    s = P.sample_forests(Gd, l, 4001, sample_begin=2, dump=[2, l + 1], strata=strata)
+    assert s["walk_kernel"] == ("cycle_pop_strata" if strata else "cycle_pop") and s["lds_graphs"] == 1
+    _check(s, ref, l)
+
+
+def test_cycle_pop_root_sets_and_batches():
+    g = G.barabasi_albert(9000, 3, 6)
+    Gd = P.Graph(g.n, g.src, g.dst)
+    o = W.OracleCSR(g.n, g.src, g.dst)
+    S = [7, 4000, 8999]
+    ref = W.fastwalk_sample(o, S, 5, 0, 0, 12, want_parents=True, threads=8)
+    s = P.sample_forests(Gd, 12, 5, roots=S, dump=[0, 11])
+    assert s["walk_kernel"] == "cycle_pop"
+    _check(s, ref, 12)
+    graphs = [G.erdos_renyi_lcc(200, 6, 1), g, G.barabasi_albert(2000, 4, 2)]
+    dev = [P.Graph(x.n, x.src, x.dst) for x in graphs]
+    b = P.sample_forests(dev, 10, 17, persistent=True, capture=True)
+    assert b["walk_kernel"] == "cycle_pop" and b["lds_graphs"] == 3
+    off = 0
+    for i, x in enumerate(graphs):
+        r = W.fastwalk_sample(W.OracleCSR(x.n, x.src, x.dst), dev[i].pivot, 17, i, 0, 10, threads=8)
+        np.testing.assert_array_equal(P.as_uint64(b["counts"])[off:off + x.n], r["visits"])
+        np.testing.assert_array_equal(P.as_uint64(b["tree_hash"][i]), r["hash"])
+        off += x.n
+
+
+def test_calls_that_keep_the_walker_teams():
+    big = G.barabasi_albert(30001, 2, 3)
+    mesh = G.grid_with_deletions(1500, 0.1, 3)
+    small = G.erdos_renyi_lcc(300, 8, 1)
+    er = G.erdos_renyi_lcc(8400, 8, 2)         # no hubs: counts in the workspace, and too many trees
+    assert P.sample_forests(P.Graph(er.n, er.src, er.dst), 1400, 3, want_hash=False)["walk_kernel"] == "wilson_team<true>"
+    for g, kw in ((big, {}), (mesh, {}), (small, {"walkers_per_tree": 16}), (small, {"lds_state": False}),
+                  (small, {"trees_in_flight": 8}), (small, {"path_ring": True})):
+        s = P.sample_forests(P.Graph(g.n, g.src, g.dst), 8, 3, **kw)
+        assert s["walk_kernel"].startswith("wilson_team"), kw
+    with pytest.raises(P.RWCError) as ei:      # a faulty root set leaves trees without a root: reported, none grown
+        P.sample_forests(P.Graph(small.n, small.src, small.dst), 40, 4, roots=[small.n, small.n + 1])
+    assert ei.value.status == -2
