@@ -7,9 +7,19 @@
 // Substituting into Eq. (3) with (calL_v^{-1})_uu estimated by t~_u = C_u / l gives
 //     RWC_u = vol t~_u / d_u - 2 h_u + RWC_v,   RWC_v = sum_u d_u h_u / vol.
 // L_v is symmetric positive definite, so the solve is Jacobi-preconditioned conjugate
-// gradients in FP64.  Dot products use fixed per-block partials summed in a fixed order, so
-// results are bitwise reproducible run to run.  This file is compiled without FMA
-// contraction.
+// gradients in FP64.  Dot products use fixed partials summed in a fixed order, so results are
+// bitwise reproducible run to run.  This file is compiled without FMA contraction.
+//
+// Three forms of the same iteration, by size (what an iteration costs besides its bytes is launches
+// and dependent reductions: as five launches it took 17-20 us whatever the graph):
+//  * pcg_small: graphs whose rows fit the LDS of one work-group run the whole solve in one launch
+//    (ER(300, 8), 30 iterations: the call 1153 -> 567 us);
+//  * up to kPairNodes nodes, two launches per iteration: the new direction z + beta p is formed where it
+//    is gathered, from (z, p) pairs of 16 bytes, and every block sums the partials of the
+//    launch before by itself (97 013-node mesh: 37 -> 24 us an iteration with the gaps);
+//  * above, where the gathers are the cost and a pair would double their bytes, the direction step
+//    is a launch of its own.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -22,11 +32,13 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kMaxBlocks = 2048;
+// The iteration's kernels: blocks of 1024 threads, no more than are resident, so that the partials
+// every block sums are few.
+constexpr int kIterBlock = 1024;
+constexpr int kIterBlocks = 512;
 
 struct Scalars {
-    double rz;      // r^T z of the current iterate
-    double alpha;
-    double beta;
+    double rz[2];   // r^T z at the start of the iteration, by its parity
     double rr;      // r^T r
     double rr0;     // ||b||^2
     double rwc_v;   // RWC of the pivot (of the root set for the group estimate)
@@ -39,22 +51,40 @@ __device__ __forceinline__ bool grounded(const uint32_t* __restrict__ gmask, int
     return gmask ? ((gmask[u >> 5] >> (u & 31)) & 1u) != 0 : u == v;
 }
 
+// v plus its copy moved by a data-parallel-primitive pattern (zero where nothing arrives).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRows, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRows, 0xF, false);
+    return v + __hiloint2double(hi, lo);
+}
+
+// Sum over the wave, valid in lane 63 (no LDS round trips: row shifts by 1, 2, 4, 8, then the row
+// totals broadcast to the next row and to the upper half).
+__device__ __forceinline__ double wave_sum_last(double v) {
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    return dpp_add<0x143, 0xC>(v);
+}
+
+// Sum over the block in every thread.  `lds` holds a double per wave; it may be reused after another
+// barrier.
 __device__ __forceinline__ double block_sum(double v, double* lds) {
-    v = wave_sum(v);
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    if (lane == 0) lds[wid] = v;
+    v = wave_sum_last(v);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) lds[threadIdx.x / kWave] = v;
     __syncthreads();
     double s = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < kBlock / kWave; ++w) s += lds[w];
-    __syncthreads();
-    return s;  // valid in thread 0
+    for (int w = 0; w < static_cast<int>(blockDim.x) / kWave; ++w) s += lds[w];
+    return s;
 }
 
 __global__ void pcg_init(int32_t n, int32_t v, const uint32_t* __restrict__ gmask, const double* __restrict__ d,
                          double* __restrict__ x, double* __restrict__ r, double* __restrict__ z, double* __restrict__ p,
-                         double* __restrict__ part) {
-    __shared__ double lds[kBlock / kWave];
+                         double2* __restrict__ zp, double* __restrict__ part, Scalars* sc) {
+    __shared__ double lds[2][kIterBlock / kWave];
     double rz = 0.0, rr = 0.0;
     for (int64_t u = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; u < n;
          u += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -63,37 +93,113 @@ __global__ void pcg_init(int32_t n, int32_t v, const uint32_t* __restrict__ gmas
         const double zu = gu ? 0.0 : ru / d[u];
         x[u] = 0.0;
         r[u] = ru;
-        z[u] = zu;
-        p[u] = zu;
+        if (zp) {
+            zp[u] = make_double2(zu, 0.0);
+        } else {
+            z[u] = zu;
+            p[u] = 0.0;
+        }
         rz += ru * zu;
         rr += ru * ru;
     }
-    rz = block_sum(rz, lds);
-    rr = block_sum(rr, lds);
+    rz = block_sum(rz, lds[0]);
+    rr = block_sum(rr, lds[1]);
     if (threadIdx.x == 0) {
         part[2 * blockIdx.x] = rz;
         part[2 * blockIdx.x + 1] = rr;
+        if (blockIdx.x == 0) {
+            sc->done = 0;
+            sc->iters = 0;
+        }
     }
 }
 
-// y = L_v p on the grounded system (row and column v removed, p_v kept at zero).  Block b owns
-// rows b, b + nb, b + 2 nb, ... (nb blocks), so hub rows, which cluster at small ids in
-// power-law graphs, land in different blocks.  kRowLanes lanes share a short row (strided over its
-// entries, then a shuffle reduction); rows longer than kLongRow are left out of that pass and
-// then taken one at a time, in order, by the whole block.
-constexpr int kRowLanes = 16;
-constexpr int kLongRow = 16 * kRowLanes;
+// Start of iteration `it`, in every block: sums the partials of r^T z and r^T r that the last
+// update left, decides whether the solve is done and returns beta through *beta.  Block 0 records
+// the scalars (r^T z by parity: the other blocks still read the last one's).  True: stop.
+__device__ __forceinline__ bool begin_iteration(int it, const double* __restrict__ part, int nparts, Scalars* sc,
+                                                double tol2, double* beta, double (*lds)[kIterBlock / kWave]) {
+    if (sc->done) return true;
+    double a = 0.0, b = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += blockDim.x) {
+        a += part[2 * i];
+        b += part[2 * i + 1];
+    }
+    const double last = sc->rz[(it + 1) & 1];
+    a = block_sum(a, lds[0]);
+    b = block_sum(b, lds[1]);
+    const bool done = it == 0 ? b == 0.0 : b <= tol2 * sc->rr0;
+    *beta = (it == 0 || last == 0.0) ? 0.0 : a / last;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc->rz[it & 1] = a;
+        sc->rr = b;
+        if (it == 0) sc->rr0 = b;
+        sc->iters = it;
+        if (done) sc->done = 1;
+    }
+    return done;
+}
 
-__global__ void spmv_dot(int32_t n, int32_t v, const uint32_t* __restrict__ gmask, const Scalars* __restrict__ sc,
-                         const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                         const float* __restrict__ weight, const double* __restrict__ d, const double* __restrict__ p,
-                         double* __restrict__ ap, double* __restrict__ part) {
-    __shared__ double lds[kBlock / kWave];
-    __shared__ uint64_t long_mask[kBlock / kWave];
-    if (sc->done) return;
-    const int sub = threadIdx.x & (kRowLanes - 1);
-    const int group = threadIdx.x / kRowLanes;
-    constexpr int kGroups = kBlock / kRowLanes;
+// Direction step of the three-launch form: p = z + beta p.  With one block and n = 0 it only looks
+// at convergence (the end of a batch of launches).
+__global__ void __launch_bounds__(kIterBlock)
+    update_p(int it, int32_t n, int32_t v, const uint32_t* __restrict__ gmask, Scalars* sc, double tol2,
+             const double* __restrict__ part, int nparts, const double* __restrict__ z, double* __restrict__ p) {
+    __shared__ double lds[2][kIterBlock / kWave];
+    double beta;
+    if (begin_iteration(it, part, nparts, sc, tol2, &beta, lds)) return;
+    for (int64_t u = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; u < n;
+         u += static_cast<int64_t>(gridDim.x) * blockDim.x)
+        if (!grounded(gmask, v, u)) p[u] = z[u] + beta * p[u];
+}
+
+// The vector an iteration gathers: p itself, or z + beta p from pairs.
+template <bool kPair>
+struct Direction;
+template <>
+struct Direction<false> {
+    const double* p;
+    double beta;
+    __device__ double at(int64_t c) const { return p[c]; }
+};
+template <>
+struct Direction<true> {
+    const double2* zp;
+    double beta;
+    __device__ double at(int64_t c) const {
+        const double2 q = zp[c];
+        return q.x + beta * q.y;
+    }
+};
+
+// y = L_v p on the grounded system (row and column v removed, p_v kept at zero), with p^T y.  Block b
+// owns rows b, b + nb, b + 2 nb, ... (nb blocks), so hub rows, which cluster at small ids in
+// power-law graphs, land in different blocks.  kLanes lanes share a short row (strided over its
+// entries, then a shuffle reduction; four on meshes, sixteen otherwise); rows longer than
+// 16 kLanes are left out of that pass and then taken one at a time, in order, by the whole block.
+// kPair: starts the iteration, and stores the new direction of the rows in zp_out.
+template <bool kPair, int kLanes>
+__global__ void __launch_bounds__(kIterBlock)
+    spmv_dot(int it, int32_t n, int32_t v, const uint32_t* __restrict__ gmask, Scalars* sc, double tol2,
+             const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const float* __restrict__ weight,
+             const double* __restrict__ d, const double* __restrict__ part_in, int nparts,
+             const double* __restrict__ p_in, const double2* __restrict__ zp_in, double2* __restrict__ zp_out,
+             double* __restrict__ ap, double* __restrict__ part) {
+    constexpr int kLongRow = 16 * kLanes;
+    constexpr int kWaves = kIterBlock / kWave;
+    __shared__ double lds[2][kWaves];
+    __shared__ uint64_t long_mask[kWaves];
+    Direction<kPair> dir;
+    if constexpr (kPair) {
+        dir.zp = zp_in;
+        if (begin_iteration(it, part_in, nparts, sc, tol2, &dir.beta, lds)) return;
+    } else {
+        dir.p = p_in;
+        if (sc->done) return;
+    }
+    const int sub = threadIdx.x & (kLanes - 1);
+    const int group = threadIdx.x / kLanes;
+    constexpr int kGroups = kIterBlock / kLanes;
     const int64_t b = blockIdx.x, nb = gridDim.x;
     double acc = 0.0;
     // A row's loads form a chain (bounds, entries, gathers).  The next row's bounds and this
@@ -115,29 +221,31 @@ __global__ void spmv_dot(int32_t n, int32_t v, const uint32_t* __restrict__ gmas
             nend = row_ptr[un + 1];
         }
         if (end - beg <= kLongRow) {
-            const double du = d[u], pu = p[u];
+            const double du = d[u];
+            const double pu = dir.at(u);
             double s = 0.0;
             int32_t k = beg + sub;
-            for (; k + 3 * kRowLanes < end; k += 4 * kRowLanes) {
+            for (; k + 3 * kLanes < end; k += 4 * kLanes) {
                 int32_t c[4];
                 float w[4];
                 double x[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    c[i] = col[k + i * kRowLanes];
-                    w[i] = weight[k + i * kRowLanes];
+                    c[i] = col[k + i * kLanes];
+                    w[i] = weight[k + i * kLanes];
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = p[c[i]];
+                for (int i = 0; i < 4; ++i) x[i] = dir.at(c[i]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) s += static_cast<double>(w[i]) * x[i];
             }
-            for (; k < end; k += kRowLanes) s += static_cast<double>(weight[k]) * p[col[k]];
+            for (; k < end; k += kLanes) s += static_cast<double>(weight[k]) * dir.at(col[k]);
 #pragma unroll
-            for (int off = kRowLanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+            for (int off = kLanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
             if (sub == 0) {
                 const double y = grounded(gmask, v, u) ? 0.0 : du * pu - s;
                 ap[u] = y;
+                if constexpr (kPair) zp_out[u].y = pu;
                 acc += pu * y;
             }
         }
@@ -145,107 +253,244 @@ __global__ void spmv_dot(int32_t n, int32_t v, const uint32_t* __restrict__ gmas
         beg = nbeg;
         end = nend;
     }
-    for (int64_t base = b; base < n; base += kBlock * nb) {
-        const int64_t u = base + threadIdx.x * nb;
-        const bool is_long = u < n && row_ptr[u + 1] - row_ptr[u] > kLongRow;
+    for (int64_t base = b; base < n; base += kIterBlock * nb) {
+        const int64_t w = base + threadIdx.x * nb;
+        const bool is_long = w < n && row_ptr[w + 1] - row_ptr[w] > kLongRow;
         const uint64_t m = __ballot(is_long);
+        __syncthreads();
         if ((threadIdx.x & (kWave - 1)) == 0) long_mask[threadIdx.x / kWave] = m;
         __syncthreads();
-        for (int wv = 0; wv < kBlock / kWave; ++wv) {
+        int turn = 0;
+        for (int wv = 0; wv < kWaves; ++wv) {
             uint64_t bits = long_mask[wv];
             while (bits) {
                 const int bit = __builtin_ctzll(bits);
                 bits &= bits - 1;
                 const int64_t r = base + (wv * kWave + bit) * nb;
-                const int32_t beg = row_ptr[r], end = row_ptr[r + 1];
+                const int32_t rb = row_ptr[r], re = row_ptr[r + 1];
                 double s = 0.0;
-                for (int32_t k = beg + static_cast<int32_t>(threadIdx.x); k < end; k += kBlock)
-                    s += static_cast<double>(weight[k]) * p[col[k]];
-                s = block_sum(s, lds);
+                for (int32_t k = rb + static_cast<int32_t>(threadIdx.x); k < re; k += kIterBlock)
+                    s += static_cast<double>(weight[k]) * dir.at(col[k]);
+                s = block_sum(s, lds[turn]);
+                turn ^= 1;   // the other array's readers have passed this sum's barrier
                 if (threadIdx.x == 0) {
-                    const double y = grounded(gmask, v, r) ? 0.0 : d[r] * p[r] - s;
+                    const double pr = dir.at(r);
+                    const double y = grounded(gmask, v, r) ? 0.0 : d[r] * pr - s;
                     ap[r] = y;
-                    acc += p[r] * y;
+                    if constexpr (kPair) zp_out[r].y = pr;
+                    acc += pr * y;
                 }
             }
         }
-        __syncthreads();
     }
-    acc = block_sum(acc, lds);
-    if (threadIdx.x == 0) part[2 * blockIdx.x] = acc;
+    __syncthreads();
+    acc = block_sum(acc, lds[0]);
+    if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
-__global__ void update_xr(int32_t n, int32_t v, const uint32_t* __restrict__ gmask, const Scalars* __restrict__ sc,
-                          const double* __restrict__ d, double* __restrict__ x, double* __restrict__ r,
-                          double* __restrict__ z, const double* __restrict__ p, const double* __restrict__ ap,
-                          double* __restrict__ part) {
-    __shared__ double lds[kBlock / kWave];
+// x += alpha p, r -= alpha A p, z = r / d, with r^T z and r^T r; alpha from the product's partials,
+// summed by every block.
+template <bool kPair>
+__global__ void __launch_bounds__(kIterBlock)
+    update_xr(int it, int32_t n, int32_t v, const uint32_t* __restrict__ gmask, const Scalars* __restrict__ sc,
+              const double* __restrict__ part_in, int nparts, const double* __restrict__ d, double* __restrict__ x,
+              double* __restrict__ r, double* __restrict__ z, const double* __restrict__ p, double2* __restrict__ zp,
+              const double* __restrict__ ap, double* __restrict__ part) {
+    __shared__ double lds[3][kIterBlock / kWave];
     if (sc->done) return;
-    const double alpha = sc->alpha;
+    double pap = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += blockDim.x) pap += part_in[i];
+    pap = block_sum(pap, lds[2]);
+    const double alpha = (pap != 0.0) ? sc->rz[it & 1] / pap : 0.0;
     double rz = 0.0, rr = 0.0;
     for (int64_t u = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; u < n;
          u += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        if (grounded(gmask, v, u)) continue;
-        x[u] = x[u] + alpha * p[u];
+        if (grounded(gmask, v, u)) {
+            if constexpr (kPair) zp[u] = make_double2(0.0, 0.0);
+            continue;
+        }
+        const double pu = kPair ? zp[u].y : p[u];
+        x[u] = x[u] + alpha * pu;
         const double ru = r[u] - alpha * ap[u];
         const double zu = ru / d[u];
         r[u] = ru;
-        z[u] = zu;
+        if constexpr (kPair)
+            zp[u].x = zu;
+        else
+            z[u] = zu;
         rz += ru * zu;
         rr += ru * ru;
     }
-    rz = block_sum(rz, lds);
-    rr = block_sum(rr, lds);
+    rz = block_sum(rz, lds[0]);
+    rr = block_sum(rr, lds[1]);
     if (threadIdx.x == 0) {
         part[2 * blockIdx.x] = rz;
         part[2 * blockIdx.x + 1] = rr;
     }
 }
 
-__global__ void update_p(int32_t n, int32_t v, const uint32_t* __restrict__ gmask, const Scalars* __restrict__ sc,
-                         const double* __restrict__ z, double* __restrict__ p) {
-    if (sc->done) return;
-    const double beta = sc->beta;
-    for (int64_t u = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; u < n;
-         u += static_cast<int64_t>(gridDim.x) * blockDim.x)
-        if (!grounded(gmask, v, u)) p[u] = z[u] + beta * p[u];
+// ---------------------------------------------------------------------------------------
+// The whole solve in one work-group: rows in LDS (16-bit columns, float weights unless they are
+// all 1), p and A p's gathered sums in LDS, the node's x, r and d in the registers of its thread.
+// What bounds it is the latency of an iteration's four barriers, two block sums and LDS gathers.
+// Eight lanes share a row; a row of more than kSmallLongRow entries is taken by a wave.
+// ---------------------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallPerThread = 4;
+constexpr int kSmallNodes = kSmallThreads * kSmallPerThread;
+constexpr size_t kSmallLds = 152 * 1024;
+constexpr int kSmallLanes = 8;
+constexpr int kSmallLongRow = 128;
+
+struct SmallLayout {
+    size_t p, s, rows, col, weight, list, total;   // byte offsets
+    __host__ __device__ SmallLayout(int32_t n, int64_t nnz, bool weighted) {
+        p = 0;
+        s = p + 8 * static_cast<size_t>(n);
+        rows = s + 8 * static_cast<size_t>(n);
+        weight = rows + 4 * (static_cast<size_t>(n) + 1);
+        col = weight + (weighted ? 4 * static_cast<size_t>(nnz) : 0);
+        list = col + 2 * static_cast<size_t>(nnz);
+        total = list + 2 * static_cast<size_t>(nnz / kSmallLongRow + 1);   // long rows
+    }
+};
+
+bool solves_small(const rwc_csr& g) {
+    return g.n <= kSmallNodes && SmallLayout(g.n, g.nnz, g.weighted != 0).total <= kSmallLds;
 }
 
-// Sums the per-block partials in a fixed order and advances the CG scalars.
-//   mode 0: after pcg_init (rz, rr0)    mode 1: after spmv_dot (alpha)
-//   mode 2: after update_xr (beta, rr)  mode 3: after pivot_partials (rwc_v)
-//   The iteration kernels return at once after the step that met the tolerance (`done`), so
-//   a fixed number of launched iterations stops exactly where a host-checked loop would.
-__global__ void scalars_step(const double* __restrict__ part, int nparts, Scalars* sc, int mode, double vol,
-                             double tol2) {
+__global__ void __launch_bounds__(kSmallThreads)
+    pcg_small(int32_t n, int32_t nnz, bool weighted, int32_t v, const uint32_t* __restrict__ gmask,
+              const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const float* __restrict__ weight,
+              const double* __restrict__ d, double vol, double tol2, int max_iter, double* __restrict__ x_out,
+              Scalars* sc, WsHeader* header) {
+    extern __shared__ __align__(16) unsigned char small_lds[];
+    __shared__ double red[3][kSmallThreads / kWave];
+    __shared__ uint32_t nlong;
+    const SmallLayout L(n, nnz, weighted);
+    double* const p = reinterpret_cast<double*>(small_lds + L.p);
+    double* const sum = reinterpret_cast<double*>(small_lds + L.s);
+    int32_t* const rows = reinterpret_cast<int32_t*>(small_lds + L.rows);
+    float* const lw = reinterpret_cast<float*>(small_lds + L.weight);
+    uint16_t* const lc = reinterpret_cast<uint16_t*>(small_lds + L.col);
+    uint16_t* const list = reinterpret_cast<uint16_t*>(small_lds + L.list);
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    if (t == 0) nlong = 0;
+    for (int i = t; i <= n; i += kSmallThreads) rows[i] = row_ptr[i];
+    for (int i = t; i < nnz; i += kSmallThreads) {
+        lc[i] = static_cast<uint16_t>(col[i]);
+        if (weighted) lw[i] = weight[i];
+    }
+    double x[kSmallPerThread], r[kSmallPerThread], dd[kSmallPerThread], ap[kSmallPerThread];
+    bool live[kSmallPerThread];
+    double rz = 0.0, rr = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSmallPerThread; ++i) {
+        const int u = t + i * kSmallThreads;
+        live[i] = u < n && !grounded(gmask, v, u);
+        dd[i] = live[i] ? d[u] : 1.0;
+        x[i] = 0.0;
+        ap[i] = 0.0;
+        r[i] = live[i] ? dd[i] : 0.0;
+        const double z = r[i] / dd[i];
+        if (u < n) p[u] = z;
+        rz += r[i] * z;
+        rr += r[i] * r[i];
+    }
+    __syncthreads();
+    for (int u = t; u < n; u += kSmallThreads)
+        if (rows[u + 1] - rows[u] > kSmallLongRow) list[atomicAdd(&nlong, 1u)] = static_cast<uint16_t>(u);
+    rz = block_sum(rz, red[0]);
+    rr = block_sum(rr, red[1]);
+    const double rr0 = rr;
+    bool done = rr0 == 0.0;
+    int it = 0;
+    const int sub = t & (kSmallLanes - 1);
+    while (!done && it < max_iter) {
+        // (p is complete: the barrier of the last block sum, or the one at the end of the loop)
+        for (int u = t / kSmallLanes; u < n; u += kSmallThreads / kSmallLanes) {
+            const int beg = rows[u], end = rows[u + 1];
+            if (end - beg > kSmallLongRow) continue;
+            double s = 0.0;
+            for (int k = beg + sub; k < end; k += kSmallLanes)
+                s += weighted ? static_cast<double>(lw[k]) * p[lc[k]] : p[lc[k]];
+#pragma unroll
+            for (int off = kSmallLanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+            if (sub == 0) sum[u] = s;
+        }
+        for (uint32_t j = t / kWave; j < nlong; j += kSmallThreads / kWave) {
+            const int u = list[j];
+            double s = 0.0;
+            for (int k = rows[u] + lane; k < rows[u + 1]; k += kWave)
+                s += weighted ? static_cast<double>(lw[k]) * p[lc[k]] : p[lc[k]];
+            s = wave_sum_last(s);
+            if (lane == kWave - 1) sum[u] = s;
+        }
+        __syncthreads();
+        double pap = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSmallPerThread; ++i) {
+            const int u = t + i * kSmallThreads;
+            if (live[i]) {
+                ap[i] = dd[i] * p[u] - sum[u];
+                pap += p[u] * ap[i];
+            }
+        }
+        pap = block_sum(pap, red[2]);
+        const double alpha = pap != 0.0 ? rz / pap : 0.0;
+        double nrz = 0.0, z[kSmallPerThread];
+        rr = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSmallPerThread; ++i) {
+            const int u = t + i * kSmallThreads;
+            z[i] = 0.0;
+            if (live[i]) {
+                x[i] = x[i] + alpha * p[u];
+                r[i] = r[i] - alpha * ap[i];
+                z[i] = r[i] / dd[i];
+                nrz += r[i] * z[i];
+                rr += r[i] * r[i];
+            }
+        }
+        nrz = block_sum(nrz, red[0]);
+        rr = block_sum(rr, red[1]);
+        const double beta = rz != 0.0 ? nrz / rz : 0.0;
+        rz = nrz;
+        ++it;
+        done = rr <= tol2 * rr0;
+#pragma unroll
+        for (int i = 0; i < kSmallPerThread; ++i) {
+            const int u = t + i * kSmallThreads;
+            if (live[i]) p[u] = z[i] + beta * p[u];
+        }
+        __syncthreads();
+    }
+    double h = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSmallPerThread; ++i) {
+        const int u = t + i * kSmallThreads;
+        if (u < n) x_out[u] = x[i];
+        if (live[i]) h += dd[i] * x[i];
+    }
+    h = block_sum(h, red[2]);
+    if (t == 0) {
+        sc->rz[0] = rz;
+        sc->rr = rr;
+        sc->rr0 = rr0;
+        sc->rwc_v = h / vol;
+        sc->done = done ? 1 : 0;
+        sc->iters = it;
+        header->iters = it;
+        if (!done) atomicOr(&header->status, static_cast<uint32_t>(kErrNotConverged));
+    }
+}
+
+__global__ void rwc_of_pivot(const double* __restrict__ part, int nparts, Scalars* sc, double vol) {
     __shared__ double lds[kBlock / kWave];
-    if ((mode == 1 || mode == 2) && sc->done) return;
-    double a = 0.0, b = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x) {
-        a += part[2 * i];
-        b += part[2 * i + 1];
-    }
+    double a = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += blockDim.x) a += part[i];
     a = block_sum(a, lds);
-    b = block_sum(b, lds);
-    if (threadIdx.x != 0) return;
-    if (mode == 0) {
-        sc->rz = a;
-        sc->rr0 = b;
-        sc->rr = b;
-        sc->beta = 0.0;
-        sc->done = (b == 0.0) ? 1 : 0;
-        sc->iters = 0;
-    } else if (mode == 1) {
-        sc->alpha = (a != 0.0) ? sc->rz / a : 0.0;
-    } else if (mode == 2) {
-        sc->beta = (sc->rz != 0.0) ? a / sc->rz : 0.0;
-        sc->rz = a;
-        sc->rr = b;
-        sc->iters += 1;
-        sc->done = (b <= tol2 * sc->rr0) ? 1 : 0;
-    } else {
-        sc->rwc_v = a / vol;
-    }
+    if (threadIdx.x == 0) sc->rwc_v = a / vol;
 }
 
 __global__ void pivot_partials(int32_t n, const double* __restrict__ d, const double* __restrict__ h,
@@ -256,10 +501,7 @@ __global__ void pivot_partials(int32_t n, const double* __restrict__ d, const do
          u += static_cast<int64_t>(gridDim.x) * blockDim.x)
         s += d[u] * h[u];
     s = block_sum(s, lds);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = s;
-        part[2 * blockIdx.x + 1] = 0.0;
-    }
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
 // Thread per internal index u; the caller's arrays (counts in, RWC, standard errors and
@@ -372,9 +614,14 @@ __global__ void solve_finish(const Scalars* __restrict__ sc, WsHeader* header) {
     if (!sc->done) atomicOr(&header->status, static_cast<uint32_t>(kErrNotConverged));
 }
 
+// The two-launch form's pairs (16 bytes a node) stay in each XCD's 4 MB of L2 up to here.
+constexpr int32_t kPairNodes = 200000;
+
 struct EstLayout {
     WsHeader* header;
     double *x, *r, *z, *p, *ap, *part;
+    double2* zp[2];   // (z, p) pairs, in turn (up to kPairNodes nodes)
+    double* part_ap;  // partials of p^T A p
     Scalars* sc;
     uint32_t* gmask;
     int64_t mask_words;
@@ -388,10 +635,14 @@ EstLayout carve_est(void* ws, int32_t n, bool group) {
     L.header = c.take<WsHeader>(kHeaderBytes / sizeof(WsHeader));
     L.x = c.take<double>(n);
     L.r = c.take<double>(n);
-    L.z = c.take<double>(n);
-    L.p = c.take<double>(n);
+    const bool pair = n <= kPairNodes;
+    L.z = pair ? nullptr : c.take<double>(n);
+    L.p = pair ? nullptr : c.take<double>(n);
+    L.zp[0] = pair ? c.take<double2>(n) : nullptr;
+    L.zp[1] = pair ? c.take<double2>(n) : nullptr;
     L.ap = c.take<double>(n);
-    L.part = c.take<double>(2 * kMaxBlocks);
+    L.part = c.take<double>(kMaxBlocks);   // at least 2 kIterBlocks
+    L.part_ap = c.take<double>(kIterBlocks);
     L.sc = c.take<Scalars>(1);
     L.mask_words = group ? (static_cast<int64_t>(n) + 31) / 32 : 0;
     L.gmask = group ? c.take<uint32_t>(L.mask_words) : nullptr;
@@ -412,62 +663,92 @@ int check_solve_params(const rwc_solve_params* sp) {
     return RWC_OK;
 }
 
-// Jacobi-PCG on the system grounded at v (or at the set in L.gmask): x solves L_G x = d_{-G}.
-// Host-checked mode reads the scalars every `check` iterations; stream-ordered mode
-// (check < 0) launches max_iter iterations, which stop on the device at convergence, and
-// leaves the outcome in the workspace header.
+// Jacobi-PCG on the system grounded at v (or at the set in L.gmask): x solves L_G x = d_{-G}, and
+// RWC of the pivot (of the set).  Host-checked mode reads the scalars after `check` iterations
+// and then after twice as many each time (at most kMaxCheck; always `check` if the caller chose
+// it); stream-ordered mode (check < 0) launches max_iter iterations, which stop on the device at
+// convergence, and leaves the outcome in the workspace header.  The iterations run do not
+// depend on the mode.
+constexpr int kMaxCheck = 128;
+
 int pivot_solve(const rwc_csr* g, int32_t v, const EstLayout& L, const rwc_solve_params* sp, int32_t* iters,
                 hipStream_t s, bool* async_out) {
     const int32_t n = g->n;
     const double tol = (sp && sp->tol > 0) ? sp->tol : 1e-12;
     const bool async = sp && sp->check_every < 0;
     const int max_iter = (sp && sp->max_iter > 0) ? sp->max_iter : (async ? 0 : 20000);
-    const int check = (sp && sp->check_every > 0) ? sp->check_every : 16;
+    const bool chosen = sp && sp->check_every > 0;
     const double tol2 = tol * tol;
-    const unsigned nb = blocks_for(n, kBlock) < kMaxBlocks ? blocks_for(n, kBlock) : kMaxBlocks;
-    const int64_t spmv_threads = static_cast<int64_t>(n) * kRowLanes;
-    const unsigned nb_spmv = blocks_for(spmv_threads, kBlock) < kMaxBlocks ? blocks_for(spmv_threads, kBlock) : kMaxBlocks;
     *async_out = async;
-
-    hipLaunchKernelGGL(pcg_init, dim3(nb), dim3(kBlock), 0, s, n, v, L.gmask, g->strength, L.x, L.r, L.z, L.p, L.part);
-    hipLaunchKernelGGL(scalars_step, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(nb), L.sc, 0, g->vol, tol2);
-    auto iteration = [&]() {
-        hipLaunchKernelGGL(spmv_dot, dim3(nb_spmv), dim3(kBlock), 0, s, n, v, L.gmask, L.sc, g->row_ptr, g->col,
-                           g->weight, g->strength, L.p, L.ap, L.part);
-        hipLaunchKernelGGL(scalars_step, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(nb_spmv), L.sc, 1,
-                           g->vol, tol2);
-        hipLaunchKernelGGL(update_xr, dim3(nb), dim3(kBlock), 0, s, n, v, L.gmask, L.sc, g->strength, L.x, L.r, L.z,
-                           L.p, L.ap, L.part);
-        hipLaunchKernelGGL(scalars_step, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(nb), L.sc, 2, g->vol,
-                           tol2);
-        hipLaunchKernelGGL(update_p, dim3(nb), dim3(kBlock), 0, s, n, v, L.gmask, L.sc, L.z, L.p);
-    };
-    if (async) {
-        for (int it = 0; it < max_iter; ++it) iteration();
-        hipLaunchKernelGGL(solve_finish, dim3(1), dim3(1), 0, s, L.sc, L.header);
+    Scalars host{};
+    auto read = [&]() -> int {
         RWC_HIP(hipGetLastError());
+        RWC_HIP(hipMemcpyAsync(&host, L.sc, sizeof(host), hipMemcpyDeviceToHost, s));
+        RWC_HIP(hipStreamSynchronize(s));
+        return RWC_OK;
+    };
+    auto outcome = [&]() -> int {
+        if (iters) *iters = host.iters;
+        if (!host.done)
+            return fail(RWC_ERR_NOT_CONVERGED, "pivot solve: relative residual %.3e after %d iterations",
+                        host.rr > 0 ? std::sqrt(host.rr / host.rr0) : 0.0, host.iters);
+        return RWC_OK;
+    };
+    if (solves_small(*g)) {
+        const bool weighted = g->weighted != 0;
+        const size_t lds = SmallLayout(n, g->nnz, weighted).total;
+        hipLaunchKernelGGL(pcg_small, dim3(1), dim3(kSmallThreads), lds, s, n, static_cast<int32_t>(g->nnz), weighted, v,
+                           L.gmask, g->row_ptr, g->col, g->weight, g->strength, g->vol, tol2, max_iter, L.x, L.sc,
+                           L.header);
+        RWC_HIP(hipGetLastError());
+        if (async) {
+            if (iters) *iters = -1;
+            return RWC_OK;
+        }
+        RWC_CHECK(read());
+        return outcome();
+    }
+    const bool pair = n <= kPairNodes;
+    const bool few = g->nnz <= 6 * static_cast<int64_t>(n);   // meshes: four lanes per row
+    const unsigned nb = std::min<unsigned>(blocks_for(n, kIterBlock), kIterBlocks);
+    const unsigned nbs = std::min<unsigned>(blocks_for(static_cast<int64_t>(n) * (few ? 4 : 16), kIterBlock), kIterBlocks);
+    const int np = static_cast<int>(nb), nps = static_cast<int>(nbs);
+    auto product = pair ? (few ? spmv_dot<true, 4> : spmv_dot<true, 16>) : (few ? spmv_dot<false, 4> : spmv_dot<false, 16>);
+    auto update = pair ? update_xr<true> : update_xr<false>;
+    hipLaunchKernelGGL(pcg_init, dim3(nb), dim3(kIterBlock), 0, s, n, v, L.gmask, g->strength, L.x, L.r, L.z, L.p,
+                       L.zp[0], L.part, L.sc);
+    auto direction = [&](int it, int32_t nodes) {
+        hipLaunchKernelGGL(update_p, dim3(nodes > 0 ? nb : 1), dim3(kIterBlock), 0, s, it, nodes, v, L.gmask, L.sc, tol2,
+                           L.part, np, L.z, L.p);
+    };
+    auto iteration = [&](int it) {
+        double2 *const in = L.zp[it & 1], *const out = L.zp[(it + 1) & 1];
+        if (!pair) direction(it, n);
+        hipLaunchKernelGGL(product, dim3(nbs), dim3(kIterBlock), 0, s, it, n, v, L.gmask, L.sc, tol2, g->row_ptr, g->col,
+                           g->weight, g->strength, L.part, np, L.p, in, out, L.ap, L.part_ap);
+        hipLaunchKernelGGL(update, dim3(nb), dim3(kIterBlock), 0, s, it, n, v, L.gmask, L.sc, L.part_ap, nps, g->strength,
+                           L.x, L.r, L.z, L.p, out, L.ap, L.part);
+    };
+    int launched = 0;
+    for (int chunk = async ? max_iter : chosen ? sp->check_every : 16; launched < max_iter;
+         chunk = chosen || 2 * chunk > kMaxCheck ? chunk : 2 * chunk) {
+        const int stop = std::min(launched + chunk, max_iter);
+        for (; launched < stop; ++launched) iteration(launched);
+        direction(launched, 0);   // the last iteration's convergence
+        if (async) break;
+        RWC_CHECK(read());
+        if (host.done) break;
+    }
+    hipLaunchKernelGGL(solve_finish, dim3(1), dim3(1), 0, s, L.sc, L.header);
+    const unsigned np2 = blocks_for(n, kBlock) < kMaxBlocks ? blocks_for(n, kBlock) : kMaxBlocks;
+    hipLaunchKernelGGL(pivot_partials, dim3(np2), dim3(kBlock), 0, s, n, g->strength, L.x, L.part);
+    hipLaunchKernelGGL(rwc_of_pivot, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(np2), L.sc, g->vol);
+    RWC_HIP(hipGetLastError());
+    if (async) {
         if (iters) *iters = -1;
         return RWC_OK;
     }
-    RWC_HIP(hipGetLastError());
-    Scalars host{};
-    RWC_HIP(hipMemcpyAsync(&host, L.sc, sizeof(host), hipMemcpyDeviceToHost, s));
-    RWC_HIP(hipStreamSynchronize(s));
-    int launched = 0;
-    while (!host.done && launched < max_iter) {
-        const int chunk = (max_iter - launched) < check ? (max_iter - launched) : check;
-        for (int c = 0; c < chunk; ++c) iteration();
-        RWC_HIP(hipGetLastError());
-        launched += chunk;
-        RWC_HIP(hipMemcpyAsync(&host, L.sc, sizeof(host), hipMemcpyDeviceToHost, s));
-        RWC_HIP(hipStreamSynchronize(s));
-    }
-    hipLaunchKernelGGL(solve_finish, dim3(1), dim3(1), 0, s, L.sc, L.header);
-    if (iters) *iters = host.iters;
-    if (!host.done)
-        return fail(RWC_ERR_NOT_CONVERGED, "pivot solve: relative residual %.3e after %d iterations",
-                    host.rr > 0 ? std::sqrt(host.rr / host.rr0) : 0.0, host.iters);
-    return RWC_OK;
+    return outcome();
 }
 
 }  // namespace
@@ -500,8 +781,6 @@ extern "C" int rwc_estimate(const rwc_csr* g, const uint64_t* counts, const uint
     hipLaunchKernelGGL(header_start, dim3(1), dim3(1), 0, s, L.header);
     bool async = false;
     RWC_CHECK(pivot_solve(g, v, L, sp, iters, s, &async));
-    hipLaunchKernelGGL(pivot_partials, dim3(nb), dim3(kBlock), 0, s, n, g->strength, L.x, L.part);
-    hipLaunchKernelGGL(scalars_step, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(nb), L.sc, 3, g->vol, 0.0);
     hipLaunchKernelGGL(assemble, dim3(nb), dim3(kBlock), 0, s, n, v, g->vol, static_cast<double>(l), g->node_id, counts,
                        counts_sq, g->strength, L.x, L.sc, rwc, stderr_out, hit);
     RWC_HIP(hipGetLastError());
@@ -524,8 +803,6 @@ extern "C" int rwc_estimate_diag(const rwc_csr* g, const double* diag, const rwc
     hipLaunchKernelGGL(header_start, dim3(1), dim3(1), 0, s, L.header);
     bool async = false;
     RWC_CHECK(pivot_solve(g, v, L, sp, iters, s, &async));
-    hipLaunchKernelGGL(pivot_partials, dim3(nb), dim3(kBlock), 0, s, n, g->strength, L.x, L.part);
-    hipLaunchKernelGGL(scalars_step, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(nb), L.sc, 3, g->vol, 0.0);
     hipLaunchKernelGGL(assemble_diag, dim3(nb), dim3(kBlock), 0, s, n, v, g->vol, g->node_id, diag, g->strength, L.x,
                        L.sc, rwc, hit);
     RWC_HIP(hipGetLastError());
@@ -568,8 +845,6 @@ extern "C" int rwc_estimate_group(const rwc_csr* g, const int32_t* roots, int32_
     }
     bool async = false;
     RWC_CHECK(pivot_solve(g, -1, L, sp, iters, s, &async));
-    hipLaunchKernelGGL(pivot_partials, dim3(nb), dim3(kBlock), 0, s, n, g->strength, L.x, L.part);
-    hipLaunchKernelGGL(scalars_step, dim3(1), dim3(kBlock), 0, s, L.part, static_cast<int>(nb), L.sc, 3, g->vol, 0.0);
     hipLaunchKernelGGL(assemble_group, dim3(nb), dim3(kBlock), 0, s, n, L.gmask, g->vol, static_cast<double>(l),
                        g->node_id, counts, g->strength, L.x, L.sc, marginal, hit, group_rwc);
     RWC_HIP(hipGetLastError());
