@@ -165,9 +165,12 @@ int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src_dev, const int32_t
 
 #define RWC_SAMPLE_NO_LDS_STATE 512u /* keep every graph's tree state in HBM.  Without it, a
                                         call that leaves the plan open (no walkers, trees in
-                                        flight or path ring asked for) on graphs of at most
-                                        30 000 nodes and pivot eccentricity up to 32 pops its
-                                        trees' cycles in LDS, a work-group per tree; else,
+                                        flight or path ring asked for) may pop its trees'
+                                        cycles in rounds, a work-group per tree: on graphs
+                                        of at most 30 000 nodes and pivot eccentricity up to
+                                        32 (state in LDS) and on meshes (a larger
+                                        eccentricity) of at most 200 000 nodes (above 20 500
+                                        in the workspace) while that is the faster; else,
                                         a call whose graphs all use walker teams and all fit
                                         (64 / W trees of n 8-byte words in 48 KB of LDS; at
                                         most 2^24 samples) grows its trees in LDS instead:
@@ -239,8 +242,10 @@ typedef struct rwc_sample_outputs {
     int32_t* plan;               /* HOST [8] or NULL, as used for graph 0: walkers per tree,
                                     trees in flight, number of batches, walk kernel (0 one
                                     walker per tree, 1 walker teams, 2 walker teams with the
-                                    LDS path ring), team starts (0 shared, 1 spread), start
-                                    order (0 ascending ids, 1 breadth-first), hipGraph
+                                    LDS path ring; trees in LDS: 3 walker teams, 4 with the
+                                    path ring; cycles popped in rounds: 5, of meshes 6),
+                                    team starts (0 shared, 1 spread), start order
+                                    (0 ascending ids, 1 breadth-first), hipGraph
                                     (-1 none, 0 captured by this call, 1 a cached graph
                                     replayed), graphs with LDS-resident trees.  The walk
                                     kernel is 3 (4 with the path ring) when graph 0's trees
@@ -383,9 +388,9 @@ typedef struct rwc_solve_params {
     double tol;        /* relative residual of the pivot solve; 0 = 1e-12                 */
     int32_t max_iter;  /* 0 = 20000 (host-checked mode); stream-ordered mode: 1..4096,
                           required                                                        */
-    int32_t check_every; /* iterations between host convergence checks; 0 = 16.  A negative
-                          value selects stream-ordered mode: max_iter iterations are
-                          enqueued at once and the solve stops on the device when the
+    int32_t check_every; /* iterations between host convergence checks; 0 = 16, then twice as
+                          many after each up to 128.  A negative value selects
+                          stream-ordered mode: max_iter iterations are enqueued at once and the solve stops on the device when the
                           residual meets tol (the same iterations a host-checked solve
                           runs, so the results are identical); the call then returns
                           without waiting, *iters is set to -1, and convergence is

@@ -248,9 +248,9 @@ def sample_forests(graphs: Graph | Sequence[Graph], num_samples: int, seed: int,
     res["roots"] = rt
     res["walkers_per_tree"], res["trees_in_flight"], res["batches"] = int(plan[0]), int(plan[1]), int(plan[2])
     kernels = (("wilson_walk", "wilson_team<false>", "wilson_team<true>", "wilson_team_lds<false>",
-                "wilson_team_lds<true>", "cycle_pop") if strata < 2 else
+                "wilson_team_lds<true>", "cycle_pop", "mesh_pop") if strata < 2 else
                ("wilson_walk_strata", "wilson_team_strata<false>", "wilson_team_strata<true>",
-                "wilson_team_lds_strata<false>", "wilson_team_lds_strata<true>", "cycle_pop_strata"))
+                "wilson_team_lds_strata<false>", "wilson_team_lds_strata<true>", "cycle_pop_strata", "mesh_pop_strata"))
     res["walk_kernel"] = kernels[int(plan[3])]
     res["lds_graphs"] = int(plan[7])
     res["starts"] = "spread" if plan[4] else "shared"

@@ -1,5 +1,5 @@
-// Cycle popping in rounds: Wilson's algorithm for graphs of up to kPopMaxNodes nodes whose walks
-// are short, one work-group per tree.  Included by sampler.hip.
+// Cycle popping in rounds: Wilson's algorithm for graphs of up to kPopMaxNodes nodes, one
+// work-group per tree, the tree in LDS.  Included by sampler.hip.
 //
 // Wilson's algorithm is cycle popping (Propp and Wilson, "How to get a perfectly random sample from
 // a generic Markov chain and generate a random spanning tree of a directed graph", J. Algorithms
@@ -25,6 +25,9 @@
 // that one LDS read per step answers both questions.  Departure counts (32 bits) are in LDS for
 // small graphs, else in a slot of the workspace per work-group (read together with the node's
 // record, whose latency it shares).
+//
+// Meshes take thousands of rounds of few cycles each (a 20 000-node mesh: 3 000) and have a kernel of
+// their own (tokens.hpp).
 //
 // What bounds it: the latency of a round (levels of two barriers and two LDS accesses, then a draw) while
 // the device is not full, and the issue of the levels' instructions once it is.  On graphs above
@@ -70,7 +73,7 @@ struct PopArgs {
     int64_t sample_begin, l;
     uint64_t seed;
     const int64_t* node_off;
-    uint32_t* count_slots;    // [work-groups][slot_stride], for graphs above kPopLdsCounts
+    uint32_t* slots;          // [work-groups][slot_stride] words of the trees in the workspace
     int64_t slot_stride;
     uint64_t* sums;           // [work-groups][2][sum_stride] visits and squared visits of the work-group's trees,
     int64_t sum_stride;       // reduced by pop_reduce; null: every tree is added to the totals
@@ -302,32 +305,21 @@ __device__ __forceinline__ void pop_tree(const GraphArgs& G, uint64_t sample, ui
     }
 }
 
-template <bool kStrat, bool kLdsCounts, int kPerThread>
-__device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps, const GraphArgs& G, int32_t graph,
-                                         int64_t rel, bool first, RWC_LDS uint32_t* lds, RWC_LDS uint32_t* counters,
-                                         RWC_LDS uint32_t* err, RWC_LDS uint64_t* red) {
-    const PopLayout P(G.n);
-    RWC_LDS uint16_t* const nx = (RWC_LDS uint16_t*)lds;
-    PopCounts<kLdsCounts> cnt;
-    if constexpr (kLdsCounts)
-        cnt.p = lds + (P.words() - P.counts);
-    else
-        cnt.p = global_ptr(A.count_slots + static_cast<int64_t>(blockIdx.x) * A.slot_stride);
+// Totals, checksum and parents of a grown tree (outputs are indexed by input id): count(x) is the
+// node's departures (0: a root), next(x) its parent.
+template <class Count, class Next>
+__device__ __forceinline__ void finish_tree(const PopArgs& A, const DumpArgs& dumps, const GraphArgs& G, int32_t graph,
+                                            int64_t rel, bool first, Count count, Next next,
+                                            RWC_LDS uint32_t* err, RWC_LDS uint64_t* red) {
     const int t = threadIdx.x, T = blockDim.x, lane = t & (kWave - 1);
-    if (t == 0) *err = 0;
-    pop_tree<kStrat, kLdsCounts, kPerThread>(G, static_cast<uint64_t>(A.sample_begin + rel), A.seed, A.walk_share, P,
-                                             lds, cnt,
-                                             counters, err);
-    // totals, checksum and parents (outputs are indexed by input id)
     int32_t dump_out = -1;
     for (int d = 0; d < dumps.count; ++d)
         if (dumps.slot[d] == rel) dump_out = dumps.out[d];
     const int64_t off = A.node_off[graph];
     uint64_t steps = 0, h = 0;
     for (int32_t x = t; x < G.n; x += T) {
-        const uint32_t c = cnt.get(x);
+        const uint32_t c = count(x);
         const int64_t id = G.node_id[x];
-        const uint32_t next = nx[x] & (kPopDone - 1u);
         if (A.sums) {
             uint64_t* const s = A.sums + static_cast<int64_t>(blockIdx.x) * 2 * A.sum_stride + x;
             s[0] = (first ? 0ull : s[0]) + c;
@@ -335,13 +327,16 @@ __device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps
         }
         if (c) {
             steps += c;
-            if (!A.sums) atomicAdd(reinterpret_cast<unsigned long long*>(&A.counts[off + id]), static_cast<unsigned long long>(c));
-            if (!A.sums && A.counts_sq)
-                atomicAdd(reinterpret_cast<unsigned long long*>(&A.counts_sq[off + id]),
-                          static_cast<unsigned long long>(square_count(c)));
-            if (A.tree_hash) h += splitmix64((static_cast<uint64_t>(id) << 32) | static_cast<uint32_t>(G.node_id[next]));
+            if (!A.sums) {
+                atomicAdd(reinterpret_cast<unsigned long long*>(&A.counts[off + id]), static_cast<unsigned long long>(c));
+                if (A.counts_sq)
+                    atomicAdd(reinterpret_cast<unsigned long long*>(&A.counts_sq[off + id]),
+                              static_cast<unsigned long long>(square_count(c)));
+            }
+            if (A.tree_hash)
+                h += splitmix64((static_cast<uint64_t>(id) << 32) | static_cast<uint32_t>(G.node_id[next(x)]));
         }
-        if (dump_out >= 0) A.parents[static_cast<int64_t>(dump_out) * G.n + id] = c ? G.node_id[next] : -1;
+        if (dump_out >= 0) A.parents[static_cast<int64_t>(dump_out) * G.n + id] = c ? G.node_id[next(x)] : -1;
     }
     steps = wave_sum(steps);
     h = wave_sum(h);
@@ -361,13 +356,33 @@ __device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps
         if (A.tree_hash) A.tree_hash[static_cast<int64_t>(graph) * A.l + rel] = h;
         if (*err) atomicOr(A.status, *err);
     }
-    __syncthreads();   // the next item's tree must not overtake this item's reads
+    __syncthreads();   // the next tree must not overtake this one's reads
 }
 
-// Persistent: work-groups pop trees, graph by graph, from `queue`.
-template <bool kStrat, int kPerThread>
-__device__ __forceinline__ void pop_items(const PopArgs& A, const DumpArgs& dumps, RWC_LDS uint32_t* lds) {
-    __shared__ uint32_t counters[4], err, next_item, bad;
+template <bool kStrat, bool kLdsCounts, int kPerThread>
+__device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps, const GraphArgs& G, int32_t graph,
+                                         int64_t rel, bool first, RWC_LDS uint32_t* lds, RWC_LDS uint32_t* counters,
+                                         RWC_LDS uint32_t* err, RWC_LDS uint64_t* red) {
+    const PopLayout P(G.n);
+    RWC_LDS uint16_t* const nx = (RWC_LDS uint16_t*)lds;
+    PopCounts<kLdsCounts> cnt;
+    if constexpr (kLdsCounts)
+        cnt.p = lds + (P.words() - P.counts);
+    else
+        cnt.p = global_ptr(A.slots + static_cast<int64_t>(blockIdx.x) * A.slot_stride);
+    if (threadIdx.x == 0) *err = 0;
+    pop_tree<kStrat, kLdsCounts, kPerThread>(G, static_cast<uint64_t>(A.sample_begin + rel), A.seed, A.walk_share, P, lds,
+                                             cnt, counters, err);
+    finish_tree(
+        A, dumps, G, graph, rel, first, [&](int32_t x) { return cnt.get(x); },
+        [&](int32_t x) { return nx[x] & (kPopDone - 1u); }, err, red);
+}
+
+// Persistent: work-groups pop trees, graph by graph, from `queue`, and hand them to
+// grow(graph, arguments, sample, first of this work-group, error word, scratch).
+template <class Grow>
+__device__ __forceinline__ void pop_items(const PopArgs& A, Grow grow) {
+    __shared__ uint32_t err, next_item, bad;
     __shared__ uint64_t red[2 * (kPopMaxThreads / kWave)];
     // a root set found faulty leaves trees without a root: the outputs are discarded anyway
     if (threadIdx.x == 0) bad = *A.status;
@@ -383,17 +398,24 @@ __device__ __forceinline__ void pop_items(const PopArgs& A, const DumpArgs& dump
         if (idx >= total) break;
         const int32_t graph = A.items[idx / A.l].graph;
         const GraphArgs G = A.graphs[graph];
-        if (G.n <= kPopLdsCounts)
-            pop_item<kStrat, true, kPerThread>(A, dumps, G, graph, idx % A.l, first, lds, (RWC_LDS uint32_t*)counters,
-                                   (RWC_LDS uint32_t*)&err, (RWC_LDS uint64_t*)red);
-        else
-            pop_item<kStrat, false, kPerThread>(A, dumps, G, graph, idx % A.l, first, lds, (RWC_LDS uint32_t*)counters,
-                                    (RWC_LDS uint32_t*)&err, (RWC_LDS uint64_t*)red);
+        grow(graph, G, idx % A.l, first, (RWC_LDS uint32_t*)&err, (RWC_LDS uint64_t*)red);
         first = false;
     }
     if (A.sums && first)   // no tree for this work-group
         for (int64_t i = threadIdx.x; i < 2 * A.sum_stride; i += blockDim.x)
             A.sums[static_cast<int64_t>(blockIdx.x) * 2 * A.sum_stride + i] = 0;
+}
+
+template <bool kStrat, int kPerThread>
+__device__ __forceinline__ void pop_graphs(const PopArgs& A, const DumpArgs& dumps, RWC_LDS uint32_t* lds) {
+    __shared__ uint32_t counters[4];
+    pop_items(A, [&](int32_t graph, const GraphArgs& G, int64_t rel, bool first, RWC_LDS uint32_t* err,
+                     RWC_LDS uint64_t* red) {
+        if (G.n <= kPopLdsCounts)
+            pop_item<kStrat, true, kPerThread>(A, dumps, G, graph, rel, first, lds, (RWC_LDS uint32_t*)counters, err, red);
+        else
+            pop_item<kStrat, false, kPerThread>(A, dumps, G, graph, rel, first, lds, (RWC_LDS uint32_t*)counters, err, red);
+    });
 }
 
 // Adds the work-groups' sums to the totals of a single graph: 256 nodes and kPopSlots work-groups
@@ -423,13 +445,13 @@ __global__ void __launch_bounds__(256) pop_reduce(const uint64_t* __restrict__ s
 template <int kPerThread>
 __global__ void __launch_bounds__(kPopMaxThreads, kPerThread <= 8 ? 8 : 4) cycle_pop(PopArgs A, DumpArgs dumps) {
     extern __shared__ uint32_t pop_lds[];
-    pop_items<false, kPerThread>(A, dumps, (RWC_LDS uint32_t*)pop_lds);
+    pop_graphs<false, kPerThread>(A, dumps, (RWC_LDS uint32_t*)pop_lds);
 }
 
 template <int kPerThread>
 __global__ void __launch_bounds__(kPopMaxThreads, kPerThread <= 8 ? 8 : 4) cycle_pop_strata(PopArgs A, DumpArgs dumps) {
     extern __shared__ uint32_t pop_lds[];
-    pop_items<true, kPerThread>(A, dumps, (RWC_LDS uint32_t*)pop_lds);
+    pop_graphs<true, kPerThread>(A, dumps, (RWC_LDS uint32_t*)pop_lds);
 }
 
 }  // namespace

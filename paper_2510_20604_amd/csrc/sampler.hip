@@ -13,8 +13,9 @@
 // step of some lane's work instead of parking lanes that finished a phase early.
 // wilson_team: W lanes of one wave grow one tree together (below); used for large graphs,
 // whose per-tree state limits how many trees can be in flight.
-// A third (pop.hpp, cycle_pop) pops every cycle of the current arrows at once, round by round,
-// in LDS: the automatic choice for small-world graphs of up to kPopMaxNodes nodes.
+// Two more pop the cycles of the current arrows in rounds, a work-group per tree: cycle_pop
+// (pop.hpp), the automatic choice for small-world graphs of up to kPopMaxNodes nodes, and mesh_pop
+// (tokens.hpp), for meshes.
 //
 // RandomNeighbor(u) at the k-th departure from u in sample i of graph word g is
 // Philox4x32-10((k, u, i, g), seed).  A node's successive choices are therefore fixed in
@@ -22,6 +23,7 @@
 // run (cycle popping), so results match the serial order of Algorithm 3 exactly.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <numeric>
@@ -33,6 +35,7 @@
 #include "device.hpp"
 #include "walk.hpp"
 #include "pop.hpp"
+#include "tokens.hpp"
 
 namespace rwc {
 
@@ -101,6 +104,9 @@ __global__ void init_state(const GraphArgs* __restrict__ graphs, const int64_t* 
     }
 }
 
+// Work queues: [0] HBM-state walk, [1] LDS-state walk, [2 + c] cycle popping class c.
+constexpr int kQueues = 8;
+
 // First kernel of a call: clears the outputs (unless accumulating), the root bitmap and the
 // work queue, and starts the workspace header.
 __global__ void zero_outputs(uint64_t* counts, uint64_t* counts_sq, int64_t total_nodes, uint64_t* total_steps,
@@ -116,8 +122,7 @@ __global__ void zero_outputs(uint64_t* counts, uint64_t* counts_sq, int64_t tota
         if (total_steps) total_steps[i] = 0;
     if (tid == 0) {
         header_begin(header);
-        queue[0] = 0;
-        queue[1] = 0;
+        for (int i = 0; i < kQueues; ++i) queue[i] = 0;
     }
 }
 
@@ -194,6 +199,19 @@ __global__ void reduce_batch(const GraphArgs* __restrict__ graphs, const int64_t
 }
 
 // ---------------------------------------------------------------------- planning ------
+// The graphs of a call that one launch of a cycle popping kernel takes: meshes by what their trees
+// take of the LDS (a launch's work-groups all have the largest's), then the others.
+enum : int { kPopWide = 0, kPopLarge, kPopMid, kPopSmall, kPopWorld, kPopClasses };
+
+struct PopClass {
+    int32_t first = 0, graphs = 0;   // in the order of the items
+    int threads = 0;
+    int32_t lds_words = 0;
+    int64_t grid = 0;
+    int64_t slot_words = 0;          // 4-byte words of a work-group's slot in the workspace
+    int32_t nmax = 0;
+};
+
 struct Plan {
     std::vector<int32_t> W, T, S;     // per graph: walkers per tree, tree slots, trees per wave
     std::vector<int64_t> stride;      // per graph: words per slot
@@ -203,10 +221,10 @@ struct Plan {
     int64_t lds_words = 0;            // dynamic LDS of the LDS-state kernel, in 8-byte words
     int32_t batches = 1;
     int32_t lds_graphs = 0;
-    bool pop = false;                 // every graph's trees are grown by cycle_pop
-    int64_t pop_slots = 0;            // cycle_pop: the most work-groups
-    int64_t pop_stride = 0;           // words of a work-group's count slot in HBM (0: counts in LDS)
-    int64_t pop_sums = 0;             // words of a work-group's visit sums in HBM (0: several graphs)
+    bool pop = false;                 // every graph's trees are grown by popping cycles in rounds,
+    std::vector<PopClass> classes;    // class by class
+    int64_t pop_words = 0;            // 4-byte words of their work-groups' slots
+    int64_t pop_sums = 0;             // 8-byte words of their visit sums (0: several graphs)
     bool team = false;                // some graph uses more than one walker per tree
     bool hbm_team = false;            // some graph with HBM state uses walker teams
 };
@@ -259,26 +277,50 @@ int auto_walkers(int64_t n) {
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
-// Whether cycle_pop grows the call's trees: an automatic plan (no walkers, trees in flight or path
-// ring asked for, and LDS state allowed) on graphs whose arrows fit 15 bits and whose walks are
-// short.  Measured against walker teams: 1.2 to 5 times faster (walk and reduction, ms: ER(300, 8)
-// x 2000 trees 0.93 -> 0.24, ER(1000, 8) x 2000 2.03 -> 0.67, BA(2000, 4) x 500 0.45 -> 0.13,
-// BA(20 000, 5) x 2000 3.76 -> 1.81, x 20 000 28.4 -> 15.7).  Above kPopLdsCounts nodes a graph
-// without hubs (largest degree under sqrt n) has long arrow paths and many rounds, which only
-// pays while a compute unit has few trees (ER(12 000, 8) x 500 trees 14.4 -> 8.3 ms, but x 2000
-// 16.4 -> 17.4 and x 20 000 50.7 -> 120).  Meshes (the test for spread starts) stay with the walker teams: their trees take
-// thousands of rounds of one cycle each (20 000-node grid: 2 975 rounds on average).
+int pop_class(const rwc_csr& g) {
+    if (g.bfs_depth <= kLongWalkDepth) return kPopWorld;
+    return g.n > kTokenLdsNodes     ? kPopWide
+           : g.n > kTokenMidNodes   ? kPopLarge
+           : g.n > kTokenSmallNodes ? kPopMid
+                                    : kPopSmall;
+}
+
+// Whether the call's trees are grown by popping cycles in rounds: an automatic plan (no walkers,
+// trees in flight or path ring asked for, and LDS state allowed), and graphs on which it pays.
+//
+// Small-world graphs (cycle_pop), measured against walker teams (walk and reduction): 1.2 to 5 times
+// faster (ER(300, 8) x 2000 trees 0.93 -> 0.24 ms, ER(1000, 8) x 2000 2.03 -> 0.67, BA(2000, 4)
+// x 500 0.45 -> 0.13, BA(20 000, 5) x 2000 3.76 -> 1.81, x 20 000 28.4 -> 15.7).  Above
+// kPopLdsCounts nodes a graph without hubs (largest degree under sqrt n) has long arrow paths and
+// many rounds, which only pays while a compute unit has few trees (ER(12 000, 8) x 500 trees
+// 14.4 -> 8.3 ms, but x 2000 16.4 -> 17.4 and x 20 000 50.7 -> 120).
+//
+// Meshes (mesh_pop): a tree takes about 20 sqrt n rounds, and as many trees run at once as the LDS
+// holds; walker teams take about 10 us a node for a tree (twice and more on unit weights), but
+// run 10 G steps/s, about 14 n steps a tree, once they fill the device.  So the rounds win while a
+// call has few trees of its large meshes, and always below 2048 nodes.
 bool pops_cycles(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) {
     if (p->walkers_per_tree != 0 || p->walkers_per_graph || p->trees_in_flight > 0) return false;
     if (p->flags & (RWC_SAMPLE_NO_LDS_STATE | RWC_SAMPLE_PATH_RING)) return false;
     if (p->num_samples > kLdsMaxSamples || p->num_samples * G > (int64_t{1} << 30)) return false;
+    const double cus = device_cu_count(), l = static_cast<double>(p->num_samples);
     const bool few = p->num_samples * G <= 4 * device_cu_count();
+    double rounds_us = 0.0, latest_us = 0.0, steps_us = 0.0;
     for (int32_t g = 0; g < G; ++g) {
-        if (graphs[g].n > kPopMaxNodes || graphs[g].bfs_depth > kLongWalkDepth) return false;
-        const bool hubs = static_cast<int64_t>(graphs[g].max_degree) * graphs[g].max_degree >= graphs[g].n;
-        if (graphs[g].n > kPopLdsCounts && !hubs && !few) return false;
+        const int64_t n = graphs[g].n;
+        const int c = pop_class(graphs[g]);
+        if (n > (c == kPopWorld ? kPopMaxNodes : kTokenMaxNodes)) return false;
+        if (c == kPopWorld) {
+            const bool hubs = static_cast<int64_t>(graphs[g].max_degree) * graphs[g].max_degree >= n;
+            if (n > kPopLdsCounts && !hubs && !few) return false;
+        } else if (c != kPopSmall) {
+            const double tree_us = 20.0 * std::sqrt(static_cast<double>(n)) * (c == kPopWide ? 25.0 : 5.0);
+            rounds_us += tree_us * l / (cus * (c == kPopLarge ? 1.0 : 2.0));
+            latest_us = std::max(latest_us, 10.0 * n - 2.0 * tree_us);   // (a slow tree takes twice the rounds)
+            steps_us += 14.0 * n * l / 1e4;
+        }
     }
-    return true;
+    return rounds_us <= std::max(latest_us, steps_us);
 }
 
 // Threads of a cycle_pop work-group.  A round is a chain of barriers and LDS latencies, so while the
@@ -314,6 +356,7 @@ int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan
     // the device (256 mixed graphs: the batch autotuner picks HBM state), so a call uses LDS
     // state only when every graph's trees fit.
     plan->pop = pops_cycles(graphs, G, p);
+    plan->classes.assign(plan->pop ? kPopClasses : 0, PopClass{});
     bool all_fit = plan->pop || (!(p->flags & RWC_SAMPLE_NO_LDS_STATE) && l <= kLdsMaxSamples);
     for (int32_t g = 0; g < G && all_fit && !plan->pop; ++g) {
         const int Wg = p->walkers_per_graph ? p->walkers_per_graph[g]
@@ -343,8 +386,17 @@ int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan
             plan->T[g] = 0;
             ++plan->lds_graphs;
             if (plan->pop) {
-                plan->lds_words = std::max<int64_t>(plan->lds_words, (PopLayout(graphs[g].n).words() + 1) / 2);
-                if (n > kPopLdsCounts) plan->pop_stride = std::max(plan->pop_stride, plan->stride[g]);
+                const int cl = pop_class(graphs[g]);
+                PopClass& c = plan->classes[cl];
+                ++c.graphs;
+                c.nmax = std::max(c.nmax, graphs[g].n);
+                const int32_t words =
+                    cl == kPopWorld ? PopLayout(graphs[g].n).words() : TokenLayout(graphs[g].n).words();
+                c.lds_words = std::max(c.lds_words, words);
+                const int64_t slot = cl == kPopWide    ? 3 * plan->stride[g]
+                                     : cl != kPopWorld ? plan->stride[g]
+                                                       : (n > kPopLdsCounts ? plan->stride[g] : 0);
+                c.slot_words = std::max(c.slot_words, slot);
             } else {
                 plan->lds_words = std::max<int64_t>(plan->lds_words, S * plan->stride[g]);
             }
@@ -353,11 +405,24 @@ int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan
         plan->hbm_team = plan->hbm_team || W > 1;
         state_words += T * plan->stride[g];
     }
-    if (plan->pop) {
-        // eight work-groups of 256 threads, or two of kPopMaxThreads, fill a compute unit
-        plan->pop_slots = std::min<int64_t>(l * G, (plan->pop_stride > 0 ? 2 : 8) * device_cu_count());
-        plan->pop_sums = G == 1 ? plan->stride[0] : 0;
+    int32_t first = 0;
+    int64_t most = 0;
+    for (int cl = 0; cl < static_cast<int>(plan->classes.size()); ++cl) {
+        PopClass& c = plan->classes[cl];
+        c.first = first;
+        first += c.graphs;
+        if (c.graphs == 0) continue;
+        c.threads = cl == kPopWorld   ? pop_threads(c.nmax, l * c.graphs)
+                    : cl == kPopSmall ? 256
+                    : cl == kPopMid   ? 512
+                                      : kTokenThreads;
+        // as many work-groups as a compute unit's 160 KB of LDS (1 KB of it fixed) and 32 waves hold
+        const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((160 * 1024) / (4 * c.lds_words + 1024), 2048 / c.threads));
+        c.grid = std::min<int64_t>(l * c.graphs, per_cu * device_cu_count());
+        plan->pop_words = std::max(plan->pop_words, c.grid * c.slot_words);
+        most = std::max(most, c.grid);
     }
+    if (plan->pop && G == 1) plan->pop_sums = most * 2 * plan->stride[0];
     const int64_t budget = (p->trees_in_flight <= 0) ? default_state_budget() : 0;
     if (p->trees_in_flight <= 0 && state_words * 8 > budget) {
         // shrink every graph's slots by the same factor to fit the automatic budget
@@ -388,7 +453,7 @@ struct SampleLayout {
     uint32_t* rootmask;
     int64_t mask_words;
     uint32_t* cover;   // [n0] components holding a root (graphs of several components)
-    uint32_t* pop_counts;   // departure counts of cycle_pop's work-groups
+    uint32_t* pop_slots;    // slots of the cycle popping kernels' work-groups
     uint64_t* pop_sums;     // their visit sums
     size_t total;
 };
@@ -419,13 +484,13 @@ SampleLayout carve_sample(void* ws, int32_t G, const Plan& plan, int32_t n0, int
     L.graphs = c.take<GraphArgs>(G);
     L.node_off = c.take<int64_t>(G + 1);
     L.items = c.take<Item>(max_items(G, plan, l));
-    L.queue = c.take<uint32_t>(2);   // [0] HBM-state walk, [1] LDS-state walk
+    L.queue = c.take<uint32_t>(kQueues);
     // root bitmap of graph 0 (an explicit root set is for single-graph calls)
     L.mask_words = (static_cast<int64_t>(n0) + 31) / 32;
     L.rootmask = c.take<uint32_t>(L.mask_words);
     L.cover = c.take<uint32_t>(n0);
-    L.pop_counts = c.take<uint32_t>(static_cast<size_t>(plan.pop_slots) * plan.pop_stride);
-    L.pop_sums = c.take<uint64_t>(static_cast<size_t>(plan.pop_slots) * 2 * plan.pop_sums);
+    L.pop_slots = c.take<uint32_t>(plan.pop_words);
+    L.pop_sums = c.take<uint64_t>(plan.pop_sums);
     L.total = c.used();
     return L;
 }
@@ -502,14 +567,20 @@ struct Setup {
     bool ring = false, lds_ring = false;
     WalkKernel walk = nullptr;
     LdsKernel walk_lds = nullptr;
-    PopKernel pop = nullptr;
-    int pop_block = 0;
-    int32_t pop_walk_share = 0;
     int grid_persistent = 0;
     int32_t nit_hbm = 0, nit_lds = 0, grid_lds = 0;
     size_t lds_bytes = 0;
     SampleLayout L;
 };
+
+PopKernel pop_kernel(int cl, const PopClass& c, bool strat) {
+    if (cl != kPopWorld) return strat ? mesh_pop_strata : mesh_pop;
+    if (c.nmax <= 2 * c.threads) return strat ? cycle_pop_strata<2> : cycle_pop<2>;
+    if (c.nmax <= 4 * c.threads) return strat ? cycle_pop_strata<4> : cycle_pop<4>;
+    if (c.nmax <= 8 * c.threads) return strat ? cycle_pop_strata<8> : cycle_pop<8>;
+    if (c.nmax <= 16 * c.threads) return strat ? cycle_pop_strata<16> : cycle_pop<16>;
+    return strat ? cycle_pop_strata<32> : cycle_pop<32>;
+}
 
 int make_setup(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, void* ws, Setup* S) {
     Plan& plan = S->plan;
@@ -590,12 +661,13 @@ int make_setup(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, voi
         if (!plan.lds[g])
             for (int32_t s0 = 0; s0 < plan.T[g]; s0 += plan.S[g]) S->items.push_back(Item{g, s0});
     S->nit_hbm = static_cast<int32_t>(S->items.size());
+    for (int c = 0; c < static_cast<int>(plan.classes.size()); ++c)
+        for (int32_t g : order)
+            if (pop_class(graphs[g]) == c) S->items.push_back(Item{g, 0});
     for (int32_t g : order)
-        if (plan.pop)
-            S->items.push_back(Item{g, 0});
-        else if (plan.lds[g])
+        if (plan.lds[g] && !plan.pop)
             for (int64_t s0 = 0; s0 < l; s0 += plan.S[g]) S->items.push_back(Item{g, static_cast<int32_t>(s0)});
-    S->nit_lds = static_cast<int32_t>(S->items.size()) - S->nit_hbm;
+    S->nit_lds = plan.pop ? 0 : static_cast<int32_t>(S->items.size()) - S->nit_hbm;
     const bool hbm_team = plan.hbm_team || (plan.team && S->nit_hbm == 0);
     const bool strat = p->strata >= 2;
     if (strat)
@@ -612,31 +684,7 @@ int make_setup(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, voi
         if (per_cu < 1) per_cu = 1;
         S->grid_persistent = per_cu * device_cu_count();
     }
-    if (plan.pop) {
-        S->lds_bytes = static_cast<size_t>(plan.lds_words) * 8;
-        int32_t nmax = 0;
-        for (int32_t g = 0; g < G; ++g) nmax = std::max(nmax, graphs[g].n);
-        S->pop_block = pop_threads(nmax, p->num_samples * G);
-        if (nmax <= 2 * S->pop_block)
-            S->pop = strat ? cycle_pop_strata<2> : cycle_pop<2>;
-        else if (nmax <= 4 * S->pop_block)
-            S->pop = strat ? cycle_pop_strata<4> : cycle_pop<4>;
-        else if (nmax <= 8 * S->pop_block)
-            S->pop = strat ? cycle_pop_strata<8> : cycle_pop<8>;
-        else if (nmax <= 16 * S->pop_block)
-            S->pop = strat ? cycle_pop_strata<16> : cycle_pop<16>;
-        else
-            S->pop = strat ? cycle_pop_strata<32> : cycle_pop<32>;
-        // Following only the changed nodes' paths pays where a thread would double many nodes'
-        // arrows (BA(20 000, 5), 2000 trees: 4.07 -> 2.40 ms; BA(8000, 5): 1.21 -> 1.12 ms, but
-        // ER(8000, 8), whose paths are long: 7.7 -> 8.6 ms).
-        S->pop_walk_share = nmax > kPopLdsCounts ? 16 : 0;
-        int per_cu = 0;
-        RWC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, S->pop, S->pop_block, S->lds_bytes));
-        if (per_cu < 1) per_cu = 1;
-        int64_t grid = static_cast<int64_t>(per_cu) * device_cu_count();
-        S->grid_lds = static_cast<int32_t>(std::min(grid, plan.pop_slots));
-    } else if (S->nit_lds > 0) {
+    if (S->nit_lds > 0) {
         if (strat)
             S->walk_lds = S->lds_ring ? static_cast<LdsKernel>(wilson_team_lds_strata<true>)
                                       : static_cast<LdsKernel>(wilson_team_lds_strata<false>);
@@ -842,17 +890,26 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
                         ++ldumps.count;
                     }
                 if (plan.pop) {
-                    const PopArgs args{L.graphs,      L.items,         G,          L.queue + 1,      p->sample_begin,
-                                       l,             p->seed,         L.node_off, L.pop_counts,     plan.pop_stride,
-                                       plan.pop_sums > 0 ? L.pop_sums : nullptr, plan.pop_sums,
-                                       out->counts,   out->counts_sq,  out->parents, out->tree_hash, out->total_steps,
-                                       status,        S.pop_walk_share};
-                    hipLaunchKernelGGL(S.pop, dim3(S.grid_lds), dim3(S.pop_block), S.lds_bytes, ls, args, ldumps);
-                    if (plan.pop_sums > 0)
-                        hipLaunchKernelGGL(pop_reduce,
-                                           dim3(blocks_for(graphs[0].n, 256), blocks_for(S.grid_lds, kPopSlots)), dim3(256),
-                                           0, ls, L.pop_sums, plan.pop_sums, S.grid_lds, graphs[0].n, graphs[0].node_id,
-                                           out->counts, out->counts_sq);
+                    for (int c = 0; c < kPopClasses; ++c) {
+                        const PopClass& pc = plan.classes[c];
+                        if (pc.graphs == 0) continue;
+                        // Following only the changed nodes' paths pays where a thread would double many
+                        // nodes' arrows (BA(20 000, 5), 2000 trees: 4.07 -> 2.40 ms; BA(8000, 5):
+                        // 1.21 -> 1.12 ms, but ER(8000, 8), whose paths are long: 7.7 -> 8.6 ms).
+                        const int32_t walk_share = pc.nmax > kPopLdsCounts ? 16 : 0;
+                        const PopArgs args{L.graphs, L.items + pc.first, pc.graphs, L.queue + 2 + c, p->sample_begin,
+                                           l, p->seed, L.node_off, L.pop_slots, pc.slot_words,
+                                           plan.pop_sums > 0 ? L.pop_sums : nullptr,
+                                           plan.pop_sums > 0 ? plan.stride[0] : int64_t{0}, out->counts, out->counts_sq,
+                                           out->parents, out->tree_hash, out->total_steps, status, walk_share};
+                        hipLaunchKernelGGL(pop_kernel(c, pc, p->strata >= 2), dim3(static_cast<unsigned>(pc.grid)),
+                                           dim3(pc.threads), static_cast<size_t>(pc.lds_words) * 4, ls, args, ldumps);
+                        if (plan.pop_sums > 0)
+                            hipLaunchKernelGGL(pop_reduce,
+                                               dim3(blocks_for(graphs[0].n, 256), blocks_for(pc.grid, kPopSlots)), dim3(256),
+                                               0, ls, L.pop_sums, plan.stride[0], static_cast<int32_t>(pc.grid), graphs[0].n,
+                                               graphs[0].node_id, out->counts, out->counts_sq);
+                    }
                 } else {
                     hipLaunchKernelGGL(S.walk_lds, dim3(S.grid_lds), dim3(kWave), S.lds_bytes, ls, L.graphs,
                                        L.items + S.nit_hbm, S.nit_lds, L.queue + 1, p->sample_begin, l, p->seed,
@@ -956,7 +1013,8 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
         out->plan[0] = plan.W[0];
         out->plan[1] = plan.T[0];
         out->plan[2] = plan.batches;
-        out->plan[3] = plan.pop ? 5 : plan.lds[0] ? (S.lds_ring ? 4 : 3) : (!plan.team ? 0 : (S.ring ? 2 : 1));
+        out->plan[3] = plan.pop      ? (pop_class(graphs[0]) == kPopWorld ? 5 : 6)
+                       : plan.lds[0] ? (S.lds_ring ? 4 : 3) : (!plan.team ? 0 : (S.ring ? 2 : 1));
         out->plan[4] = S.hg[0].spread;
         out->plan[5] = S.hg[0].order != nullptr ? 1 : 0;
         out->plan[6] = replayed;

@@ -1,7 +1,8 @@
 """The cycle-popping kernel (trees popped round by round in LDS) against the serial oracle, bit for
 bit: counts in LDS and in the workspace (above 8192 nodes), the last size it takes, work-group
 sizes, rounds that change more nodes than a list holds, deep rounds (two cliques joined by one
-edge), root sets, stratified entries, batches, and the calls that keep the walker teams."""
+edge), root sets, stratified entries, batches, the same for the kernel of the meshes, and the calls
+that keep the walker teams."""
 import numpy as np
 import pytest
 
@@ -81,13 +82,72 @@ def test_cycle_pop_root_sets_and_batches():
         off += x.n
 
 
+def _rect(a, b):
+    ids = np.arange(a * b).reshape(a, b)
+    src = np.concatenate([ids[:, :-1].ravel(), ids[:-1].ravel()])
+    dst = np.concatenate([ids[:, 1:].ravel(), ids[1:].ravel()])
+    return G.graphs.EdgeList(a * b, src.astype(np.int32), dst.astype(np.int32), None)
+
+
+def _mesh(name):
+    if name == "path":
+        return G.path_graph(150)
+    if name == "tail":           # hubs, and a path that makes the graph deep
+        g, k = G.barabasi_albert(3000, 4, 1), 40
+        src = np.concatenate([g.src, [0], np.arange(g.n, g.n + k - 1)])
+        dst = np.concatenate([g.dst, [g.n], np.arange(g.n + 1, g.n + k)])
+        return G.graphs.EdgeList(g.n + k, src.astype(np.int32), dst.astype(np.int32), None)
+    return _rect(*(int(x) for x in name.split("x")))
+
+
+# the classes' edges (2048, 8000 and 20 500 nodes; above, the tree's words are in the workspace), with
+# 9 to 13 bits of round in a word (a sweep over all nodes every 2^bits rounds), the last word of the bitmaps whole and not
+@pytest.mark.parametrize("name,l,weighted,strata", [
+    ("path", 40, False, 0), ("tail", 30, False, 0), ("3x113", 60, True, 64), ("32x64", 30, False, 0), ("3x683", 6, True, 0),
+    ("50x160", 12, True, 0), ("53x151", 8, False, 32), ("100x205", 8, False, 0), ("59x349", 8, True, 32), ("180x182", 6, False, 0),
+    ("256x257", 4, True, 0)])
+def test_mesh_pop_is_bit_exact(name, l, weighted, strata):
+    g = _mesh(name)
+    if weighted:
+        g = g.with_weights(G.uniform_weights(g.m, 0.5, 2.0, 9))
+    Gd = P.Graph(g.n, g.src, g.dst, g.w)
+    o = W.OracleCSR(g.n, g.src, g.dst, g.w)
+    ref = W.fastwalk_sample(o, o.pivot, 4001, 0, 2, l, want_parents=True, threads=8, strata=strata)
+    s = P.sample_forests(Gd, l, 4001, sample_begin=2, dump=[2, l + 1], strata=strata)
+    assert s["walk_kernel"] == ("mesh_pop_strata" if strata else "mesh_pop") and s["lds_graphs"] == 1
+    _check(s, ref, l)
+
+
+def test_mesh_pop_root_sets_and_mixed_batches():
+    g = _rect(90, 91)
+    Gd = P.Graph(g.n, g.src, g.dst)
+    S = [5, 4100, 8189]
+    ref = W.fastwalk_sample(W.OracleCSR(g.n, g.src, g.dst), S, 5, 0, 0, 12, want_parents=True, threads=8)
+    s = P.sample_forests(Gd, 12, 5, roots=S, dump=[0, 11])
+    assert s["walk_kernel"] == "mesh_pop"
+    _check(s, ref, 12)
+    graphs = [_rect(40, 45), G.barabasi_albert(2000, 4, 2), _rect(150, 151), g, _rect(60, 61), G.erdos_renyi_lcc(200, 6, 1)]
+    dev = [P.Graph(x.n, x.src, x.dst) for x in graphs]
+    for _ in range(2):           # the second call replays the captured launches
+        b = P.sample_forests(dev, 10, 17, persistent=True, capture=True)
+        assert b["walk_kernel"] == "mesh_pop" and b["lds_graphs"] == 6
+        off = 0
+        for i, x in enumerate(graphs):
+            r = W.fastwalk_sample(W.OracleCSR(x.n, x.src, x.dst), dev[i].pivot, 17, i, 0, 10, threads=8)
+            np.testing.assert_array_equal(P.as_uint64(b["counts"])[off:off + x.n], r["visits"])
+            np.testing.assert_array_equal(P.as_uint64(b["tree_hash"][i]), r["hash"])
+            off += x.n
+
+
 def test_calls_that_keep_the_walker_teams():
     big = G.barabasi_albert(30001, 2, 3)
-    mesh = G.grid_with_deletions(1500, 0.1, 3)
+    mesh = G.grid_with_deletions(9000, 0.1, 3)   # too many trees for its size (below)
     small = G.erdos_renyi_lcc(300, 8, 1)
     er = G.erdos_renyi_lcc(8400, 8, 2)         # no hubs: counts in the workspace, and too many trees
     assert P.sample_forests(P.Graph(er.n, er.src, er.dst), 1400, 3, want_hash=False)["walk_kernel"] == "wilson_team<true>"
-    for g, kw in ((big, {}), (mesh, {}), (small, {"walkers_per_tree": 16}), (small, {"lds_state": False}),
+    s = P.sample_forests(P.Graph(mesh.n, mesh.src, mesh.dst), 20000, 3, want_hash=False, want_sq=False)
+    assert s["walk_kernel"] == "wilson_team<true>"
+    for g, kw in ((big, {}), (mesh, {"lds_state": False}), (small, {"walkers_per_tree": 16}), (small, {"lds_state": False}),
                   (small, {"trees_in_flight": 8}), (small, {"path_ring": True})):
         s = P.sample_forests(P.Graph(g.n, g.src, g.dst), 8, 3, **kw)
         assert s["walk_kernel"].startswith("wilson_team"), kw
