@@ -17,8 +17,7 @@
 // column u the later columns of its window with a factor entry (the inverse).  IChol has two
 // forms with the same result:
 //   - dense (the default while the matrix's packed lower triangle fits): right-looking on that
-//     triangle in HBM; launch k forms column k + 1 of R on 16 workgroups while the others subtract
-//     R(i, k) R(j, k) for step k's kept pairs, one launch per step;
+//     triangle in HBM, in panels of 32 columns, one launch per panel;
 //   - chain: left-looking on one wave, sparse throughout, for any size.
 // The inverse's columns form a shallow dependency DAG, which eight waves of one workgroup run,
 // each column on one wave with its lanes over the column's entries.
@@ -26,6 +25,7 @@
 // entry's updates in ascending k, norms and tails summed one entry at a time, sorts by total
 // orders), so the factor, S~ and tau~ are the serial ones bit for bit.
 #include <algorithm>
+#include <utility>
 
 #include "common.hpp"
 #include "device.hpp"
@@ -75,14 +75,15 @@ struct FcArgs {
     double* dense;      // dense IChol: the lower triangle of S, packed by columns (column j holds
                         // rows j .. N - 1 from packed_column(j, N))
     double* colnorm;    // dense IChol: ||A(j:N, j)||_1 per column
-    double* xk;         // dense IChol: R(i, j) of the last column j that kept row i ...
-    int32_t* xstamp;    // ... and that j (-1 before any)
-    int32_t* stage_row; // dense IChol, two columns by parity: each forming workgroup's kept
-    double* stage_val;  // entries (rows ascending), stage_cap per workgroup ...
-    uint32_t* stage_cnt;  // ... their counts [2][kFormGroups] ...
-    double* stage_piv;    // ... the pivot [2] ...
-    int32_t* stage_first; // ... and whether row j + 1 was kept [2]
-    int64_t stage_cap;
+    // dense IChol, two panels by parity: rows' entries R(i, J .. J + kPanel - 1) (dropped ones 0) ...
+    double* prow;        // [2][N][kPanel]
+    uint32_t* pmask;     // [2][N] which were kept
+    double* pnext;       // [2][kPanel][kPanel] those of the next panel's rows, by column
+    int32_t* act;        // [2][parts * kPanelRows] the rows below the panel with a kept entry, part by part
+    uint32_t* act_cnt;   // [2][parts]
+    uint32_t* act_skip;  // [2] how many of them are the next panel's
+    uint32_t* col_cnt;   // [2][parts][kPanel] kept entries per column
+    int32_t parts;
     double* tau;        // [n] output by input id
     WsHeader* header;
     int64_t* counters;  // [2]: entries of R and of S~
@@ -421,22 +422,28 @@ __global__ void __launch_bounds__(kWave) fc_ichol(FcArgs A) {
     if (lane == 0) A.counters[0] = rp;
 }
 
-// ---- IChol, dense right-looking ----
-// S starts as the lower triangle of calL_v.  Step k takes column k of S after steps 0..k-1: its
-// pivot and the entries that pass the drop rule become column k of R, and every kept pair
-// i >= j loses R(i, k) R(j, k) from S(i, j).  Each S(i, j) meets its updates in ascending k, as
-// in the left-looking chain, so the two forms give the same factor bit for bit.
+// ---- IChol, dense right-looking, in panels ----
+// S starts as the lower triangle of calL_v, and every entry S(i, j) loses its products R(i, k)
+// R(j, k) in ascending k, as in the left-looking chain, so the two forms give the same factor bit
+// for bit.  A panel of kPanel columns is formed at once: its diagonal block is factored by one
+// wave, column after column, and every row below then takes its kPanel entries by itself (a
+// triangular solve with the drop rule), a thread per row.  Launch p forms panel p + 1, applying
+// panel p's products to its columns as it reads them, while other workgroups subtract panel p's
+// products from the columns to the right and others copy panel p into the compact factor.
 //
-// Launch k forms column k + 1 of R on kFormGroups workgroups, each over a contiguous range of its
-// rows, into a staging area (two columns, by parity); the other workgroups apply step k's pairs,
-// reading column k from the staging area, and one of them copies it, in row order, into the
-// compact factor.
-constexpr int kDenseBlock = 1024;
-constexpr int kDenseWaves = kDenseBlock / kWave;
-constexpr int kFormGroups = 16;   // workgroups forming a column
-constexpr int kFormRows = 4;      // rows per thread in one round of a workgroup's range
-constexpr int kDenseGrid = 256;   // workgroups of a launch
-constexpr int kDenseItems = 4;    // (column, 64-row chunk) items a wave loads at once
+// What bounds it: a launch's serial part (read and apply 18 us, 32 dependent columns of the diagonal
+// block 11, 32 of the rows' solves 11) up to about 10 000 columns, then the updates' reads and writes
+// of S.  Against a launch per column, each column's products applied as soon as it was formed (all of
+// IChol, ms): BA(5000, 5) 46 -> 8.5, BA(20 000, 5) 219 -> 96, 10 000-node grid 92 -> 25; the whole call
+// on BA(60 000, 5) 772 -> 576.
+constexpr int kPanel = 32;
+constexpr int kPanelRows = 256;                      // rows (threads) of a forming or copying workgroup
+constexpr int kPanelBlock = kPanelRows + kWave;      // and a wave for the diagonal block
+constexpr int kPanelWaves = kPanelBlock / kWave;
+constexpr int kTile = 64;                            // active rows and columns of an update's tile
+constexpr int kTilePitch = kPanel + 1;               // the last entry 0; odd: rows in different banks
+constexpr int kTileCols = (kTile + kPanelWaves - 1) / kPanelWaves;   // columns of a wave
+constexpr int kMaxParts = 4096;                      // kDenseMaxColumns / kPanelRows
 
 // Offset of column j in the packed lower triangle of an N x N matrix (columns of N - j rows).
 __host__ __device__ __forceinline__ int64_t packed_column(int64_t j, int64_t N) { return j * N - j * (j - 1) / 2; }
@@ -461,7 +468,6 @@ __global__ void __launch_bounds__(256) fc_dense_scatter(FcArgs A) {
         double* Sj = A.dense + (packed_column(j, N) - j);   // Sj[i], i >= j
         if (lane == 0) {
             Sj[j] = 1.0;
-            A.xstamp[j] = -1;
         }
         double colnorm = 1.0;
         for (int32_t b0 = beg; b0 < end; b0 += kWave) {
@@ -487,196 +493,371 @@ __global__ void __launch_bounds__(256) fc_dense_scatter(FcArgs A) {
     }
 }
 
-// Part p of column j of R.  Step j - 1's update of column j (the pairs (i, j) with R(j, j-1) != 0)
-// is applied here, on the loaded values, and never stored: nothing reads column j of S
-// afterwards.  xk/xstamp give R(i, j-1) by row.  The pivot is sqrt(S(j, j)); this workgroup's
-// rows i (a contiguous range of j + 1 .. N - 1) whose x = S(i, j) / pivot is nonzero with
-// |x| >= droptol colnorm[j] go, ascending, to its staging slots, and become xk/xstamp for column
-// j + 1.  Rows are read q-major: round r, slot q, thread t reads row base + q * kDenseBlock + t.
-__device__ void form_part(const FcArgs& A, int32_t j, int p, uint32_t* counts /* [kFormRows][kDenseWaves] */) {
-    const int64_t N = A.N;
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    const double* Sj = A.dense + (packed_column(j, N) - j);   // Sj[i], i >= j
-    const int64_t M = N - 1 - j;
-    const int64_t R = (M + kFormGroups - 1) / kFormGroups;
-    const int64_t lo = j + 1 + p * R;
-    const int64_t hi = lo + R < N ? lo + R : N;
-    const int par = j & 1;
-    int32_t* srow = A.stage_row + (static_cast<int64_t>(par) * kFormGroups + p) * A.stage_cap;
-    double* sval = A.stage_val + (static_cast<int64_t>(par) * kFormGroups + p) * A.stage_cap;
-    double wjj = Sj[j];
-    const int32_t xsj = A.xstamp[j];
-    const double xkj = A.xk[j];
-    const double thr = A.droptol * A.colnorm[j];
-    const bool upd = j > 0 && xsj == j - 1;
-    const double x0 = upd ? xkj : 0.0;   // R(j, j - 1), 0 when column j - 1 dropped row j
-    if (upd) wjj = wjj - x0 * x0;
-    const bool bad = !(wjj > 0.0);
-    const double piv = sqrt(wjj);
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-    uint32_t kept = 0;
-    bool first_kept = false;
-    for (int64_t base = lo; base < hi; base += static_cast<int64_t>(kDenseBlock) * kFormRows) {
-        double xv[kFormRows], xo[kFormRows];
-        int32_t xs[kFormRows];
-#pragma unroll
-        for (int q = 0; q < kFormRows; ++q) {
-            const int64_t i = base + q * kDenseBlock + threadIdx.x;
-            const int64_t ic = i < hi ? i : j;   // a valid address for every thread
-            xv[q] = Sj[ic];
-            xs[q] = A.xstamp[ic];
-            xo[q] = A.xk[ic];
-        }
-        if (bad) break;   // uniform
-        uint64_t km[kFormRows];
-#pragma unroll
-        for (int q = 0; q < kFormRows; ++q) {
-            const int64_t i = base + q * kDenseBlock + threadIdx.x;
-            const double sv = upd && xs[q] == j - 1 ? xv[q] - xo[q] * x0 : xv[q];
-            xv[q] = i < hi ? sv / piv : 0.0;
-            const bool keep = i < hi && xv[q] != 0.0 && fabs(xv[q]) >= thr;
-            if (i == j + 1) first_kept = keep;
-            km[q] = __ballot(keep);
-            if (lane == 0) counts[q * kDenseWaves + wave] = static_cast<uint32_t>(__popcll(km[q]));
-        }
-        __syncthreads();
-        uint32_t at[kFormRows], round = 0;
-#pragma unroll
-        for (int q = 0; q < kFormRows; ++q) {
-            uint32_t before = 0, all = 0;
-            for (int w = 0; w < kDenseWaves; ++w) {
-                const uint32_t c = counts[q * kDenseWaves + w];
-                before += w < wave ? c : 0;
-                all += c;
-            }
-            at[q] = kept + round + before;
-            round += all;
-        }
-#pragma unroll
-        for (int q = 0; q < kFormRows; ++q) {
-            if ((km[q] >> lane) & 1ull) {
-                const uint32_t pos = at[q] + static_cast<uint32_t>(__popcll(km[q] & below));
-                const int32_t i = static_cast<int32_t>(base + q * kDenseBlock + threadIdx.x);
-                srow[pos] = i;
-                sval[pos] = xv[q];
-                A.xk[i] = xv[q];   // this thread read row i's previous xk / xstamp above
-                A.xstamp[i] = j;
-            }
-        }
-        kept += round;
-        __syncthreads();   // counts are rewritten by the next round
+// A row of kPanel values that every lane needs: lane l holds values l % 16 and 16 + l % 16, and each
+// value is broadcast within the rows of 16 lanes by one DPP move (from LDS, a wave's broadcast of
+// 16 bytes takes eight cycles of the one port that all waves share: BA(20 000, 5)'s call took 151 ms
+// instead of 115, with 166 registers instead of 126).
+struct Spread {
+    double lo, hi;
+    __device__ __forceinline__ void load(const double* row) {
+        const int l = threadIdx.x & 15;
+        lo = row[l];
+        hi = row[16 + l];
     }
-    if (bad) {
-        if (p == 0 && threadIdx.x == 0) atomicOr(&A.header->status, static_cast<uint32_t>(kErrPivot));
-        return;
-    }
-    if (threadIdx.x == 0) A.stage_cnt[par * kFormGroups + p] = kept;
-    if (p == 0 && threadIdx.x == 0) {
-        A.stage_piv[par] = piv;
-        A.stage_first[par] = first_kept ? 1 : 0;   // thread 0 of part 0 holds row j + 1
-    }
-}
-
-// The staged column k: entry a of its kept rows (ascending) from the parts' counts.
-struct Staged {
-    uint32_t pre[kFormGroups + 1];
-    const int32_t* row;
-    const double* val;
-    int64_t cap;
-    __device__ __forceinline__ int64_t slot(int32_t a) const {
-        int p = 0;
-#pragma unroll
-        for (int q = 1; q < kFormGroups; ++q) p += static_cast<uint32_t>(a) >= pre[q] ? 1 : 0;
-        return p * cap + (a - static_cast<int32_t>(pre[p]));
+    template <int kAt>
+    __device__ __forceinline__ double get() const {
+        const int64_t x = __builtin_bit_cast(int64_t, kAt < 16 ? lo : hi);
+        const int64_t r = __builtin_amdgcn_update_dpp(x, x, 0x150 + (kAt & 15), 0xf, 0xf, true);   // row_newbcast
+        return __builtin_bit_cast(double, r);
     }
 };
 
-// Launch k: workgroups 0 .. kFormGroups-1 form column k + 1; the others subtract R(i, k) R(j, k)
-// from S(i, j) for the kept pairs of column k, except in column k + 1 (which the forming
-// workgroups update as they read it), and the first of them copies column k into the factor.
-__global__ void __launch_bounds__(kDenseBlock) fc_dense_step(FcArgs A, int32_t k) {
-    __shared__ uint32_t counts[kFormRows * kDenseWaves];
-    const int64_t N = A.N;
-    // Forming a column reads no status (its barriers need every wave of the workgroup; after an
-    // error it only fills the staging area, which nothing uses); the other workgroups, which
-    // have no barriers, stop once an earlier launch or this one has reported one.
-    if (blockIdx.x < kFormGroups) {
-        if (k + 1 < N) form_part(A, k + 1, blockIdx.x, counts);
-        return;
+// s[b] = s[b + kDown] - a row[b + kDown] for b < kCount - kDown.  Eight at a time, phase by phase: left
+// to the compiler each product waits for the one before (they share its registers).
+template <int kDown, int kFirst, int... kAt>
+__device__ __forceinline__ void subtract_some(double* s, double a, const Spread& row, std::integer_sequence<int, kAt...>) {
+    double x[sizeof...(kAt)] = {row.get<kFirst + kAt + kDown>()...};
+    __builtin_amdgcn_sched_barrier(0);
+    ((x[kAt] = a * x[kAt]), ...);
+    __builtin_amdgcn_sched_barrier(0);
+    ((s[kFirst + kAt] = s[kFirst + kAt + kDown] - x[kAt]), ...);
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <int kDown, int kCount, int kFirst = 0>
+__device__ __forceinline__ void subtract(double* s, double a, const Spread& row) {
+    constexpr int kNow = kCount - kDown - kFirst < 8 ? kCount - kDown - kFirst : 8;
+    subtract_some<kDown, kFirst>(s, a, row, std::make_integer_sequence<int, kNow>{});
+    if constexpr (kFirst + kNow < kCount - kDown) subtract<kDown, kCount, kFirst + kNow>(s, a, row);
+}
+
+// Steps j0 .. j0 + 7 of the diagonal block's factorisation, a row per lane, and of a row's solve.
+// s[b] is the row's entry in column j + b: a step takes s[0] and moves the others down by one, so
+// that the loop is short code on registers.  D[j][b] = R(J + j + b, J + j), 0 past the block's last
+// row; kLeft = kPanel - j0 columns are left at the first step.
+constexpr int kSteps = 8;
+
+template <int kLeft>
+__device__ __forceinline__ bool factor_steps(double* s, double* D, double thr, int lane, int nb) {
+    bool fine = true;
+    const int last = nb < kPanel - kLeft + kSteps ? nb : kPanel - kLeft + kSteps;
+    for (int j = kPanel - kLeft; j < last; ++j) {
+        const double wjj = lane_value(s[0], j);
+        fine = fine && wjj > 0.0;
+        const double piv = sqrt(wjj);
+        double x = s[0] / piv;
+        x = lane > j && lane < nb && x != 0.0 && fabs(x) >= lane_value(thr, j) ? x : 0.0;
+        if (lane >= j && lane < j + kPanel) D[j * kPanel + lane - j] = lane == j ? piv : x;
+        wave_order();
+        Spread d;
+        d.load(D + j * kPanel);
+        subtract<1, kLeft>(s, x, d);
     }
-    if (__hip_atomic_load(&A.header->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-    const int par = k & 1;
-    Staged st;
-    st.pre[0] = 0;
-#pragma unroll
-    for (int q = 0; q < kFormGroups; ++q) st.pre[q + 1] = st.pre[q] + A.stage_cnt[par * kFormGroups + q];
-    st.row = A.stage_row + static_cast<int64_t>(par) * kFormGroups * A.stage_cap;
-    st.val = A.stage_val + static_cast<int64_t>(par) * kFormGroups * A.stage_cap;
-    st.cap = A.stage_cap;
-    const int32_t c = static_cast<int32_t>(st.pre[kFormGroups]);   // kept entries below the pivot
-    if (blockIdx.x == kFormGroups) {
-        // column k of the factor: the pivot, then the kept rows ascending
-        const int64_t rp = A.r_ptr[k];
-        if (rp + 1 + c > A.r_cap) {
-            if (threadIdx.x == 0) atomicOr(&A.header->status, static_cast<uint32_t>(kErrCapacity));
-            return;
-        }
-        for (int32_t a = threadIdx.x; a < c; a += kDenseBlock) {
-            const int64_t sl = st.slot(a);
-            A.r_row[rp + 1 + a] = st.row[sl];
-            A.r_val[rp + 1 + a] = st.val[sl];
-        }
-        if (threadIdx.x == 0) {
-            A.r_row[rp] = k;
-            A.r_val[rp] = A.stage_piv[par];
-            A.r_ptr[k + 1] = rp + 1 + c;
-            A.counters[0] = rp + 1 + c;
-        }
+    if constexpr (kLeft > kSteps) fine = factor_steps<kLeft - kSteps>(s, D, thr, lane, nb) && fine;
+    return fine;
+}
+
+// take(j, x, keep) may replace the entry and the decision.
+template <int kLeft, class Take>
+__device__ __forceinline__ void solve_steps(double* s, const double* D, const double* thr_of, int nb, Take&& take) {
+    const int last = nb < kPanel - kLeft + kSteps ? nb : kPanel - kLeft + kSteps;
+    for (int j = kPanel - kLeft; j < last; ++j) {
+        Spread d;
+        d.load(D + j * kPanel);
+        double x = s[0] / d.get<0>();
+        x = take(j, x, x != 0.0 && fabs(x) >= thr_of[j]);
+        subtract<1, kLeft>(s, x, d);
     }
-    const int32_t b_lo = A.stage_first[par];   // 1: row k + 1 was kept, column k + 1 is being formed
-    // columns b = b_lo .. c-1 in items (h, b): rows a in [b + 64 h, min(b + 64 h + 64, c)).
-    // Items are numbered h-major: chunk h has the c - b_lo - 64 h columns b < c - 64 h.
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t gw = static_cast<int64_t>(blockIdx.x - kFormGroups) * kDenseWaves + threadIdx.x / kWave;
-    const int64_t nw = static_cast<int64_t>(gridDim.x - kFormGroups) * kDenseWaves;
-    int64_t items = 0;
-    for (int32_t h = 0; c - b_lo - 64 * h > 0; ++h) items += c - b_lo - 64 * h;
-    for (int64_t t0 = gw; t0 < items; t0 += nw * kDenseItems) {
-        int32_t ra[kDenseItems], rb[kDenseItems];
-        double xa[kDenseItems], xb[kDenseItems], sv[kDenseItems];
-        bool on[kDenseItems];
+    if constexpr (kLeft > kSteps) solve_steps<kLeft - kSteps>(s, D, thr_of, nb, take);
+}
+
+// Forms columns J .. J + nb - 1 of R (panel p + 1) on the rows of part q, J + q kPanelRows and on.
+__device__ void form_panel(const FcArgs& A, int32_t p, int32_t q, double* D /* [kPanel][kPanel] */,
+                           double* next /* [kPanel][kPanel] */, double* thr_of /* [kPanel] */,
+                           uint32_t* counts /* [4][kPanel + 1] */, int32_t* bad) {
+    const int64_t N = A.N, J = static_cast<int64_t>(p + 1) * kPanel;
+    const int nb = N - J < kPanel ? static_cast<int>(N - J) : kPanel;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const bool diag = wave == kPanelWaves - 1;   // this wave takes rows J + lane
+    const int64_t i = J + (diag ? lane : q * kPanelRows + static_cast<int64_t>(threadIdx.x));
+    const bool valid = i < N && !(diag && lane >= kPanel);
+    const int64_t ic = valid ? i : J;
+    if (diag) __builtin_amdgcn_s_setprio(3);   // the others wait for it
+    // Row i of the panel's columns (entries above the diagonal are never used)
+    double s[kPanel];
 #pragma unroll
-        for (int q = 0; q < kDenseItems; ++q) {
-            int64_t t = t0 + q * nw;
-            on[q] = false;
-            ra[q] = rb[q] = 0;
-            xa[q] = xb[q] = 0.0;
-            if (t < items) {
-                int32_t h = 0;
-                while (t >= c - b_lo - 64 * h) {   // wave-uniform
-                    t -= c - b_lo - 64 * h;
-                    ++h;
-                }
-                const int32_t b = b_lo + static_cast<int32_t>(t);
-                const int32_t a = b + 64 * h + lane;
-                const int64_t sb = st.slot(b);
-                rb[q] = st.row[sb];
-                xb[q] = st.val[sb];
-                if (a < c) {
-                    const int64_t sa = st.slot(a);
-                    on[q] = true;
-                    ra[q] = st.row[sa];
-                    xa[q] = st.val[sa];
-                }
+    for (int b = 0; b < kPanel; ++b) {
+        const int64_t jb = J + b < N ? J + b : N - 1;
+        const int64_t r = ic > jb ? ic : jb;
+        s[b] = A.dense[packed_column(jb, N) + (r - jb)];
+    }
+    double thr = 0.0;
+    if (diag) thr = A.droptol * A.colnorm[ic];
+    if (p >= 0) {   // panel p's products
+        const int par = p & 1;
+        constexpr int kAhead = 4;   // entries of the row loaded ahead
+        const double2* a2 = reinterpret_cast<const double2*>(A.prow + (par * N + ic) * kPanel);
+        double2 ahead[kAhead / 2];
+#pragma unroll
+        for (int k = 0; k < kAhead / 2; ++k) ahead[k] = a2[k];
+        for (int e = threadIdx.x; e < kPanel * kPanel; e += kPanelBlock) next[e] = A.pnext[par * kPanel * kPanel + e];
+        __syncthreads();
+        for (int k = 0; k < kPanel; k += kAhead) {
+            double a[kAhead];
+            Spread row[kAhead];
+#pragma unroll
+            for (int kk = 0; kk < kAhead; ++kk) row[kk].load(next + (k + kk) * kPanel);
+#pragma unroll
+            for (int kk = 0; kk < kAhead / 2; ++kk) {
+                a[2 * kk] = ahead[kk].x;
+                a[2 * kk + 1] = ahead[kk].y;
+                if (k + kAhead < kPanel) ahead[kk] = a2[(k + kAhead) / 2 + kk];
+            }
+#pragma unroll
+            for (int kk = 0; kk < kAhead; ++kk) {
+                if (__ballot(a[kk] != 0.0) == 0ull) continue;
+                subtract<0, kPanel>(s, a[kk], row[kk]);
             }
         }
-#pragma unroll
-        for (int q = 0; q < kDenseItems; ++q)
-            if (on[q]) sv[q] = A.dense[packed_column(rb[q], N) + (ra[q] - rb[q])];
-#pragma unroll
-        for (int q = 0; q < kDenseItems; ++q)
-            if (on[q]) A.dense[packed_column(rb[q], N) + (ra[q] - rb[q])] = sv[q] - xa[q] * xb[q];
     }
+    if (diag) {
+        if (lane < kPanel) thr_of[lane] = thr;
+        const bool fine = factor_steps<kPanel>(s, D, thr, lane, nb);
+        if (lane == 0) *bad = fine ? 0 : 1;
+        __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();
+    if (*bad) {
+        if (q == 0 && threadIdx.x == 0) atomicOr(&A.header->status, static_cast<uint32_t>(kErrPivot));
+        if (threadIdx.x == 0) {   // nothing to copy or subtract
+            const int64_t at = static_cast<int64_t>((p + 1) & 1) * A.parts + q;
+            A.act_cnt[at] = 0;
+            if (q == 0) A.act_skip[(p + 1) & 1] = 0;
+            for (int c = 0; c < kPanel; ++c) A.col_cnt[at * kPanel + c] = 0;
+        }
+        if (i < N && !diag) A.pmask[((p + 1) & 1) * N + i] = 0;
+        return;
+    }
+    const int par = (p + 1) & 1;
+    const int t = threadIdx.x;
+    const bool block = q == 0 && t < kPanel;   // a row of the diagonal block
+    uint32_t mask = 0, mine = 0;
+    if (!diag) {
+        double* out = A.prow + (par * N + ic) * kPanel;
+        solve_steps<kPanel>(s, D, thr_of, nb, [&](int j, double x, bool keep) {
+            if (block) {
+                x = t >= j ? D[j * kPanel + t - j] : 0.0;
+                keep = x != 0.0;
+            }
+            keep = keep && valid;
+            x = keep ? x : 0.0;
+            mask |= keep ? 1u << j : 0u;
+            const uint32_t c = static_cast<uint32_t>(__popcll(__ballot(keep)));
+            if (lane == j) mine = c;
+            if (valid) out[j] = x;
+            if (q == 0 && t >= kPanel && t < 2 * kPanel) A.pnext[(par * kPanel + j) * kPanel + t - kPanel] = x;
+            return x;
+        });
+        if (valid) A.pmask[par * N + i] = mask;
+        if (lane < kPanel) counts[wave * (kPanel + 1) + lane] = mine;
+        const uint64_t on = __ballot(mask != 0 && !block);
+        if (lane == 0) counts[wave * (kPanel + 1) + kPanel] = static_cast<uint32_t>(__popcll(on));
+        if (q == 0 && t == 0) A.act_skip[par] = static_cast<uint32_t>(__popcll(on));   // lanes kPanel .. 63
+    }
+    __syncthreads();
+    const int64_t at = static_cast<int64_t>(par) * A.parts + q;
+    if (t < kPanel) {
+        uint32_t c = 0;
+        for (int w = 0; w < kPanelWaves - 1; ++w) c += counts[w * (kPanel + 1) + t];
+        A.col_cnt[at * kPanel + t] = c;
+    }
+    if (!diag) {
+        uint32_t before = 0, all = 0;
+        for (int w = 0; w < kPanelWaves - 1; ++w) {
+            const uint32_t c = counts[w * (kPanel + 1) + kPanel];
+            before += w < wave ? c : 0;
+            all += c;
+        }
+        const uint64_t on = __ballot(mask != 0 && !block);
+        if ((on >> lane) & 1ull)
+            A.act[at * kPanelRows + before + __popcll(on & ((1ull << lane) - 1ull))] = static_cast<int32_t>(i);
+        if (t == 0) A.act_cnt[at] = all;
+    }
+}
+
+// Copies panel p's entries in the rows of part q into the compact factor (columns by ascending
+// rows, the diagonal first).
+__device__ void copy_panel(const FcArgs& A, int32_t p, int32_t q, int64_t* offset /* [kPanel] */,
+                           uint32_t* counts /* [4][kPanel + 1] */, int32_t* full) {
+    const int64_t N = A.N, J = static_cast<int64_t>(p) * kPanel;
+    const int nb = N - J < kPanel ? static_cast<int>(N - J) : kPanel;
+    const int par = p & 1, t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1);
+    const int parts = static_cast<int>((N - J + kPanelRows - 1) / kPanelRows);
+    const int64_t i = J + q * kPanelRows + static_cast<int64_t>(t);
+    const bool valid = t < kPanelRows && i < N;
+    const uint32_t mask = valid ? A.pmask[par * N + i] : 0u;
+    if (wave == kPanelWaves - 1) {
+        const uint32_t* cnt = A.col_cnt + static_cast<int64_t>(par) * A.parts * kPanel + (lane & (kPanel - 1));
+        int64_t before = 0, all = 0;
+        for (int w = 0; w < parts; ++w) {
+            const uint32_t c = lane < nb ? cnt[w * kPanel] : 0u;
+            before += w < q ? c : 0;
+            all += c;
+        }
+        int64_t end = all;   // of the columns up to this one
+        for (int off = 1; off < kPanel; off <<= 1) {
+            const int64_t o = __shfl_up(end, off, kWave);
+            if (lane >= off) end += o;
+        }
+        const int64_t rp = A.r_ptr[J];
+        if (lane < kPanel) offset[lane] = rp + end - all + before;
+        const int64_t total = rp + __shfl(end, kPanel - 1, kWave);
+        if (lane == 0) *full = total > A.r_cap ? 1 : 0;
+        if (q == 0) {
+            if (lane < nb) A.r_ptr[J + lane + 1] = rp + end;
+            if (lane == 0) A.counters[0] = total;
+            if (lane == 0 && total > A.r_cap) atomicOr(&A.header->status, static_cast<uint32_t>(kErrCapacity));
+        }
+    } else {
+        uint32_t mine = 0;
+        for (int j = 0; j < kPanel; ++j) {
+            const uint32_t c = static_cast<uint32_t>(__popcll(__ballot(((mask >> j) & 1u) != 0)));
+            if (lane == j) mine = c;
+        }
+        if (lane < kPanel) counts[wave * (kPanel + 1) + lane] = mine;
+    }
+    __syncthreads();
+    if (*full || wave == kPanelWaves - 1) return;
+    for (int j = 0; j < nb; ++j) {
+        const uint64_t m = __ballot(((mask >> j) & 1u) != 0);
+        if ((mask >> j) & 1u) {
+            int64_t pos = offset[j] + __popcll(m & ((1ull << lane) - 1ull));
+            for (int w = 0; w < wave; ++w) pos += counts[w * (kPanel + 1) + j];
+            A.r_row[pos] = static_cast<int32_t>(i);
+            A.r_val[pos] = A.prow[(par * N + i) * kPanel + j];
+        }
+    }
+}
+
+// Subtracts panel p's products from S in tiles of kTile active rows by kTile active columns (the
+// lower triangle of the panel's active rows past the next panel).  A column's kept entries are
+// few (a fifth of the panel on BA(5000, 5)), and the same for all lanes: only they are gone through.
+__device__ void update_tiles(const FcArgs& A, int32_t p, int64_t first, int64_t stride, double* ta, double* tb,
+                             int32_t* ra, int32_t* rb, uint32_t* mb, uint32_t* prefix, int32_t* stop) {
+    const int64_t N = A.N, J = static_cast<int64_t>(p) * kPanel;
+    const int par = p & 1, t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1);
+    const int parts = static_cast<int>((N - J + kPanelRows - 1) / kPanelRows);
+    const uint32_t* cnt = A.act_cnt + static_cast<int64_t>(par) * A.parts;
+    if (wave == 0) {   // where each part's active rows start
+        uint32_t base = 0;
+        for (int w0 = 0; w0 < parts; w0 += kWave) {
+            uint32_t c = w0 + lane < parts ? cnt[w0 + lane] : 0u, end = c;
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t o = __shfl_up(end, off, kWave);
+                if (lane >= off) end += o;
+            }
+            if (w0 + lane < parts) prefix[w0 + lane] = base + end - c;
+            base += __shfl(end, kWave - 1, kWave);
+        }
+        if (lane == 0) {
+            prefix[parts] = base;
+            *stop = __hip_atomic_load(&A.header->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ? 1 : 0;
+        }
+    }
+    __syncthreads();
+    if (*stop) return;
+    const int64_t skip = A.act_skip[par], count = static_cast<int64_t>(prefix[parts]) - skip;
+    const int64_t side = (count + kTile - 1) / kTile, tiles = side * (side + 1) / 2;
+    auto row_of = [&](int64_t x) {   // the x-th active row past the next panel, -1 past the end
+        if (x >= count) return int32_t{-1};
+        const uint32_t at = static_cast<uint32_t>(x + skip);
+        int lo = 0, hi = parts;   // prefix[lo] <= at < prefix[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) / 2;
+            if (prefix[mid] <= at)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        return A.act[(static_cast<int64_t>(par) * A.parts + lo) * kPanelRows + (at - prefix[lo])];
+    };
+    for (int64_t tile = first; tile < tiles; tile += stride) {
+        int64_t h = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(tile) + 1.0) - 1.0) * 0.5);
+        while (h * (h + 1) / 2 > tile) --h;
+        while ((h + 1) * (h + 2) / 2 <= tile) ++h;
+        const int64_t g = tile - h * (h + 1) / 2;   // rows h, columns g <= h
+        if (t < kTile) ra[t] = row_of(h * kTile + t);
+        if (t >= kTile && t < 2 * kTile) {
+            const int32_t r = row_of(g * kTile + t - kTile);
+            rb[t - kTile] = r;
+            mb[t - kTile] = r >= 0 ? A.pmask[par * N + r] : 0u;
+        }
+        __syncthreads();
+        for (int e = t; e < 2 * kTile * (kPanel / 2); e += kPanelBlock) {
+            const int l = (e / (kPanel / 2)) & (kTile - 1), k = 2 * (e % (kPanel / 2));
+            const bool rows = e < kTile * (kPanel / 2);
+            const int32_t r = rows ? ra[l] : rb[l];
+            const double2 x = r >= 0 ? *reinterpret_cast<const double2*>(A.prow + (par * N + r) * kPanel + k) : double2{0.0, 0.0};
+            double* to = (rows ? ta : tb) + l * kTilePitch + k;
+            to[0] = x.x;
+            to[1] = x.y;
+        }
+        if (t < 2 * kTile) (t < kTile ? ta : tb)[(t & (kTile - 1)) * kTilePitch + kPanel] = 0.0;
+        const int32_t r = ra[lane];
+        const uint32_t mr = r >= 0 ? A.pmask[par * N + r] : 0u;
+        uint32_t any = mr;   // of all rows
+        for (int off = kWave / 2; off > 0; off >>= 1) any |= __shfl_xor(any, off, kWave);
+        double s[kTileCols];
+        uint32_t touched = 0;
+#pragma unroll
+        for (int c = 0; c < kTileCols; ++c) {
+            const int b = c * kPanelWaves + wave;
+            const int32_t rc = b < kTile ? rb[b] : -1;
+            const bool on = rc >= 0 && r >= rc && (mr & mb[b]) != 0;
+            touched |= on ? 1u << c : 0u;
+            s[c] = on ? A.dense[packed_column(rc, N) + (r - rc)] : 0.0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kTileCols; ++c) {
+            const int b = c * kPanelWaves + wave;
+            if (b >= kTile) continue;
+            uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(mb[b] & any)));
+            while (m != 0) {   // four entries at a time; past the last the zeros at kPanel
+                double x[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int e = m != 0 ? __builtin_ctz(m) : kPanel;
+                    m &= m - 1;
+                    x[k] = ta[lane * kTilePitch + e] * tb[b * kTilePitch + e];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[c] = s[c] - x[k];
+            }
+            if ((touched >> c) & 1u) A.dense[packed_column(rb[b], N) + (r - rb[b])] = s[c];
+        }
+        __syncthreads();   // the tiles are rewritten
+    }
+}
+
+// Launch p: workgroups 0 .. form - 1 form panel p + 1, the next `copy` ones copy panel p into the
+// factor, the others subtract panel p's products.
+__global__ void __launch_bounds__(kPanelBlock) fc_panel(FcArgs A, int32_t p, int32_t form, int32_t copy) {
+    __shared__ double tiles[2 * kTile * kTilePitch];   // forming: two blocks of kPanel x kPanel
+    __shared__ double thr_of[kPanel];
+    __shared__ int64_t offset[kPanel];
+    __shared__ uint32_t counts[(kPanelWaves - 1) * (kPanel + 1)];
+    __shared__ uint32_t prefix[kMaxParts + 1];
+    __shared__ int32_t ra[kTile], rb[kTile];
+    __shared__ uint32_t mb[kTile];
+    __shared__ int32_t flag;
+    const int32_t w = static_cast<int32_t>(blockIdx.x);
+    if (w < form)
+        form_panel(A, p, w, tiles, tiles + kPanel * kPanel, thr_of, counts, &flag);
+    else if (w < form + copy)
+        copy_panel(A, p, w - form, offset, counts, &flag);
+    else
+        update_tiles(A, p, w - form - copy, static_cast<int64_t>(gridDim.x) - form - copy, tiles, tiles + kTile * kTilePitch,
+                     ra, rb, mb, prefix, &flag);
 }
 
 // The windowed, sparsified inverse and tau~.  Column u needs exactly the later columns i of its
@@ -920,14 +1101,10 @@ struct FcLayout {
     int64_t *r_ptr, *r_next, *r_colend, *head, *tail, *s_start;
     int32_t *r_row, *s_len, *s_row, *stamp, *touched, *done, *inv_row;
     double* inv_val;
-    double *r_val, *s_val, *acc, *colnorm, *xk, *dense;
-    int32_t* xstamp;
-    int32_t* stage_row;
-    double* stage_val;
-    uint32_t* stage_cnt;
-    double* stage_piv;
-    int32_t* stage_first;
-    int64_t stage_cap;
+    double *r_val, *s_val, *acc, *colnorm, *dense, *prow, *pnext;
+    uint32_t *pmask, *act_cnt, *act_skip, *col_cnt;
+    int32_t* act;
+    int32_t parts;
     size_t total;
 };
 
@@ -971,15 +1148,14 @@ FcLayout carve_fc(void* ws, int32_t n, int64_t r_cap, int64_t s_cap, bool dense)
         L.r_colend = c.take<int64_t>(r_cap);
     } else {
         L.colnorm = c.take<double>(N);
-        L.xk = c.take<double>(N);
-        L.xstamp = c.take<int32_t>(N);
-        const size_t cap = static_cast<size_t>((N - 1 + kFormGroups - 1) / kFormGroups + 1);
-        L.stage_row = c.take<int32_t>(2 * kFormGroups * cap);
-        L.stage_val = c.take<double>(2 * kFormGroups * cap);
-        L.stage_cnt = c.take<uint32_t>(2 * kFormGroups);
-        L.stage_piv = c.take<double>(2);
-        L.stage_first = c.take<int32_t>(2);
-        L.stage_cap = static_cast<int64_t>(cap);
+        L.parts = static_cast<int32_t>((N + kPanelRows - 1) / kPanelRows);
+        L.prow = c.take<double>(2 * N * kPanel);
+        L.pmask = c.take<uint32_t>(2 * N);
+        L.pnext = c.take<double>(2 * kPanel * kPanel);
+        L.act = c.take<int32_t>(static_cast<size_t>(2) * L.parts * kPanelRows);
+        L.act_cnt = c.take<uint32_t>(2 * L.parts);
+        L.act_skip = c.take<uint32_t>(2);
+        L.col_cnt = c.take<uint32_t>(static_cast<size_t>(2) * L.parts * kPanel);
         L.dense = c.take<double>(static_cast<size_t>(N) * static_cast<size_t>(N + 1) / 2);
     }
     L.total = c.used();
@@ -1059,14 +1235,14 @@ extern "C" int rwc_fastchol(const rwc_csr* g, const rwc_fastchol_params* p, doub
     A.dmax = L.dmax;
     A.dense = L.dense;
     A.colnorm = L.colnorm;
-    A.xk = L.xk;
-    A.xstamp = L.xstamp;
-    A.stage_row = L.stage_row;
-    A.stage_val = L.stage_val;
-    A.stage_cnt = L.stage_cnt;
-    A.stage_piv = L.stage_piv;
-    A.stage_first = L.stage_first;
-    A.stage_cap = L.stage_cap;
+    A.prow = L.prow;
+    A.pmask = L.pmask;
+    A.pnext = L.pnext;
+    A.act = L.act;
+    A.act_cnt = L.act_cnt;
+    A.act_skip = L.act_skip;
+    A.col_cnt = L.col_cnt;
+    A.parts = L.parts;
     A.tau = tau;
     A.header = L.header;
     A.counters = L.counters;
@@ -1083,11 +1259,17 @@ extern "C" int rwc_fastchol(const rwc_csr* g, const rwc_fastchol_params* p, doub
         hipLaunchKernelGGL(fc_dense_clear, dim3(static_cast<unsigned>(std::min<int64_t>(blocks_for(cells, 256), 8192))),
                            dim3(256), 0, s, reinterpret_cast<uint64_t*>(L.dense), cells);
         hipLaunchKernelGGL(fc_dense_scatter, dim3(blocks_for(N, 256 / kWave)), dim3(256), 0, s, A);
-        // one launch per step: launch k reads what every workgroup of launch k - 1 wrote; the
-        // last one only copies column N - 1 into the factor
-        for (int64_t k = -1; k < N; ++k)
-            hipLaunchKernelGGL(fc_dense_step, dim3(k < 0 ? kFormGroups : kDenseGrid), dim3(kDenseBlock), 0, s, A,
-                               static_cast<int32_t>(k));
+        // launch p reads what every workgroup of launch p - 1 wrote; the last one only copies
+        const int64_t panels = (N + kPanel - 1) / kPanel;
+        for (int64_t q = -1; q < panels; ++q) {
+            const int64_t J0 = q * kPanel, J1 = J0 + kPanel;
+            const int64_t form = J1 < N ? (N - J1 + kPanelRows - 1) / kPanelRows : 0;
+            const int64_t copy = q >= 0 ? (N - J0 + kPanelRows - 1) / kPanelRows : 0;
+            const int64_t side = J1 + kPanel < N ? (N - J1 - kPanel + kTile - 1) / kTile : 0;   // at most, in tiles
+            const int64_t tiles = q >= 0 ? std::min<int64_t>(side * (side + 1) / 2, 3 * device_cu_count()) : 0;
+            hipLaunchKernelGGL(fc_panel, dim3(static_cast<unsigned>(form + copy + tiles)), dim3(kPanelBlock), 0, s, A,
+                               static_cast<int32_t>(q), static_cast<int32_t>(form), static_cast<int32_t>(copy));
+        }
     } else {
         hipLaunchKernelGGL(fc_ichol, dim3(1), dim3(kWave), 0, s, A);
     }
