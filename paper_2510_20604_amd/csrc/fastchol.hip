@@ -19,8 +19,8 @@
 //   - dense (the default while the matrix's packed lower triangle fits): right-looking on that
 //     triangle in HBM, in panels of 32 columns, one launch per panel;
 //   - chain: left-looking on one wave, sparse throughout, for any size.
-// The inverse's columns form a shallow dependency DAG, which eight waves of one workgroup run,
-// each column on one wave with its lanes over the column's entries.
+// The inverse's columns form a dependency DAG, which sixteen waves of one workgroup run, each
+// column on one wave with its lanes over the column's entries.
 // Every floating-point operation happens in the order the serial algorithm performs it (each
 // entry's updates in ascending k, norms and tails summed one entry at a time, sorts by total
 // orders), so the factor, S~ and tau~ are the serial ones bit for bit.
@@ -861,69 +861,500 @@ __global__ void __launch_bounds__(kPanelBlock) fc_panel(FcArgs A, int32_t p, int
 }
 
 // The windowed, sparsified inverse and tau~.  Column u needs exactly the later columns i of its
-// window with R(i, u) != 0, which are few (0.9 on average on BA(20000, 5)), so the columns form a
-// shallow DAG: kInvWaves waves of one workgroup take columns in descending order from a counter
-// and each waits, on a done flag, for the columns it reads.  The wave holding the largest
+// window with R(i, u) != 0, so the columns form a DAG, on BA(5000, 5) 2225 deep: what bounds it is
+// the latency of one column.  kInvWaves waves of one workgroup take columns in descending order from
+// a counter and each waits, on a flag, for the columns it reads.  The wave holding the largest
 // unfinished column never waits, so every wave finishes; a wait that outlasts kInvSpinLimit
-// naps, or any error, stops the kernel.  Each wave has its own accumulator, stamps and touched
-// list (a slice of N of each), and orders a column in LDS when it has at most kInvLds nonzeros,
-// else in its own kSortCap-entry slice of global scratch.  A column's arithmetic is the serial
-// one; only its place in the S~ pool depends on the schedule.
-constexpr int kInvWaves = 8;
+// polls, or any error, stops the kernel.  A column's arithmetic is the serial one; only its place in
+// the S~ pool depends on the schedule.
+//
+// The last kRing columns are also kept in LDS, up to kRingLen entries each, and a column with a window
+// of at most kRingWindow and at most kInvEntries distinct rows stays in LDS altogether: its rows are
+// found in a hash table while it waits, the sums are kept there, and the two orders (by magnitude, by row) are
+// ranks counted against all entries: 5.2 us a level (32.1 -> 11.6 ms; ER(1000, 5) 7.2 -> 1.9, 10 000-node grid
+// 146 -> 34).  The others have a dense accumulator, stamps and a touched list
+// (a slice of N of each per wave) in the workspace, and order a column in LDS when it has at
+// most kInvLds nonzeros, else in their own kSortCap-entry slice of it (14 us a level).
+constexpr int kInvWaves = 16;
 constexpr int kInvLds = 512;
 constexpr int64_t kInvSpinLimit = int64_t{1} << 26;
+constexpr int kRing = 64;          // columns, a power of two
+constexpr int kRingLen = 64;       // one entry per lane
+constexpr int kRingWindow = 32;    // columns up to kRing - kRingWindow apart can be under way
+constexpr int kInvEntries = 127;   // distinct rows besides u: with it two per lane
+constexpr int kInvTable = 256;     // of them and one column more, at most three quarters full
 
-__global__ void __launch_bounds__(kInvWaves * kWave) fc_inverse(FcArgs A) {
-    __shared__ double lval[kInvWaves][kInvLds];
-    __shared__ int32_t lrow[kInvWaves][kInvLds];
-    __shared__ int32_t next_col;
-    __shared__ unsigned long long pool;
-    __shared__ int32_t abort_all;
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    const int32_t N = A.N, v = A.v;
-    if (threadIdx.x == 0) {
-        next_col = 0;
-        pool = 0;
-        abort_all = A.header->status != 0 ? 1 : 0;   // the factor is incomplete
+// LDS of one wave: the hash table (rows, sums), each read entry's place in it, the table's places
+// in the order they were taken, and two arrays to order entries by.  The general path uses it as one array.
+struct InvWave {
+    double sum[kInvTable];
+    double val[kInvEntries + 1];
+    int32_t key[kInvTable];   // -1: empty
+    int32_t row[kInvEntries + 1];
+    uint8_t place[kRingWindow * kRingLen];
+    uint8_t taken[kInvEntries + 1];
+};
+static_assert(sizeof(InvWave) >= kInvLds * 12 && sizeof(InvWave) % 16 == 0);
+
+struct InvShared {
+    InvWave wave[kInvWaves];
+    double val[kRing * kRingLen];
+    int32_t row[kRing * kRingLen];
+    int32_t len[kRing];             // -1: not kept here
+    int32_t column[kRing];          // which column a slot holds, once it is published
+    int32_t current[kInvWaves];     // the column each wave is at
+    int32_t next_col, abort_all;
+    unsigned long long pool;
+};
+static_assert(sizeof(InvShared) <= 160 * 1024);
+
+template <class T>
+__device__ __forceinline__ T shared_load(const RWC_LDS T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <class T>
+__device__ __forceinline__ void shared_store(RWC_LDS T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// A wave's LDS operations are performed in the order it issues them; this also waits for them.
+__device__ __forceinline__ void lds_order() {
+    wave_order();
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_wave_barrier();
+}
+
+// A wave stops on an error of its own or of another wave.
+__device__ void inv_fail(const FcArgs& A, RWC_LDS InvShared* S, uint32_t code) {
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicOr(&A.header->status, code);
+        shared_store(&S->abort_all, 1);
     }
-    __syncthreads();
-    const double dmax = *A.dmax;
+}
+
+// Column u's slot in LDS may be written once no wave can be reading the column it held, u + kRing:
+// the readers of that are at columns from u + kRing - kRingWindow on.
+__device__ bool wait_for_slot(RWC_LDS InvShared* S, int32_t u) {
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t spins = 0;
+    while (__ballot(lane < kInvWaves && shared_load(&S->current[lane < kInvWaves ? lane : 0]) >= u + kRing - kRingWindow) !=
+           0ull) {
+        if (shared_load(&S->abort_all) != 0 || ++spins > kInvSpinLimit) return false;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return true;
+}
+
+enum InvResult { kInvDone, kInvGeneral, kInvStop };
+
+// Column u in LDS.  i, coef: lane d's d-th entry of the window (rows ascending), `deps` of them.
+__device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t u, double ruu, int32_t i, double coef,
+                                 int deps) {
+    const int lane = threadIdx.x & (kWave - 1);
+    RWC_LDS InvWave* const W = &S->wave[threadIdx.x / kWave];
+    // every row's place in the table, columns in the order they become ready
+    uint32_t nt = 0;
+    bool general = false;
+    for (int d = deps - 1; d >= 0 && !general; --d) {
+        const int32_t c = __builtin_amdgcn_readlane(i, d), slot = c & (kRing - 1);
+        int64_t spins = 0;
+        while (__builtin_amdgcn_readfirstlane(shared_load(&S->column[slot])) != c)
+            if (shared_load(&S->abort_all) != 0 || ++spins > kInvSpinLimit) return kInvStop;
+        wave_order();
+        const int32_t len = __builtin_amdgcn_readfirstlane(S->len[slot]);
+        if (len < 0) {
+            general = true;
+            break;
+        }
+        const int32_t r = S->row[slot * kRingLen + lane];
+        uint32_t h = (static_cast<uint32_t>(r) * 0x9E3779B1u) >> 24;
+        bool fresh = false, open = lane < len;
+        while (__ballot(open) != 0ull) {   // at most kInvEntries + kRingLen rows in kInvTable places
+            if (open) {
+                int32_t old = -1;
+                __hip_atomic_compare_exchange_strong(&W->key[h], &old, r, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WAVEFRONT);
+                fresh = old == -1;
+                open = !fresh && old != r;
+                h = open ? (h + 1) & (kInvTable - 1) : h;
+            }
+        }
+        if (lane < len) W->place[d * kRingLen + lane] = static_cast<uint8_t>(h);
+        uint32_t cnt = 0;
+        const uint32_t rank = rank_of(fresh, cnt);
+        if (fresh) {
+            W->sum[h] = 0.0;
+            if (nt + rank <= kInvEntries) W->taken[nt + rank] = static_cast<uint8_t>(h);
+        }
+        nt += cnt;
+        general = nt > static_cast<uint32_t>(kInvEntries);
+    }
+    lds_order();
+    if (general) {   // empty the table
+        for (int k = lane; k < kInvTable; k += kWave) W->key[k] = -1;
+        lds_order();
+        return kInvGeneral;
+    }
+    // the sums, in ascending row order of column u (the next column's entries are read ahead)
+    if (deps > 0) {
+        auto read = [&](int d, int32_t& len, uint32_t& h, double& x) {
+            const int32_t slot = __builtin_amdgcn_readlane(i, d) & (kRing - 1);
+            len = S->len[slot];
+            h = W->place[d * kRingLen + lane];
+            x = lane_value(coef, d) * S->val[slot * kRingLen + lane];
+        };
+        int32_t len, len1 = 0;
+        uint32_t h, h1 = 0;
+        double x, x1 = 0.0;
+        read(0, len, h, x);
+        for (int d = 0; d < deps; ++d) {
+            if (d + 1 < deps) read(d + 1, len1, h1, x1);
+            if (lane < len) W->sum[h] = W->sum[h] - x;
+            wave_order();
+            len = len1;
+            h = h1;
+            x = x1;
+        }
+    }
+    // entry e of lane e % 64: the diagonal, then the table's rows
+    const int m = static_cast<int>(nt) + 1;
+    double a[2];
+    int32_t row[2];
+    bool live[2];
+    uint32_t nz = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int e = lane + k * kWave;
+        a[k] = 1.0 / ruu;
+        row[k] = u;
+        live[k] = e < m;
+        if (live[k] && e > 0) {
+            const uint32_t h = W->taken[e - 1];
+            row[k] = W->key[h];
+            a[k] = W->sum[h];
+            W->key[h] = -1;
+        }
+        live[k] = live[k] && a[k] != 0.0;
+        nz += static_cast<uint32_t>(__popcll(__ballot(live[k])));
+    }
+    wave_order();
+    int32_t keep = static_cast<int32_t>(nz);
+    bool kept[2] = {live[0], live[1]};
+    int listed = m;   // W->row's entries to order the kept ones by
+    if (static_cast<int64_t>(nz) > A.zeta) {
+        // by decreasing magnitude, ties by row
+        double mag[2];
+        int32_t before[2] = {0, 0}, same[2] = {0, 0};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            mag[k] = live[k] ? fabs(a[k]) : 0.0;
+            W->val[lane + k * kWave] = mag[k];
+            W->row[lane + k * kWave] = row[k];
+        }
+        lds_order();
+        for (int j = 0; j < m; j += 4) {   // (past m: zeros, smaller than any)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double o = W->val[j + q];
+                before[0] += o > mag[0] ? 1 : 0;
+                same[0] += o == mag[0] ? 1 : 0;
+                before[1] += o > mag[1] ? 1 : 0;
+                same[1] += o == mag[1] ? 1 : 0;
+            }
+        }
+        if (__ballot((live[0] && same[0] > 1) || (live[1] && same[1] > 1)) != 0ull) {
+            for (int j = 0; j < m; ++j) {
+                const double o = W->val[j];
+                const int32_t r = W->row[j];
+                before[0] += o == mag[0] && r < row[0] ? 1 : 0;
+                before[1] += o == mag[1] && r < row[1] ? 1 : 0;
+            }
+        }
+        lds_order();
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (live[k]) W->val[before[k]] = mag[k];
+        lds_order();
+        // the 1-norm in that order, then the tail grown from the smallest entry
+        double l1 = 0.0;
+        for (int32_t j = 0; j < keep; ++j) l1 += W->val[j];
+        const double lim = A.eps_p * l1;
+        double tail = 0.0;
+        while (keep > 0) {
+            const double x = W->val[keep - 1];
+            if (!(tail + x <= lim)) break;
+            tail += x;
+            --keep;
+        }
+        keep = __builtin_amdgcn_readfirstlane(keep);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            kept[k] = live[k] && before[k] < keep;
+            if (kept[k]) W->row[before[k]] = row[k];
+        }
+        listed = keep;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            W->row[lane + k * kWave] = live[k] ? row[k] : 0x7FFFFFFF;
+    }
+    lds_order();
+    int32_t at[2] = {0, 0};   // by ascending row
+    for (int j = 0; j < listed; ++j) {
+        const int32_t r = W->row[j];
+        at[0] += r < row[0] ? 1 : 0;
+        at[1] += r < row[1] ? 1 : 0;
+    }
+    if (!wait_for_slot(S, u)) return kInvStop;
+    const int32_t slot = u & (kRing - 1);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (kept[k]) {
+            W->val[at[k]] = a[k];
+            if (keep <= kRingLen) {
+                S->val[slot * kRingLen + at[k]] = a[k];
+                S->row[slot * kRingLen + at[k]] = row[k];
+            }
+        }
+    if (lane == 0) S->len[slot] = keep <= kRingLen ? keep : -1;
+    lds_order();
+    if (lane == 0) shared_store(&S->column[slot], u);   // what waits for column u goes on
+    unsigned long long got = 0;
+    if (lane == 0) got = __hip_atomic_fetch_add(&S->pool, static_cast<unsigned long long>(keep), __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+    const int64_t sp = static_cast<int64_t>(__shfl(got, 0, kWave));
+    if (sp + keep > A.s_cap) {
+        inv_fail(A, S, static_cast<uint32_t>(kErrCapacity));
+        return kInvStop;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (kept[k]) {
+            A.s_row[sp + at[k]] = row[k];
+            A.s_val[sp + at[k]] = a[k];
+        }
+    double t2 = 0.0;   // ||S~(:, u)||^2 in row order
+    for (int32_t j = 0; j < keep; ++j) {
+        const double x = W->val[j];
+        t2 += x * x;
+    }
+    if (lane == 0) {
+        A.s_start[u] = sp;
+        A.s_len[u] = keep;
+        A.tau[node_of_column(u, A.v)] = t2;
+    }
+    return kInvDone;
+}
+
+// Column u by the dense accumulator, the window's entries [c0 + 1, c1) of any number.
+__device__ InvResult general_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t u, int64_t c0, int64_t c1, double ruu,
+                                    int64_t w) {
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int64_t N = A.N;
     double* acc = A.acc + static_cast<int64_t>(wave) * N;
     int32_t* stamps = A.stamp + static_cast<int64_t>(wave) * N;
     int32_t* touched = A.touched + static_cast<int64_t>(wave) * N;
-    // a wave stops on an error of its own or of another wave
-    auto fail = [&](uint32_t code) {
-        if (lane == 0) {
-            atomicOr(&A.header->status, code);
-            __hip_atomic_store(&abort_all, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const int32_t stamp = -(u + 1);   // negative stamps: the factor's are positive
+    uint32_t nt = 1;
+    if (lane == 0) {
+        st(&acc[u], 1.0 / ruu);
+        st(&stamps[u], stamp);
+        st(&touched[0], u);
+    }
+    wave_order();
+    // the window's entries of column u, 64 at a time (lane l: entry p0 + l); their columns of
+    // S~ are waited for together, then added in ascending row order, each a dependent load of
+    // its entries and then of their stamps and accumulators
+    for (int64_t p0 = c0 + 1; p0 < c1; p0 += kWave) {
+        const int64_t p = p0 + lane;
+        int32_t i = -1;
+        double coef = 0.0;
+        if (p < c1) {
+            const int32_t r = A.r_row[p];
+            if (r <= u + w) {
+                i = r;
+                coef = A.r_val[p] / ruu;
+            }
         }
-    };
-    while (__hip_atomic_load(&abort_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) {
+        const uint64_t live = __ballot(i >= 0);   // a prefix: rows ascend
+        if (live == 0ull) break;
+        int64_t spins = 0;
+        while (__ballot(i >= 0 && __hip_atomic_load(&A.done[i], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) !=
+               0ull) {
+            if (shared_load(&S->abort_all) != 0 || ++spins > kInvSpinLimit) return kInvStop;
+            __builtin_amdgcn_s_sleep(2);
+        }
+        int64_t s0 = 0;
+        int32_t sl = 0;
+        if (i >= 0) {
+            s0 = A.s_start[i];
+            sl = A.s_len[i];
+        }
+        for (uint64_t bits = live; bits != 0ull; bits &= bits - 1) {
+            const int l = __builtin_ctzll(bits);
+            const double cf = __shfl(coef, l, kWave);
+            const int64_t b0 = __shfl(s0, l, kWave);
+            const int32_t bl = __shfl(sl, l, kWave);
+            for (int32_t q0 = 0; q0 < bl; q0 += kWave) {
+                const int32_t q = q0 + lane;
+                int32_t r = -1;
+                double sv = 0.0;
+                if (q < bl) {
+                    r = A.s_row[b0 + q];
+                    sv = A.s_val[b0 + q];
+                }
+                const int32_t rc = r >= 0 ? r : u;   // a valid address for every lane
+                const int32_t sg = ld(&stamps[rc]);
+                const double old = ld(&acc[rc]);
+                const bool fresh = r >= 0 && sg != stamp;
+                uint32_t cnt = 0;
+                const uint32_t rk = rank_of(fresh, cnt);
+                if (fresh) {
+                    st(&stamps[r], stamp);
+                    st(&touched[nt + rk], r);   // distinct rows below N
+                }
+                nt += cnt;
+                if (r >= 0) st(&acc[r], (fresh ? 0.0 : old) - cf * sv);
+            }
+            wave_order();
+        }
+    }
+    wave_order();
+    // the nonzeros of S*(:, u), in LDS when they fit, else in this wave's global scratch
+    const bool small = nt <= static_cast<uint32_t>(kInvLds);
+    double* const lds = (double*)(&S->wave[wave]);
+    double* val = small ? lds : A.inv_val + static_cast<int64_t>(wave) * kSortCap;
+    int32_t* row = small ? reinterpret_cast<int32_t*>(lds + kInvLds) : A.inv_row + static_cast<int64_t>(wave) * kSortCap;
+    uint32_t nz = 0;
+    for (uint32_t t0 = 0; t0 < nt; t0 += kWave) {
+        const uint32_t tt = t0 + lane;
+        int32_t r = -1;
+        double a = 0.0;
+        if (tt < nt) {
+            r = ld(&touched[tt]);
+            a = ld(&acc[r]);
+        }
+        const bool live = r >= 0 && a != 0.0;
+        uint32_t cnt = 0;
+        const uint32_t rk = rank_of(live, cnt);
+        if (nz + cnt > static_cast<uint32_t>(kSortCap)) {
+            inv_fail(A, S, static_cast<uint32_t>(kErrCapacity));
+            return kInvStop;
+        }
+        if (live) {
+            val[nz + rk] = a;
+            row[nz + rk] = r;
+        }
+        nz += cnt;
+    }
+    lds_order();
+    int32_t keep = static_cast<int32_t>(nz);
+    if (static_cast<int64_t>(nz) > A.zeta) {
+        wave_sort(val, row, static_cast<int32_t>(nz), [](double va, int32_t ra, double vb, int32_t rb) {
+            const double a = fabs(va), b = fabs(vb);
+            return a > b || (a == b && ra < rb);
+        });
+        // the 1-norm in sorted order, then the tail grown from the smallest entry: every lane
+        // adds the same values in the same order, read from the lanes that loaded them
+        double l1 = 0.0;
+        for (int32_t t0 = 0; t0 < static_cast<int32_t>(nz); t0 += kWave) {
+            const int32_t t = t0 + lane;
+            const double a = t < static_cast<int32_t>(nz) ? fabs(val[t]) : 0.0;
+            const int32_t m = static_cast<int32_t>(nz) - t0 < kWave ? static_cast<int32_t>(nz) - t0 : kWave;
+            for (int32_t l = 0; l < m; ++l) l1 += lane_value(a, l);
+        }
+        const double lim = A.eps_p * l1;
+        double tail = 0.0;
+        int32_t k = static_cast<int32_t>(nz);
+        for (bool more = true; more && k > 0;) {
+            const int32_t base = k > kWave ? k - kWave : 0;   // entries [base, k), largest index first
+            const int32_t t = base + lane;
+            const double a = t < k ? fabs(val[t]) : 0.0;
+            for (int32_t l = k - 1 - base; l >= 0; --l) {
+                const double x = lane_value(a, l);
+                if (!(tail + x <= lim)) {
+                    more = false;
+                    break;
+                }
+                tail += x;
+                --k;
+            }
+        }
+        keep = k;
+    }
+    wave_sort(val, row, keep, [](double, int32_t ra, double, int32_t rb) { return ra < rb; });
+    unsigned long long got = 0;
+    if (lane == 0) got = __hip_atomic_fetch_add(&S->pool, static_cast<unsigned long long>(keep), __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+    const int64_t sp = static_cast<int64_t>(__shfl(got, 0, kWave));
+    if (sp + keep > A.s_cap) {
+        inv_fail(A, S, static_cast<uint32_t>(kErrCapacity));
+        return kInvStop;
+    }
+    for (int32_t k = lane; k < keep; k += kWave) {
+        A.s_row[sp + k] = row[k];
+        A.s_val[sp + k] = val[k];
+    }
+    double t2 = 0.0;   // ||S~(:, u)||^2 in row order, as above
+    for (int32_t t0 = 0; t0 < keep; t0 += kWave) {
+        const int32_t t = t0 + lane;
+        const double a = t < keep ? val[t] : 0.0;
+        const int32_t m = keep - t0 < kWave ? keep - t0 : kWave;
+        for (int32_t l = 0; l < m; ++l) {
+            const double x = lane_value(a, l);
+            t2 += x * x;
+        }
+    }
+    if (lane == 0) {
+        A.s_start[u] = sp;
+        A.s_len[u] = keep;
+        A.tau[node_of_column(u, A.v)] = t2;
+    }
+    // the columns kept in LDS, then the table empty again
+    if (!wait_for_slot(S, u)) return kInvStop;
+    const int32_t slot = u & (kRing - 1);
+    if (lane < keep && keep <= kRingLen) {
+        S->val[slot * kRingLen + lane] = val[lane];
+        S->row[slot * kRingLen + lane] = row[lane];
+    }
+    if (lane == 0) S->len[slot] = keep <= kRingLen ? keep : -1;
+    lds_order();
+    if (lane == 0) shared_store(&S->column[slot], u);
+    for (int k = lane; k < kInvTable; k += kWave) S->wave[wave].key[k] = -1;
+    lds_order();
+    return kInvDone;
+}
+
+__global__ void __launch_bounds__(kInvWaves * kWave) fc_inverse(FcArgs A) {
+    extern __shared__ double inv_lds[];
+    RWC_LDS InvShared* const S = (RWC_LDS InvShared*)inv_lds;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int32_t N = A.N, v = A.v;
+    if (threadIdx.x == 0) {
+        S->next_col = 0;
+        S->pool = 0;
+        S->abort_all = A.header->status != 0 ? 1 : 0;   // the factor is incomplete
+    }
+    for (int k = threadIdx.x; k < kRing; k += kInvWaves * kWave) S->column[k] = -1;
+    for (int k = lane; k < kInvTable; k += kWave) S->wave[wave].key[k] = -1;
+    if (lane == 0) S->current[wave] = N;
+    __syncthreads();
+    const double dmax = *A.dmax;
+    while (shared_load(&S->abort_all) == 0) {
         int32_t t = 0;
-        if (lane == 0) t = atomicAdd(&next_col, 1);
-        t = __shfl(t, 0, kWave);
+        if (lane == 0) t = __hip_atomic_fetch_add(&S->next_col, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        t = __builtin_amdgcn_readfirstlane(t);
         if (t >= N) break;
         const int32_t u = N - 1 - t;
-        const int32_t stamp = -(u + 1);   // negative stamps: the factor's are positive
-        const int32_t node = node_of_column(u, v);
-        const int32_t x = A.node_index[node];
+        if (lane == 0) shared_store(&S->current[wave], u);
+        wave_order();
+        const int32_t x = A.node_index[node_of_column(u, v)];
         const int64_t c0 = A.r_ptr[u], c1 = A.r_ptr[u + 1];
         const double ruu = A.r_val[c0];
         int64_t w = static_cast<int64_t>(floor(A.ws * (1.0 + A.strength[x] / dmax)));
         if (w > N) w = N;
-        uint32_t nt = 1;
-        if (lane == 0) {
-            st(&acc[u], 1.0 / ruu);
-            st(&stamps[u], stamp);
-            st(&touched[0], u);
-        }
-        wave_order();
-        // the window's entries of column u, 64 at a time (lane l: entry p0 + l); their columns of
-        // S~ are waited for together, then added in ascending row order, each a dependent load of
-        // its entries and then of their stamps and accumulators
-        bool stop = false;
-        for (int64_t p0 = c0 + 1; p0 < c1 && !stop; p0 += kWave) {
-            const int64_t p = p0 + lane;
+        InvResult result = kInvGeneral;
+        if (w <= kRingWindow) {   // its entries in the window are among the first 32 below the diagonal
+            const int64_t p = c0 + 1 + lane;
             int32_t i = -1;
             double coef = 0.0;
             if (p < c1) {
@@ -933,165 +1364,22 @@ __global__ void __launch_bounds__(kInvWaves * kWave) fc_inverse(FcArgs A) {
                     coef = A.r_val[p] / ruu;
                 }
             }
-            const uint64_t live = __ballot(i >= 0);   // a prefix: rows ascend
-            if (live == 0ull) break;
-            int64_t spins = 0;
-            while (__ballot(i >= 0 && __hip_atomic_load(&A.done[i], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) !=
-                   0ull) {
-                if (__hip_atomic_load(&abort_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0 ||
-                    ++spins > kInvSpinLimit) {
-                    stop = true;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(2);
-            }
-            if (stop) break;
-            int64_t s0 = 0;
-            int32_t sl = 0;
-            if (i >= 0) {
-                s0 = A.s_start[i];
-                sl = A.s_len[i];
-            }
-            for (uint64_t bits = live; bits != 0ull; bits &= bits - 1) {
-                const int l = __builtin_ctzll(bits);
-                const double cf = __shfl(coef, l, kWave);
-                const int64_t b0 = __shfl(s0, l, kWave);
-                const int32_t bl = __shfl(sl, l, kWave);
-                for (int32_t q0 = 0; q0 < bl; q0 += kWave) {
-                    const int32_t q = q0 + lane;
-                    int32_t r = -1;
-                    double sv = 0.0;
-                    if (q < bl) {
-                        r = A.s_row[b0 + q];
-                        sv = A.s_val[b0 + q];
-                    }
-                    const int32_t rc = r >= 0 ? r : u;   // a valid address for every lane
-                    const int32_t sg = ld(&stamps[rc]);
-                    const double old = ld(&acc[rc]);
-                    const bool fresh = r >= 0 && sg != stamp;
-                    uint32_t cnt = 0;
-                    const uint32_t rk = rank_of(fresh, cnt);
-                    if (fresh) {
-                        st(&stamps[r], stamp);
-                        st(&touched[nt + rk], r);   // distinct rows below N
-                    }
-                    nt += cnt;
-                    if (r >= 0) st(&acc[r], (fresh ? 0.0 : old) - cf * sv);
-                }
-                wave_order();
-            }
+            result = ring_column(A, S, u, ruu, i, coef, static_cast<int>(__popcll(__ballot(i >= 0))));
         }
-        if (stop) {
-            if (__hip_atomic_load(&abort_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
-                fail(static_cast<uint32_t>(kErrWait));   // a wait ran out (not expected)
+        if (result == kInvGeneral) result = general_column(A, S, u, c0, c1, ruu, w);
+        if (result == kInvStop) {
+            if (shared_load(&S->abort_all) == 0) inv_fail(A, S, static_cast<uint32_t>(kErrWait));   // a wait ran out (not expected)
             break;
-        }
-        wave_order();
-        // the nonzeros of S*(:, u), in LDS when they fit, else in this wave's global scratch
-        const bool small = nt <= static_cast<uint32_t>(kInvLds);
-        double* val = small ? lval[wave] : A.inv_val + static_cast<int64_t>(wave) * kSortCap;
-        int32_t* row = small ? lrow[wave] : A.inv_row + static_cast<int64_t>(wave) * kSortCap;
-        uint32_t nz = 0;
-        bool full = false;
-        for (uint32_t t0 = 0; t0 < nt; t0 += kWave) {
-            const uint32_t tt = t0 + lane;
-            int32_t r = -1;
-            double a = 0.0;
-            if (tt < nt) {
-                r = ld(&touched[tt]);
-                a = ld(&acc[r]);
-            }
-            const bool live = r >= 0 && a != 0.0;
-            uint32_t cnt = 0;
-            const uint32_t rk = rank_of(live, cnt);
-            if (nz + cnt > static_cast<uint32_t>(kSortCap)) {
-                full = true;
-                break;
-            }
-            if (live) {
-                val[nz + rk] = a;
-                row[nz + rk] = r;
-            }
-            nz += cnt;
-        }
-        if (full) {
-            fail(static_cast<uint32_t>(kErrCapacity));
-            break;
-        }
-        wave_order();
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_wave_barrier();
-        int32_t keep = static_cast<int32_t>(nz);
-        if (static_cast<int64_t>(nz) > A.zeta) {
-            wave_sort(val, row, static_cast<int32_t>(nz), [](double va, int32_t ra, double vb, int32_t rb) {
-                const double a = fabs(va), b = fabs(vb);
-                return a > b || (a == b && ra < rb);
-            });
-            // the 1-norm in sorted order, then the tail grown from the smallest entry: every lane
-            // adds the same values in the same order, read from the lanes that loaded them
-            double l1 = 0.0;
-            for (int32_t t0 = 0; t0 < static_cast<int32_t>(nz); t0 += kWave) {
-                const int32_t t = t0 + lane;
-                const double a = t < static_cast<int32_t>(nz) ? fabs(val[t]) : 0.0;
-                const int32_t m = static_cast<int32_t>(nz) - t0 < kWave ? static_cast<int32_t>(nz) - t0 : kWave;
-                for (int32_t l = 0; l < m; ++l) l1 += lane_value(a, l);
-            }
-            const double lim = A.eps_p * l1;
-            double tail = 0.0;
-            int32_t k = static_cast<int32_t>(nz);
-            for (bool more = true; more && k > 0;) {
-                const int32_t base = k > kWave ? k - kWave : 0;   // entries [base, k), largest index first
-                const int32_t t = base + lane;
-                const double a = t < k ? fabs(val[t]) : 0.0;
-                for (int32_t l = k - 1 - base; l >= 0; --l) {
-                    const double x = lane_value(a, l);
-                    if (!(tail + x <= lim)) {
-                        more = false;
-                        break;
-                    }
-                    tail += x;
-                    --k;
-                }
-            }
-            keep = k;
-        }
-        wave_sort(val, row, keep, [](double, int32_t ra, double, int32_t rb) { return ra < rb; });
-        unsigned long long at = 0;
-        if (lane == 0) at = atomicAdd(&pool, static_cast<unsigned long long>(keep));
-        const int64_t sp = static_cast<int64_t>(__shfl(at, 0, kWave));
-        if (sp + keep > A.s_cap) {
-            fail(static_cast<uint32_t>(kErrCapacity));
-            break;
-        }
-        for (int32_t k = lane; k < keep; k += kWave) {
-            A.s_row[sp + k] = row[k];
-            A.s_val[sp + k] = val[k];
-        }
-        double t2 = 0.0;   // ||S~(:, u)||^2 in row order, as above
-        for (int32_t t0 = 0; t0 < keep; t0 += kWave) {
-            const int32_t t = t0 + lane;
-            const double a = t < keep ? val[t] : 0.0;
-            const int32_t m = keep - t0 < kWave ? keep - t0 : kWave;
-            for (int32_t l = 0; l < m; ++l) {
-                const double x = lane_value(a, l);
-                t2 += x * x;
-            }
-        }
-        if (lane == 0) {
-            A.s_start[u] = sp;
-            A.s_len[u] = keep;
-            A.tau[node] = t2;
         }
         // every lane's stores of column u are done before the flag that publishes it
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
         if (lane == 0) __hip_atomic_store(&A.done[u], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        wave_order();
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_wave_barrier();
+        lds_order();
     }
+    if (lane == 0) shared_store(&S->current[wave], -1);
     __syncthreads();
-    if (threadIdx.x == 0 && abort_all == 0) A.counters[1] = static_cast<int64_t>(pool);
+    if (threadIdx.x == 0 && S->abort_all == 0) A.counters[1] = static_cast<int64_t>(S->pool);
 }
 
 struct FcLayout {
@@ -1273,7 +1561,7 @@ extern "C" int rwc_fastchol(const rwc_csr* g, const rwc_fastchol_params* p, doub
     } else {
         hipLaunchKernelGGL(fc_ichol, dim3(1), dim3(kWave), 0, s, A);
     }
-    hipLaunchKernelGGL(fc_inverse, dim3(1), dim3(kInvWaves * kWave), 0, s, A);
+    hipLaunchKernelGGL(fc_inverse, dim3(1), dim3(kInvWaves * kWave), sizeof(InvShared), s, A);
     RWC_HIP(hipGetLastError());
     return RWC_OK;
 }
