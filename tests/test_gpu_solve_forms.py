@@ -75,3 +75,19 @@ def test_solve_in_every_form(name, weighted):
         c = P.estimate(Gd, counts, 1, stream_ordered=True, max_iter=a["iters"] - 1)
         with pytest.raises(P.RWCError):
             P.workspace_status(c["workspace"])
+
+
+@pytest.mark.parametrize("degree", [63, 64, 65, 200])
+def test_longest_row_at_the_block_limit(degree):
+    """Four lanes per row take rows of up to 64 entries; a graph with a longer one has them taken by
+    the block.  An extra node joined to `degree` nodes of an ER graph, not grounded."""
+    g = G.erdos_renyi_lcc(5100, 4, 3)
+    to = np.linspace(0, g.n - 1, degree).astype(np.int32)
+    g = G.graphs.EdgeList(g.n + 1, np.concatenate([g.src, to]), np.concatenate([g.dst, np.full(degree, g.n, np.int32)]), None)
+    assert 2 * g.m <= 6 * g.n and g.n > 4096
+    Gd = P.Graph(g.n, g.src, g.dst, None)
+    assert Gd.csr.max_degree == degree
+    roots = np.array([1, g.n // 2], np.int32)
+    e = P.estimate_group(Gd, roots, torch.ones(g.n, dtype=torch.int64, device="cuda"), 1)
+    want = _hitting_times(g, None, roots)
+    np.testing.assert_allclose(e["hit"].cpu().numpy(), want, rtol=1e-9, atol=1e-9 * want.max())
