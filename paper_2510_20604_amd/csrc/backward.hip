@@ -46,7 +46,7 @@ __global__ void fill_zero(double* __restrict__ x, int64_t count) {
 }
 
 struct ColScalars {
-    double alpha, beta, zr, rr, rr0, zr_new, zro, rp, pap;
+    double alpha, alpha_prev, beta, zr, rr, rr0, zro, rp, pap;   // alpha_prev: the iteration before's
     int32_t done;
     int32_t pad;
 };
@@ -211,7 +211,7 @@ constexpr int kScalarBatch = 8;
 // as in bpcg_update (the thread count is a multiple of R; thread t keeps column t mod R and
 // fills partial slot t / R).
 __global__ void bpcg_init(int32_t n, int32_t v, int32_t R, const double* __restrict__ d, double* __restrict__ Y,
-                          double* __restrict__ X, float* __restrict__ P32, double* __restrict__ part,
+                          double* __restrict__ X, float* __restrict__ P32, float* __restrict__ P32_next, double* __restrict__ part,
                           double* __restrict__ rp_part, BpcgState* __restrict__ st) {
     const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
     if (t == 0) *st = BpcgState{0, 0};
@@ -226,6 +226,7 @@ __global__ void bpcg_init(int32_t n, int32_t v, int32_t R, const double* __restr
         X[i] = 0.0;
         const float p = static_cast<float>(z);
         P32[p_index(u, c, R, n)] = p;
+        if (u == v) P32_next[p_index(u, c, R, n)] = 0.0f;
         zr += z * r;
         rr += r * r;
         rp += r * static_cast<double>(p);
@@ -534,25 +535,33 @@ int64_t spmm_resident_waves() {
     return w < kMaxWaves ? w : kMaxWaves;
 }
 
-// X += alpha P, r -= alpha AP, and the partial dots z.r, z.r_old, r.r.  One thread per (row,
-// column) element, rows strided, so every load and store is a contiguous stream; the thread
-// count is a multiple of R, so thread t keeps column t mod R and its partials fill slot t
-// (virtual wave t / R of the column-partial layout).
+// r -= alpha AP, and the partial dots z.r, z.r_old, r.r; kBoth: also X += alpha P of the iteration
+// before and of this one, in that order.  Nothing but the end reads X, so every second iteration reads
+// and writes it (36 bytes an element and iteration on average instead of 44; R-MAT of scale 21, R = 66:
+// 433 -> 406 us, BA(100 000, 4) 45 -> 41; the solution is the same bit for bit).  Four rows in flight per
+// thread: 279 and 564 instead of 295 and 517 us without and with X, so one.  One thread per (row,
+// column) element, rows strided, so every load and store is a contiguous stream; the thread count is
+// a multiple of R, so thread t keeps column t mod R and its partials fill slot t (virtual wave t / R of
+// the column-partial layout).
+template <bool kBoth>
 __global__ void bpcg_update(int32_t n, int32_t v, int32_t R, const ColScalars* __restrict__ sc,
                             const double* __restrict__ d, double* __restrict__ X, double* __restrict__ Rr,
-                            const float* __restrict__ P32, const double* __restrict__ AP, double* __restrict__ part,
-                            const BpcgState* __restrict__ st) {
+                            const float* __restrict__ P_prev, const float* __restrict__ P32,
+                            const double* __restrict__ AP, double* __restrict__ part, const BpcgState* __restrict__ st) {
     if (st->ndone == R) return;
     const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
     const int64_t rows_step = static_cast<int64_t>(gridDim.x) * blockDim.x / R;
     const int32_t c = static_cast<int32_t>(t % R);
-    const double alpha = sc[c].alpha;
+    const double alpha = sc[c].alpha, alpha_prev = sc[c].alpha_prev;
     double zr = 0.0, zro = 0.0, rr = 0.0;
     for (int64_t u = t / R; u < n; u += rows_step) {
         if (u == v) continue;
         const int64_t i = u * R + c;
-        const double p = static_cast<double>(P32[p_index(u, c, R, n)]);
-        X[i] = X[i] + alpha * p;
+        if constexpr (kBoth) {
+            const int64_t pi = p_index(u, c, R, n);
+            const double x = X[i] + alpha_prev * static_cast<double>(P_prev[pi]);
+            X[i] = x + alpha * static_cast<double>(P32[pi]);
+        }
         const double r_old = Rr[i];
         const double r = r_old - alpha * AP[i];
         Rr[i] = r;
@@ -567,12 +576,26 @@ __global__ void bpcg_update(int32_t n, int32_t v, int32_t R, const ColScalars* _
     part[part_index(2, c, slot, R, rows_step)] = rr;
 }
 
-// P = z + beta P (z = r / d), and the partial dot r.P with P as stored; element layout and
+// X += alpha P of the last iteration, where that was the first of a pair.
+__global__ void bpcg_finish(int32_t n, int32_t v, int32_t R, const ColScalars* __restrict__ sc, double* __restrict__ X,
+                            const float* __restrict__ P32) {
+    const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+    const int64_t rows_step = static_cast<int64_t>(gridDim.x) * blockDim.x / R;
+    const int32_t c = static_cast<int32_t>(t % R);
+    const double alpha = sc[c].alpha;
+    for (int64_t u = t / R; u < n; u += rows_step) {
+        if (u == v) continue;
+        const int64_t i = u * R + c;
+        X[i] = X[i] + alpha * static_cast<double>(P32[p_index(u, c, R, n)]);
+    }
+}
+
+// P_next = z + beta P (z = r / d), and the partial dot r.P_next with P_next as stored; element layout and
 // partial slots as bpcg_update.
 constexpr int kDirRows = 8;
 __global__ void bpcg_direction(int32_t n, int32_t v, int32_t R, const ColScalars* __restrict__ sc,
-                               const double* __restrict__ d, const double* __restrict__ Rr, float* __restrict__ P32,
-                               double* __restrict__ rp_part, const BpcgState* __restrict__ st) {
+                               const double* __restrict__ d, const double* __restrict__ Rr, const float* __restrict__ P32,
+                               float* __restrict__ P_next, double* __restrict__ rp_part, const BpcgState* __restrict__ st) {
     if (st->ndone == R) return;
     const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
     const int64_t rows_step = static_cast<int64_t>(gridDim.x) * blockDim.x / R;
@@ -597,7 +620,7 @@ __global__ void bpcg_direction(int32_t n, int32_t v, int32_t R, const ColScalars
             const int64_t uq = u + q * rows_step;
             if (uq == v) continue;
             const float p = static_cast<float>(r[q] / du[q] + beta * static_cast<double>(p_old[q]));
-            P32[p_index(uq, c, R, n)] = p;
+            P_next[p_index(uq, c, R, n)] = p;
             rp += r[q] * static_cast<double>(p);
         }
     }
@@ -606,7 +629,7 @@ __global__ void bpcg_direction(int32_t n, int32_t v, int32_t R, const ColScalars
         const double r = Rr[u * R + c];
         const int64_t pi = p_index(u, c, R, n);
         const float p = static_cast<float>(r / d[u] + beta * static_cast<double>(P32[pi]));
-        P32[pi] = p;
+        P_next[pi] = p;
         rp += r * static_cast<double>(p);
     }
     rp_part[part_index(0, c, t / R, R, rows_step)] = rp;
@@ -675,12 +698,13 @@ __global__ void bpcg_scalars(int32_t R, int32_t nwaves, const double* __restrict
         s.rr0 = b;
         s.rr = b;
         s.done = (b == 0.0) ? 1 : 0;
-        s.alpha = 0.0;
+        s.alpha = s.alpha_prev = 0.0;
         s.beta = 0.0;
         if (s.done) atomicAdd(&st->ndone, 1);
     } else if (mode == 1) {
         s.rp = a;
         s.pap = b;
+        s.alpha_prev = s.alpha;
         s.alpha = (s.done || b == 0.0) ? 0.0 : a / b;
     } else {
         s.rr = e;
@@ -850,7 +874,7 @@ __global__ void edge_gradient(int32_t n, int64_t nnz, int32_t R, const int32_t* 
 struct BwdLayout {
     WsHeader* header;
     double *Y, *X, *AP, *part, *rp_part, *cut, *colmean, *coef;
-    float* P32;
+    float* P32[2];   // the directions of the even and the odd iterations
     ColScalars* sc;
     BpcgState* bst;
     EdgeScalars* es;
@@ -873,7 +897,8 @@ BwdLayout carve_bwd(void* ws, int32_t n, int64_t nnz, int32_t R) {
     L.Y = c.take<double>(nr);
     L.X = c.take<double>(nr);
     L.AP = c.take<double>(nr);
-    L.P32 = c.take<float>(nr);
+    L.P32[0] = c.take<float>(nr);
+    L.P32[1] = c.take<float>(nr);
     L.part = c.take<double>(static_cast<size_t>(kMaxWaves) * R * 3);
     L.rp_part = c.take<double>(static_cast<size_t>(kDirSlots) * R);
     L.cut = c.take<double>(2 * wmax * R);
@@ -1031,7 +1056,7 @@ extern "C" int rwc_backward(const rwc_csr* g, const double* grad_rwc, const rwc_
     const unsigned dir_blocks = static_cast<unsigned>(dir_m * R);
     const int32_t dir_nw = static_cast<int32_t>(dir_m * kBlock);
     const double tol2 = tol * tol;
-    hipLaunchKernelGGL(bpcg_init, dim3(dir_blocks), dim3(kBlock), 0, s, n, v, R, g->strength, L.Y, L.X, L.P32,
+    hipLaunchKernelGGL(bpcg_init, dim3(dir_blocks), dim3(kBlock), 0, s, n, v, R, g->strength, L.Y, L.X, L.P32[0], L.P32[1],
                        L.part, L.rp_part, L.bst);
     hipLaunchKernelGGL(bpcg_scalars, dim3(R), dim3(kBlock), 0, s, R, dir_nw, L.part, dir_nw, L.rp_part, L.sc, 0,
                        tol2, L.bst);
@@ -1043,19 +1068,21 @@ extern "C" int rwc_backward(const rwc_csr* g, const double* grad_rwc, const rwc_
     while (!converged && it < max_iter) {
         const int chunk = (max_iter - it) < check ? (max_iter - it) : check;
         for (int c = 0; c < chunk; ++c) {
+            const bool odd = ((it + c) & 1) != 0;
+            float *const P = L.P32[odd], *const P_other = L.P32[!odd];
             hipLaunchKernelGGL(bpcg_spmm, dim3(wave_blocks), dim3(kBlock), 0, s, n, v, R, nnz, nseg, g->row_ptr,
-                               g->col, g->weight, g->strength, L.P32, L.seg_k, L.seg_row, L.AP, L.cut, L.part, L.bst);
+                               g->col, g->weight, g->strength, P, L.seg_k, L.seg_row, L.AP, L.cut, L.part, L.bst);
             if (nseg > 1)
                 hipLaunchKernelGGL(spmm_fixup, dim3(fix_blocks), dim3(kBlock), 0, s, n, v, R, nseg, g->row_ptr,
-                                   L.seg_k, L.seg_row, g->strength, L.P32, L.cut, L.AP, L.part, nw, L.bst);
+                                   L.seg_k, L.seg_row, g->strength, P, L.cut, L.AP, L.part, nw, L.bst);
             hipLaunchKernelGGL(bpcg_scalars, dim3(R), dim3(kBlock), 0, s, R, nw, L.part, dir_nw, L.rp_part, L.sc, 1,
                                tol2, L.bst);
-            hipLaunchKernelGGL(bpcg_update, dim3(upd_blocks), dim3(kBlock), 0, s, n, v, R, L.sc, g->strength, L.X,
-                               L.Y, L.P32, L.AP, L.part, L.bst);
+            hipLaunchKernelGGL(odd ? bpcg_update<true> : bpcg_update<false>, dim3(upd_blocks), dim3(kBlock), 0, s, n, v, R,
+                               L.sc, g->strength, L.X, L.Y, P_other, P, L.AP, L.part, L.bst);
             hipLaunchKernelGGL(bpcg_scalars, dim3(R), dim3(kBlock), 0, s, R, upd_nw, L.part, dir_nw, L.rp_part, L.sc,
                                2, tol2, L.bst);
             hipLaunchKernelGGL(bpcg_direction, dim3(dir_blocks), dim3(kBlock), 0, s, n, v, R, L.sc, g->strength, L.Y,
-                               L.P32, L.rp_part, L.bst);
+                               P, P_other, L.rp_part, L.bst);
         }
         RWC_HIP(hipGetLastError());
         it += chunk;
@@ -1073,6 +1100,8 @@ extern "C" int rwc_backward(const rwc_csr* g, const double* grad_rwc, const rwc_
             if (host[c].rr0 > 0) worst = std::fmax(worst, std::sqrt(host[c].rr / host[c].rr0));
         return fail(RWC_ERR_NOT_CONVERGED, "adjoint solves: worst relative residual %.3e after %d iterations", worst, it);
     }
+    if (progress.iters & 1)
+        hipLaunchKernelGGL(bpcg_finish, dim3(dir_blocks), dim3(kBlock), 0, s, n, v, R, L.sc, L.X, L.P32[0]);
     // 4. L^+ y = z - mean(z), the two scalars, and the per-edge gradient
     hipLaunchKernelGGL(column_partials, dim3(wave_blocks), dim3(kBlock), 0, s, n, R, rows_per_block, L.X, L.part);
     hipLaunchKernelGGL(column_finish, dim3(R), dim3(kBlock), 0, s, static_cast<int32_t>(wave_blocks), L.part,

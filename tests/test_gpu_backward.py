@@ -224,3 +224,18 @@ def test_iterations_past_convergence_change_nothing():
     assert iters[0] == iters[1] == iters[2], iters
     for r in runs[1:]:
         assert torch.equal(r["grad_w"], runs[0]["grad_w"])
+
+
+@pytest.mark.parametrize("check_every", [0, 1, 3])
+def test_odd_and_even_iteration_counts(check_every):
+    """The iterate takes two iterations' steps at a time: solves of one iteration (a star grounded at its
+    centre), of a few and of odd and even counts against the dense gradient, at the module's bound."""
+    parity = set()
+    for g in [G.star_graph(9)] + [G.path_graph(n) for n in range(3, 11)] + [_graph(n, 3, n) for n in (40, 55, 80, 130)]:
+        w = np.ones(g.m, np.float32) if g.w is None else g.w
+        gd = np.zeros(g.n)
+        gd[[1, g.n - 1]] = [1.0, -0.5]
+        r = P.backward(P.Graph(g.n, g.src, g.dst, w), torch.tensor(gd, device="cuda"), k=0, tol=1e-12, check_every=check_every)
+        _close(r["grad_w"].cpu().numpy(), GR.grad_exact(g.n, g.src, g.dst, w, gd), 1e-7)
+        parity.add(r["iters"] % 2)
+    assert parity == {0, 1}
