@@ -871,8 +871,8 @@ __global__ void __launch_bounds__(kPanelBlock) fc_panel(FcArgs A, int32_t p, int
 // The last kRing columns are also kept in LDS, up to kRingLen entries each, and a column with a window
 // of at most kRingWindow and at most kInvEntries distinct rows stays in LDS altogether: its rows are
 // found in a hash table while it waits, the sums are kept there, and the two orders (by magnitude, by row) are
-// ranks counted against all entries: 5.2 us a level (32.1 -> 11.6 ms; ER(1000, 5) 7.2 -> 1.9, 10 000-node grid
-// 146 -> 34).  The others have a dense accumulator, stamps and a touched list
+// ranks counted against all entries: 4.7 us a level (32.1 -> 10.4 ms; BA(20 000, 5) 18.6 -> 5.9). Eight
+// waves instead of sixteen: BA(5000, 5)'s call 17.9 instead of 18.2 ms, BA(20 000, 5)'s 105 instead of 102.  The others have a dense accumulator, stamps and a touched list
 // (a slice of N of each per wave) in the workspace, and order a column in LDS when it has at
 // most kInvLds nonzeros, else in their own kSortCap-entry slice of it (14 us a level).
 constexpr int kInvWaves = 16;
@@ -957,15 +957,23 @@ __device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t 
     for (int d = deps - 1; d >= 0 && !general; --d) {
         const int32_t c = __builtin_amdgcn_readlane(i, d), slot = c & (kRing - 1);
         int64_t spins = 0;
-        while (__builtin_amdgcn_readfirstlane(shared_load(&S->column[slot])) != c)
-            if (shared_load(&S->abort_all) != 0 || ++spins > kInvSpinLimit) return kInvStop;
+        int32_t len, r;
+        while (true) {   // what is read after the flag belongs to it
+            const int32_t held = shared_load(&S->column[slot]);
+            wave_order();
+            len = shared_load(&S->len[slot]);
+            r = shared_load(&S->row[slot * kRingLen + lane]);
+            const int32_t stop = shared_load(&S->abort_all);
+            if (__builtin_amdgcn_readfirstlane(held) == c) break;
+            if (stop != 0 || ++spins > kInvSpinLimit) return kInvStop;
+            __builtin_amdgcn_s_sleep(1);
+        }
         wave_order();
-        const int32_t len = __builtin_amdgcn_readfirstlane(S->len[slot]);
+        len = __builtin_amdgcn_readfirstlane(len);
         if (len < 0) {
             general = true;
             break;
         }
-        const int32_t r = S->row[slot * kRingLen + lane];
         uint32_t h = (static_cast<uint32_t>(r) * 0x9E3779B1u) >> 24;
         bool fresh = false, open = lane < len;
         while (__ballot(open) != 0ull) {   // at most kInvEntries + kRingLen rows in kInvTable places
@@ -1039,11 +1047,13 @@ __device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t 
     wave_order();
     int32_t keep = static_cast<int32_t>(nz);
     bool kept[2] = {live[0], live[1]};
+    // What every lane needs of all entries is read from LDS eight at a time (one at a time each read is
+    // waited for; from the lanes' registers, by v_readlane: 20.8 ms for BA(5000, 5)'s call).
     int listed = m;   // W->row's entries to order the kept ones by
     if (static_cast<int64_t>(nz) > A.zeta) {
         // by decreasing magnitude, ties by row
         double mag[2];
-        int32_t before[2] = {0, 0}, same[2] = {0, 0};
+        int32_t before[2] = {0, 0};
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             mag[k] = live[k] ? fabs(a[k]) : 0.0;
@@ -1051,17 +1061,26 @@ __device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t 
             W->row[lane + k * kWave] = row[k];
         }
         lds_order();
-        for (int j = 0; j < m; j += 4) {   // (past m: zeros, smaller than any)
+        for (int j = 0; j < m; j += 8) {   // (past m: zeros, which are larger than none)
+            double o[8];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double o = W->val[j + q];
-                before[0] += o > mag[0] ? 1 : 0;
-                same[0] += o == mag[0] ? 1 : 0;
-                before[1] += o > mag[1] ? 1 : 0;
-                same[1] += o == mag[1] ? 1 : 0;
+            for (int q = 0; q < 8; ++q) o[q] = W->val[j + q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) before[0] += o[q] > mag[0] ? 1 : 0;
+            if (m > kWave) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) before[1] += o[q] > mag[1] ? 1 : 0;
             }
         }
-        if (__ballot((live[0] && same[0] > 1) || (live[1] && same[1] > 1)) != 0ull) {
+        // equal magnitudes share a rank
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (live[k]) W->taken[before[k]] = static_cast<uint8_t>(lane + k * kWave);
+        lds_order();
+        bool shared = false;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) shared = shared || (live[k] && W->taken[before[k]] != lane + k * kWave);
+        if (__ballot(shared) != 0ull) {
             for (int j = 0; j < m; ++j) {
                 const double o = W->val[j];
                 const int32_t r = W->row[j];
@@ -1072,38 +1091,60 @@ __device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t 
         lds_order();
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-            if (live[k]) W->val[before[k]] = mag[k];
+        {
+            if (lane + k * kWave >= keep) W->val[lane + k * kWave] = 0.0;
+            if (live[k]) {
+                W->val[before[k]] = mag[k];
+                W->row[before[k]] = row[k];
+            }
+        }
         lds_order();
-        // the 1-norm in that order, then the tail grown from the smallest entry
+        // the 1-norm in that order (past the end zeros), then the tail grown from the smallest entry
         double l1 = 0.0;
-        for (int32_t j = 0; j < keep; ++j) l1 += W->val[j];
+        for (int32_t j = 0; j < keep; j += 8) {
+            double o[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o[q] = W->val[j + q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) l1 += o[q];
+        }
         const double lim = A.eps_p * l1;
         double tail = 0.0;
-        while (keep > 0) {
-            const double x = W->val[keep - 1];
-            if (!(tail + x <= lim)) break;
-            tail += x;
-            --keep;
+        for (bool more = true; more && keep > 0;) {
+            double o[8];
+            const int32_t from = keep;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o[q] = W->val[from > q ? from - 1 - q : 0];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const double next = tail + o[q];
+                more = more && from > q && next <= lim;
+                tail = more ? next : tail;
+                keep -= more ? 1 : 0;
+            }
         }
         keep = __builtin_amdgcn_readfirstlane(keep);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            kept[k] = live[k] && before[k] < keep;
-            if (kept[k]) W->row[before[k]] = row[k];
-        }
+        for (int k = 0; k < 2; ++k) kept[k] = live[k] && before[k] < keep;
         listed = keep;
     } else {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            W->row[lane + k * kWave] = live[k] ? row[k] : 0x7FFFFFFF;
+        for (int k = 0; k < 2; ++k) W->row[lane + k * kWave] = live[k] ? row[k] : 0x7FFFFFFF;
+        lds_order();
+    }
+    int32_t at[2] = {0, 0};   // by ascending row
+    for (int j = 0; j < listed; j += 8) {
+        int32_t r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = W->row[j + q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int32_t x = j + q < listed ? r[q] : 0x7FFFFFFF;
+            at[0] += x < row[0] ? 1 : 0;
+            at[1] += x < row[1] ? 1 : 0;
+        }
     }
     lds_order();
-    int32_t at[2] = {0, 0};   // by ascending row
-    for (int j = 0; j < listed; ++j) {
-        const int32_t r = W->row[j];
-        at[0] += r < row[0] ? 1 : 0;
-        at[1] += r < row[1] ? 1 : 0;
-    }
     if (!wait_for_slot(S, u)) return kInvStop;
     const int32_t slot = u & (kRing - 1);
 #pragma unroll
@@ -1133,9 +1174,12 @@ __device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t 
             A.s_val[sp + at[k]] = a[k];
         }
     double t2 = 0.0;   // ||S~(:, u)||^2 in row order
-    for (int32_t j = 0; j < keep; ++j) {
-        const double x = W->val[j];
-        t2 += x * x;
+    for (int32_t j = 0; j < keep; j += 8) {
+        double o[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) o[q] = j + q < keep ? W->val[j + q] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t2 += o[q] * o[q];
     }
     if (lane == 0) {
         A.s_start[u] = sp;
