@@ -1453,6 +1453,8 @@ bool use_dense(const rwc_fastchol_params* p, int32_t n) {
     return N * (N + 1) / 2 * sizeof(double) <= kDenseAutoBytes;
 }
 
+static_assert(2 * kPanel * sizeof(double) >= kInvWaves * 16);
+
 FcLayout carve_fc(void* ws, int32_t n, int64_t r_cap, int64_t s_cap, bool dense) {
     Carver c(ws);
     FcLayout L{};
@@ -1463,9 +1465,11 @@ FcLayout carve_fc(void* ws, int32_t n, int64_t r_cap, int64_t s_cap, bool dense)
     L.r_ptr = c.take<int64_t>(N + 1);
     L.s_start = c.take<int64_t>(N);
     L.s_len = c.take<int32_t>(N);
-    L.stamp = c.take<int32_t>(kInvWaves * N);
-    L.touched = c.take<int32_t>(kInvWaves * N);
-    L.acc = c.take<double>(kInvWaves * N);
+    // the accumulators, stamps and touched lists of the inverse (and the chain); before them, the dense
+    // form's panels, which are larger
+    L.acc = c.take<double>(2 * kPanel * N);
+    L.stamp = reinterpret_cast<int32_t*>(L.acc + kInvWaves * N);
+    L.touched = L.stamp + kInvWaves * N;
     L.done = c.take<int32_t>(N);
     L.inv_val = c.take<double>(kInvWaves * kSortCap);
     L.inv_row = c.take<int32_t>(kInvWaves * kSortCap);
@@ -1481,7 +1485,7 @@ FcLayout carve_fc(void* ws, int32_t n, int64_t r_cap, int64_t s_cap, bool dense)
     } else {
         L.colnorm = c.take<double>(N);
         L.parts = static_cast<int32_t>((N + kPanelRows - 1) / kPanelRows);
-        L.prow = c.take<double>(2 * N * kPanel);
+        L.prow = L.acc;
         L.pmask = c.take<uint32_t>(2 * N);
         L.pnext = c.take<double>(2 * kPanel * kPanel);
         L.act = c.take<int32_t>(static_cast<size_t>(2) * L.parts * kPanelRows);
@@ -1580,13 +1584,12 @@ extern "C" int rwc_fastchol(const rwc_csr* g, const rwc_fastchol_params* p, doub
     A.counters = L.counters;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(fc_begin, dim3(1), dim3(kWave), 0, s, A);
-    {
-        const int64_t N = g->n - 1;
+    const int64_t N = g->n - 1;
+    auto clear_stamps = [&] {
         hipLaunchKernelGGL(fill_i32, dim3(blocks_for(kInvWaves * N, 256)), dim3(256), 0, s, L.stamp, kInvWaves * N, 0);
-        hipLaunchKernelGGL(fill_i32, dim3(blocks_for(N, 256)), dim3(256), 0, s, L.done, N, 0);
-    }
+    };
+    hipLaunchKernelGGL(fill_i32, dim3(blocks_for(N, 256)), dim3(256), 0, s, L.done, N, 0);
     if (dense) {
-        const int64_t N = g->n - 1;
         const int64_t cells = N * (N + 1) / 2;
         hipLaunchKernelGGL(fc_dense_clear, dim3(static_cast<unsigned>(std::min<int64_t>(blocks_for(cells, 256), 8192))),
                            dim3(256), 0, s, reinterpret_cast<uint64_t*>(L.dense), cells);
@@ -1602,7 +1605,9 @@ extern "C" int rwc_fastchol(const rwc_csr* g, const rwc_fastchol_params* p, doub
             hipLaunchKernelGGL(fc_panel, dim3(static_cast<unsigned>(form + copy + tiles)), dim3(kPanelBlock), 0, s, A,
                                static_cast<int32_t>(q), static_cast<int32_t>(form), static_cast<int32_t>(copy));
         }
+        clear_stamps();   // where the panels were
     } else {
+        clear_stamps();
         hipLaunchKernelGGL(fc_ichol, dim3(1), dim3(kWave), 0, s, A);
     }
     hipLaunchKernelGGL(fc_inverse, dim3(1), dim3(kInvWaves * kWave), sizeof(InvShared), s, A);
