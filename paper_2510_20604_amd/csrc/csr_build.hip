@@ -1330,8 +1330,9 @@ extern "C" int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src, const 
     }
     host.nroots = 1;
     if (host.bfs_tail != static_cast<uint32_t>(n)) {
-        // several components: label them (the entry sort's arrays are free again)
-        int32_t* parent = L.vals_a;
+        // several components: label them (an array of the node sort, n words: the entry sort's hold 2m,
+        // which isolated nodes make fewer)
+        int32_t* parent = L.nvals_b;
         hipLaunchKernelGGL(uf_init, grid(n), dim3(kBlock), 0, s, n, parent);
         hipLaunchKernelGGL(uf_hook, grid(m), dim3(kBlock), 0, s, m, src, dst, parent);
         hipLaunchKernelGGL(uf_count_roots, grid(n), dim3(kBlock), 0, s, n, parent, L.scalars);

@@ -2,10 +2,13 @@
 group of lanes, one block and the rows taken by whole blocks, tiles of the sort, and breadth-
 first levels that are narrow, wide, and expanded from the unreached nodes with short, long and
 very long unreached rows.  Checked against the oracle's CSR and SciPy's distances, exactly."""
+import ctypes
+
 import numpy as np
 import pytest
 import scipy.sparse as sp
 import scipy.sparse.csgraph as csg
+import torch
 
 import rwcgen
 from oracle import wilson as W
@@ -86,3 +89,51 @@ def test_build_at_the_edges_of_its_kernels(name, weighted):
     dist = csg.shortest_path(A, unweighted=True, indices=o.pivot)
     assert order[0] == Gd.csr.pivot_index and np.all(np.diff(dist[nid[order]]) >= 0)
     assert Gd.csr.bfs_depth == int(dist.max())
+
+
+def _build_guarded(n, src, dst, w, allow, guard=1 << 22):
+    """rwc_build_csr_ex on a workspace with `guard` bytes of a pattern behind it."""
+    L = P._lib.lib()
+    s, d = (torch.as_tensor(x, dtype=torch.int32).cuda() for x in (src, dst))
+    wt = None if w is None else torch.as_tensor(w).cuda()
+    size = ctypes.c_size_t()
+    assert L.rwc_build_csr_workspace(n, len(src), int(w is not None), ctypes.byref(size)) == 0
+    ws = torch.full((size.value + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    csr = P._lib.RwcCsr()
+    rc = L.rwc_build_csr_ex(n, len(src), s.data_ptr(), d.data_ptr(), None if wt is None else wt.data_ptr(), allow,
+                            ws.data_ptr(), size.value, ctypes.byref(csr), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert bool((ws[size.value:] == 0xA5).all()), "written past the workspace"
+
+    def view(addr, count):
+        off = addr - ws.data_ptr()
+        return ws[off:off + 4 * count].view(torch.int32).cpu().numpy()
+    return rc, csr, view
+
+
+@pytest.mark.parametrize("n,m,weighted", [(20000, 10, False), (100000, 300, True), (1000000, 100000, False), (65, 1, True)])
+def test_build_with_far_more_nodes_than_entries(n, m, weighted):
+    """Most nodes isolated: every array by node has to hold n entries where those by entry hold fewer.
+    Refused without the flag, and nothing behind the workspace is touched either way."""
+    rng = np.random.default_rng(n + m)
+    pairs = np.unique(np.sort(rng.integers(0, n, (2 * m, 2)), axis=1), axis=0)
+    pairs = rng.permutation(pairs[pairs[:, 0] != pairs[:, 1]])[:m]
+    src, dst = pairs[:, 0], pairs[:, 1]
+    w = rwcgen.uniform_weights(len(src), 0.5, 4.0, 3) if weighted else None
+    assert _build_guarded(n, src, dst, w, 0)[0] == -6
+    rc, csr, view = _build_guarded(n, src, dst, w, P._lib.RWC_BUILD_ALLOW_DISCONNECTED)
+    assert rc == 0
+    A = sp.csr_matrix((np.ones(len(src)), (src, dst)), shape=(n, n))
+    count, label = csg.connected_components(A, directed=False)
+    smallest = np.full(count, n)
+    np.minimum.at(smallest, label, np.arange(n))
+    assert csr.components == count
+    np.testing.assert_array_equal(view(csr.component, n), smallest[label])
+    order, node_id = view(csr.bfs_order, n), view(csr.node_id, n)
+    np.testing.assert_array_equal(np.sort(order), np.arange(n))
+    dist = csg.shortest_path(A, directed=False, unweighted=True, indices=csr.pivot)
+    reached = int(np.isfinite(dist).sum())
+    got = dist[node_id[order]]
+    assert order[0] == csr.pivot_index and np.all(np.diff(got[:reached]) >= 0)
+    assert csr.bfs_depth == int(got[reached - 1])
+    assert np.all(np.isinf(got[reached:])) and np.all(np.diff(order[reached:]) > 0)
