@@ -95,7 +95,10 @@ struct TokenLayout {
 };
 
 // Grows one tree; returns with the arrows and counts final.  Every thread of the work-group calls.
-// cnt: the departure counts, in the workspace.  ctl: two sets of (tokens kept, nodes popped).
+// cnt: the departure counts, in the workspace.  ctl: two sets of (tokens kept, nodes popped), and the
+// errors found while tokens walk.  *err decides for every thread whether a round is the last: it is
+// written only between the barrier after the walks and the one before it is read, so that no
+// thread of a new round changes it under another that still has to read it.
 template <bool kStrat, bool kWide>
 __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, uint64_t seed, const TokenLayout& P,
                                            RWC_LDS uint32_t* lists, const TokenTree<kWide>& W, RWC_GLOBAL uint32_t* cnt,
@@ -117,7 +120,7 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
         bits[i] = marks[words + i] = 0;
         marks[i] = ~0u;   // (bits past n are never looked at)
     }
-    if (t < 4) ctl[t] = 0;
+    if (t < 5) ctl[t] = 0;
     for (uint32_t v = t; v < n; v += T) {
         const bool root = G.rootmask ? ((G.rootmask[v >> 5] >> (v & 31)) & 1u) != 0 : static_cast<int32_t>(v) == G.root;
         W.set(v, root ? kDone | v : pop_draw<kStrat>(G, v, 0, sw, k0, k1));
@@ -150,7 +153,7 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
     auto draw_ahead = [&](uint32_t v) {
         const uint32_t k = cnt[v] + 1u;
         cnt[v] = k;
-        if (k >= kCntMax) lds_or(err, static_cast<uint32_t>(kErrCountOverflow));
+        if (k >= kCntMax) lds_or(&ctl[4], static_cast<uint32_t>(kErrCountOverflow));
         W.set_ready(v, pop_draw<kStrat>(G, v, k, sw, k0, k1));
     };
     bool sweep = true;
@@ -277,7 +280,9 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
             // the walker teams' guard on iterations, which bounds the rounds and, times 64 walkers, the
             // departures
             departures += npop;
-            if (++rounds > G.guard || departures / kWave > G.guard) lds_or(err, static_cast<uint32_t>(kErrStepLimit));
+            uint32_t found = ctl[4];
+            if (++rounds > G.guard || departures / kWave > G.guard) found |= static_cast<uint32_t>(kErrStepLimit);
+            if (found) lds_or(err, found);
         }
         __syncthreads();
         if (*err || (ntok == 0 && !sweep)) break;   // (no token: nothing was taken either)
@@ -317,7 +322,7 @@ __device__ __forceinline__ void token_item(const PopArgs& A, const DumpArgs& dum
 
 template <bool kStrat>
 __device__ __forceinline__ void token_graphs(const PopArgs& A, const DumpArgs& dumps, RWC_LDS uint32_t* lds) {
-    __shared__ uint32_t ctl[4];
+    __shared__ uint32_t ctl[5];
     pop_items(A, [&](int32_t graph, const GraphArgs& G, int64_t rel, bool first, RWC_LDS uint32_t* err,
                      RWC_LDS uint64_t* red) {
         if (G.n <= kTokenLdsNodes)
