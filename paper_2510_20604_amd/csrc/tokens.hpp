@@ -96,9 +96,9 @@ struct TokenLayout {
 
 // Grows one tree; returns with the arrows and counts final.  Every thread of the work-group calls.
 // cnt: the departure counts, in the workspace.  ctl: two sets of (tokens kept, nodes popped), and the
-// errors found while tokens walk.  *err decides for every thread whether a round is the last: it is
-// written only between the barrier after the walks and the one before it is read, so that no
-// thread of a new round changes it under another that still has to read it.
+// errors found while tokens walk.  Every thread decides by itself whether a round is the last, so no
+// word it looks at may change under another thread of a round further: *err is written between the
+// two barriers of a round and read after the second, ctl written before the first and read after it.
 template <bool kStrat, bool kWide>
 __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, uint64_t seed, const TokenLayout& P,
                                            RWC_LDS uint32_t* lists, const TokenTree<kWide>& W, RWC_GLOBAL uint32_t* cnt,
@@ -150,10 +150,10 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
         }
     };
     // the arrow after the one that v has just taken
-    auto draw_ahead = [&](uint32_t v) {
+    auto draw_ahead = [&](uint32_t v, RWC_LDS uint32_t* error) {
         const uint32_t k = cnt[v] + 1u;
         cnt[v] = k;
-        if (k >= kCntMax) lds_or(&ctl[4], static_cast<uint32_t>(kErrCountOverflow));
+        if (k >= kCntMax) lds_or(error, static_cast<uint32_t>(kErrCountOverflow));
         W.set_ready(v, pop_draw<kStrat>(G, v, k, sw, k0, k1));
     };
     bool sweep = true;
@@ -163,7 +163,7 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
     while (true) {
         const uint32_t a = cur * cap, b = (cur ^ 1) * cap;   // this round's and the next one's lists
         if (t >= walkers) {
-            for (uint32_t i = t - walkers; i < taken; i += T - walkers) draw_ahead(popped[b + i]);
+            for (uint32_t i = t - walkers; i < taken; i += T - walkers) draw_ahead(popped[b + i], &ctl[4]);
         } else {
             for (uint32_t i = t; i < ntok; i += walkers) {
                 const uint32_t c = origin[a + i], start = starts[a + i];
@@ -245,7 +245,7 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
                 }
             }
         __syncthreads();
-        const uint32_t kept = ctl[2 * cur], npop = ctl[2 * cur + 1];
+        const uint32_t kept = ctl[2 * cur], npop = ctl[2 * cur + 1], late = ctl[4];
         ++round;
         // the popped nodes take their next arrows; their tokens follow the kept ones
         auto take = [&](uint32_t v, uint32_t slot) {
@@ -266,7 +266,7 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
                 for (uint32_t w = bits[i]; w != 0; w &= w - 1) {
                     const uint32_t v = 32 * i + static_cast<uint32_t>(__builtin_ctz(w));
                     take(v, cap);
-                    draw_ahead(v);
+                    draw_ahead(v, err);
                 }
                 bits[i] = 0;
             }
@@ -280,9 +280,8 @@ __device__ __forceinline__ void token_tree(const GraphArgs& G, uint64_t sample, 
             // the walker teams' guard on iterations, which bounds the rounds and, times 64 walkers, the
             // departures
             departures += npop;
-            uint32_t found = ctl[4];
-            if (++rounds > G.guard || departures / kWave > G.guard) found |= static_cast<uint32_t>(kErrStepLimit);
-            if (found) lds_or(err, found);
+            if (++rounds > G.guard || departures / kWave > G.guard) lds_or(err, static_cast<uint32_t>(kErrStepLimit));
+            if (late) lds_or(err, late);
         }
         __syncthreads();
         if (*err || (ntok == 0 && !sweep)) break;   // (no token: nothing was taken either)
