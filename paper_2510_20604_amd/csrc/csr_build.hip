@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(kBlock)
     __syncthreads();
     const int sub = threadIdx.x & (kRowLanes - 1);
     RowPartial p{0, 0, 0x7FFFFFFF, 0, 0, 0};
-    auto entry = [&](int32_t i) -> uint64_t {
+    auto entry = [&](uint32_t i) -> uint64_t {
         if (i > 0 && keys[i - 1] == keys[i]) p.err |= kErrDupEdge;
         if (!w) return 1ull << 24;
         const float x = w[vals[i] >> 1];
@@ -432,8 +432,8 @@ __global__ void __launch_bounds__(kBlock)
         int32_t e[kRowsAhead];
 #pragma unroll
         for (int q = 0; q < kRowsAhead; ++q) {
-            const int32_t i = beg[q] + sub;
-            const bool have = i < end[q];
+            const uint32_t i = static_cast<uint32_t>(beg[q] + sub);
+            const bool have = sub < end[q] - beg[q];
             key[q] = have ? keys[i] : K{1};
             prev[q] = have && i > 0 ? keys[i - 1] : K{0};
             e[q] = have && w ? vals[i] >> 1 : 0;
@@ -441,7 +441,7 @@ __global__ void __launch_bounds__(kBlock)
         }
 #pragma unroll
         for (int q = 0; q < kRowsAhead; ++q) {
-            const bool have = beg[q] + sub < end[q];
+            const bool have = sub < end[q] - beg[q];
             const float x = have && w ? w[e[q]] : 1.0f;
             if (have && w) wrow[beg[q] + sub] = x;
             S[q] = have ? fixed_weight(x) : 0ull;
@@ -457,7 +457,8 @@ __global__ void __launch_bounds__(kBlock)
                 }
                 if (__shfl(slot, 0, kRowLanes) < kLongList) continue;
             }
-            for (int32_t i = beg[q] + sub + kRowLanes; i < end[q]; i += kRowLanes) S[q] = sat_add(S[q], entry(i));
+            for (uint32_t i = position(beg[q], sub + kRowLanes); i < position(end[q]); i += kRowLanes)
+                S[q] = sat_add(S[q], entry(i));
 #pragma unroll
             for (int off = kRowLanes / 2; off > 0; off >>= 1) S[q] = sat_add(S[q], __shfl_xor(S[q], off, kWave));
             if (sub == 0 && u[q] < n) {
@@ -472,7 +473,7 @@ __global__ void __launch_bounds__(kBlock)
         const int32_t u = long_rows[j];
         const int32_t beg = rows[u], end = rows[u + 1];
         uint64_t S = 0;
-        for (int32_t i = beg + static_cast<int32_t>(threadIdx.x); i < end; i += kBlock) S = sat_add(S, entry(i));
+        for (uint32_t i = position(beg, threadIdx.x); i < position(end); i += kBlock) S = sat_add(S, entry(i));
 #pragma unroll
         for (int off = kWave / 2; off > 0; off >>= 1) S = sat_add(S, __shfl_xor(S, off, kWave));
         __syncthreads();
@@ -768,7 +769,7 @@ __device__ __forceinline__ void bfs_finish(const BfsBuffer& b, int lane, int32_t
 
 // Visits entry k of a row (lanes with `have`; the whole wave calls): a neighbour still unreached
 // is claimed for the next level and buffered for the queue.
-__device__ __forceinline__ void bfs_expand(bool have, int32_t k, int lane, int32_t level,
+__device__ __forceinline__ void bfs_expand(bool have, uint32_t k, int lane, int32_t level,
                                            const int32_t* __restrict__ col, int32_t* __restrict__ dist,
                                            int32_t* __restrict__ order, BfsState* st, BfsBuffer& b) {
     int32_t w = 0;
@@ -813,7 +814,7 @@ __device__ __forceinline__ void bfs_up(int32_t n, int64_t wave, int64_t nw, int 
         }
         const bool short_row = end - beg <= kBfsGroupRow;
         bool found = false;
-        int32_t k = beg, stop = short_row ? end : beg;
+        uint32_t k = position(beg), stop = short_row ? position(end) : k;
         while (__any(k < stop)) {
             const bool hit = k + sub < stop && dist[col[k + sub]] == level;
             const uint64_t m = __ballot(hit);
@@ -827,7 +828,7 @@ __device__ __forceinline__ void bfs_up(int32_t n, int64_t wave, int64_t nw, int 
         while (rest) {   // longer rows: the whole wave, or every wave (bfs_long)
             const int src = __builtin_ctzll(rest);
             rest &= rest - 1;
-            const int32_t rb = __shfl(beg, src, kWave), re = __shfl(end, src, kWave);
+            const uint32_t rb = __shfl(position(beg), src, kWave), re = __shfl(position(end), src, kWave);
             if (re - rb > kBfsLongRow) {
                 uint32_t slot = 0;
                 if (lane == src) {
@@ -836,7 +837,7 @@ __device__ __forceinline__ void bfs_up(int32_t n, int64_t wave, int64_t nw, int 
                 }
                 if (__shfl(slot, src, kWave) < kBfsLongRows) continue;
             }
-            for (int32_t k0 = rb; k0 < re; k0 += kWave)
+            for (uint32_t k0 = rb; k0 < re; k0 += kWave)
                 if (__any(k0 + lane < re && dist[col[k0 + lane]] == level)) {
                     found = found || lane == src;
                     break;
@@ -878,14 +879,14 @@ __global__ void bfs_level(int32_t n, const int32_t* __restrict__ row_ptr, const 
             end = row_ptr[u + 1];
         }
         const bool short_row = end - beg <= kBfsGroupRow;
-        const int32_t stop = short_row ? end : beg;
-        for (int32_t k = beg + (lane & (kBfsLanes - 1)); __any(k < stop); k += kBfsLanes)
+        const uint32_t stop = position(short_row ? end : beg);
+        for (uint32_t k = position(beg, lane & (kBfsLanes - 1)); __any(k < stop); k += kBfsLanes)
             bfs_expand(k < stop, k, lane, level, col, dist, order, st, b);
         uint64_t rest = __ballot(!short_row && (lane & (kBfsLanes - 1)) == 0);
         while (rest) {
             const int src = __builtin_ctzll(rest);
             rest &= rest - 1;
-            const int32_t rb = __shfl(beg, src, kWave), re = __shfl(end, src, kWave);
+            const uint32_t rb = __shfl(position(beg), src, kWave), re = __shfl(position(end), src, kWave);
             if (re - rb > kBfsLongRow) {
                 uint32_t slot = 0;
                 if (lane == src) {
@@ -894,7 +895,7 @@ __global__ void bfs_level(int32_t n, const int32_t* __restrict__ row_ptr, const 
                 }
                 if (__shfl(slot, src, kWave) < kBfsLongRows) continue;
             }
-            for (int32_t k0 = rb; k0 < re; k0 += kWave)
+            for (uint32_t k0 = rb; k0 < re; k0 += kWave)
                 bfs_expand(k0 + lane < re, k0 + lane, lane, level, col, dist, order, st, b);
         }
     }
@@ -930,7 +931,7 @@ __global__ void bfs_long(const int32_t* __restrict__ row_ptr, const int32_t* __r
             continue;
         }
         for (int64_t k0 = beg + wave * kWave; k0 < end; k0 += nw * kWave)
-            bfs_expand(k0 + lane < end, static_cast<int32_t>(k0) + lane, lane, level, col, dist, order, st, b);
+            bfs_expand(k0 + lane < end, static_cast<uint32_t>(k0) + lane, lane, level, col, dist, order, st, b);
     }
     bfs_finish(b, lane, order, st);
 }
@@ -979,7 +980,7 @@ __global__ void __launch_bounds__(kNarrowThreads)
         edges = 0;
         for (int w = 0; w < kNarrowThreads / kWave; ++w) edges += wsum[w];
         if (edges > kNarrowEdges) break;
-        auto visit = [&](int32_t k) {
+        auto visit = [&](uint32_t k) {
             const int32_t w = col[k];
             if (dist[w] == -1 && atomicCAS(&dist[w], -1, level + 1) == -1) {
                 const uint32_t slot = atomicAdd(&found_count, 1u);
@@ -990,18 +991,18 @@ __global__ void __launch_bounds__(kNarrowThreads)
         for (uint32_t i = t / 8; i < size; i += kNarrowThreads / 8) {
             const int2 r = row[i];
             if (r.y - r.x <= kNarrowRow)
-                for (int32_t k = r.x + (t & 7); k < r.y; k += 8) visit(k);
+                for (uint32_t k = position(r.x, t & 7); k < position(r.y); k += 8) visit(k);
         }
         for (uint32_t i = wid; i < size; i += kNarrowThreads / kWave) {
             const int2 r = row[i];
             if (r.y - r.x > kNarrowRow && r.y - r.x <= kNarrowThreads)
-                for (int32_t k = r.x + lane; k < r.y; k += kWave) visit(k);
+                for (uint32_t k = position(r.x, lane); k < position(r.y); k += kWave) visit(k);
         }
         if (any_wide)   // at most kNarrowEdges / kNarrowThreads such rows
             for (uint32_t i = 0; i < size; ++i) {
                 const int2 r = row[i];
                 if (r.y - r.x > kNarrowThreads)
-                    for (int32_t k = r.x + t; k < r.y; k += kNarrowThreads) visit(k);
+                    for (uint32_t k = position(r.x, t); k < position(r.y); k += kNarrowThreads) visit(k);
             }
         __syncthreads();
         const uint32_t found = found_count;

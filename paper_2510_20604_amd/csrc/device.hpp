@@ -19,6 +19,11 @@ __device__ __forceinline__ RWC_GLOBAL T* global_ptr(T* p) {
     return (RWC_GLOBAL T*)p;
 }
 #define RWC_LDS __attribute__((address_space(3)))
+// Position `ahead` past a row offset.  Offsets go up to 2^31 - 2, so a loop that steps over a row's
+// entries must count without a sign: its last step may pass 2^31.
+__device__ __forceinline__ uint32_t position(int32_t offset, uint32_t ahead = 0) {
+    return static_cast<uint32_t>(offset) + ahead;
+}
 // Waits until every vector memory operation of this wave has completed, including copies
 // from memory into LDS, which the compiler does not track (s_waitcnt vmcnt(0)).
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70); }

@@ -231,8 +231,9 @@ __global__ void __launch_bounds__(kIterBlock)
             const double du = d[u];
             const double pu = dir.at(u);
             double s = 0.0;
-            int32_t k = beg + sub;
-            for (; k + 3 * kLanes < end; k += 4 * kLanes) {
+            uint32_t k = position(beg, sub);
+            const uint32_t stop = position(end);
+            for (; k + 3 * kLanes < stop; k += 4 * kLanes) {
                 int32_t c[4];
                 float w[4];
                 double x[4];
@@ -246,7 +247,7 @@ __global__ void __launch_bounds__(kIterBlock)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) s += static_cast<double>(w[i]) * x[i];
             }
-            for (; k < end; k += kLanes) s += static_cast<double>(weight[k]) * dir.at(col[k]);
+            for (; k < stop; k += kLanes) s += static_cast<double>(weight[k]) * dir.at(col[k]);
 #pragma unroll
             for (int off = kLanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
             if (sub == 0) {
@@ -276,7 +277,7 @@ __global__ void __launch_bounds__(kIterBlock)
                 const int64_t r = base + (wv * kWave + bit) * nb;
                 const int32_t rb = row_ptr[r], re = row_ptr[r + 1];
                 double s = 0.0;
-                for (int32_t k = rb + static_cast<int32_t>(threadIdx.x); k < re; k += kIterBlock)
+                for (uint32_t k = position(rb, threadIdx.x); k < position(re); k += kIterBlock)
                     s += static_cast<double>(weight[k]) * dir.at(col[k]);
                 s = block_sum(s, lds[turn]);
                 turn ^= 1;   // the other array's readers have passed this sum's barrier

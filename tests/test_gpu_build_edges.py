@@ -137,3 +137,50 @@ def test_build_with_far_more_nodes_than_entries(n, m, weighted):
     assert order[0] == csr.pivot_index and np.all(np.diff(got[:reached]) >= 0)
     assert csr.bfs_depth == int(got[reached - 1])
     assert np.all(np.isinf(got[reached:])) and np.all(np.diff(order[reached:]) > 0)
+
+
+def test_largest_entry_count():
+    """2^30 - 1 edges, the most a graph may have: every node joined to the 1023 that follow it on a ring and
+    (almost every one) to the 1024th, and 64 leaves, whose short rows end at entry 2^31 - 2.  Loops over
+    the last rows step past 2^31.  The build, and the pivot solve's residual from the ring's sums."""
+    N, D, leaves = 1 << 20, 1023, 64
+    n, m = N + leaves, (1 << 30) - 1
+    node = torch.arange(N, dtype=torch.int32, device="cuda")
+    extra = m - N * D - leaves                       # of the 1024th neighbours
+    at = torch.arange(leaves, dtype=torch.int32, device="cuda") * 16381 + 5
+    src = torch.cat([node.repeat(D), node[:extra], at])
+    dst = torch.cat([((node[None, :] + torch.arange(1, D + 1, dtype=torch.int32, device="cuda")[:, None]) % N).flatten(),
+                     (node[:extra] + D + 1) % N, node[:leaves] + N])
+    assert src.numel() == dst.numel() == m
+    Gd = P.Graph(n, src, dst)
+    del src, dst
+    deg = torch.full((n,), 2 * D, dtype=torch.int64, device="cuda")
+    deg[:extra] += 1
+    deg[(node[:extra].long() + D + 1) % N] += 1
+    deg[at.long()] += 1
+    deg[N:] = 1
+    assert (Gd.nnz, Gd.internal_order, Gd.components) == (2 * m, 0, 1)
+    assert torch.equal(Gd.strength(), deg.double()) and Gd.pivot == int((deg == deg.max()).nonzero()[0])
+    ptr = Gd.row_ptr().long()
+    assert torch.equal(ptr[1:] - ptr[:-1], deg) and int(ptr[-1]) == 2 * m
+    # the longest way: half the ring (2^19) in steps of 1024, and a leaf
+    assert 512 <= Gd.csr.bfs_depth <= 514
+    assert torch.equal(Gd.bfs_order().sort().values, torch.arange(n, dtype=torch.int32, device="cuda"))
+    assert torch.equal(Gd.col()[-leaves:], at)
+    e = P.estimate(Gd, torch.ones(n, dtype=torch.int64, device="cuda"), 1)
+    h = e["hit"]
+    ring = h[:N]
+    y = torch.zeros(n, dtype=torch.float64, device="cuda")
+    for j in range(1, D + 1):
+        y[:N] += ring.roll(j) + ring.roll(-j)
+    far = (node[:extra].long() + D + 1) % N
+    y[:extra] += ring[far]
+    y[far] += ring[:extra]
+    y[at.long()] += h[N:]
+    y[N:] = ring[at.long()]
+    r = deg * h - y - deg
+    r[Gd.pivot] = 0.0
+    # the solve's 1e-12; rounding of sums of deg terms as large as h; and the drift of a residual updated
+    # once an iteration, by as much as a product with a matrix of norm 2 max(deg) rounds
+    bound = 1e-12 * float(deg.double().norm()) + 2.0 ** -52 * float((deg * h).norm()) * (64 + 4 * e["iters"])
+    assert float(r.norm()) <= bound
