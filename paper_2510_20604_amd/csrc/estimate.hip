@@ -172,11 +172,12 @@ struct Direction<true> {
     }
 };
 
-// y = L_v p on the grounded system (row and column v removed, p_v kept at zero), with p^T y.  Block b
-// owns rows b, b + nb, b + 2 nb, ... (nb blocks), so hub rows, which cluster at small ids in
-// power-law graphs, land in different blocks.  kLanes lanes share a short row (strided over its
-// entries, then a shuffle reduction; four on meshes, sixteen otherwise); rows longer than
-// 16 kLanes are left out of that pass and then taken one at a time, in order, by the whole block.
+// y = L_v p on the grounded system (row and column v removed, p_v kept at zero), with p^T y.  kLanes
+// lanes share a short row (strided over its entries, then a shuffle reduction; four on graphs of at
+// most three edges a node, sixteen otherwise); which block takes it is said below.  Rows longer than
+// 16 kLanes are left out of that pass and then taken one at a time, in order, by the whole block:
+// block b takes those among b, b + nb, b + 2 nb, ... (nb blocks), so that hub rows, which cluster at
+// small indices in power-law graphs, land in different blocks.
 // kPair: starts the iteration, and stores the new direction of the rows in zp_out.
 template <bool kPair, int kLanes>
 __global__ void __launch_bounds__(kIterBlock)
@@ -202,19 +203,23 @@ __global__ void __launch_bounds__(kIterBlock)
     constexpr int kGroups = kIterBlock / kLanes;
     const int64_t b = blockIdx.x, nb = gridDim.x;
     double acc = 0.0;
-    // A hub's row is as much work as many others, so with sixteen lanes rows are dealt to the blocks,
-    // eight neighbours at a time, which share cache lines (dealt one by one, four and eight at a time:
-    // BA(200 000, 5) 22.5, 17.9, 17.3 us, R-MAT of scale 21 119, 108, 108).  On meshes (four lanes) all
-    // rows are alike: a block takes consecutive ones, and each XCD's L2 a consecutive eighth of them,
-    // since blocks go round the XCDs (97 013-node mesh 14.9 us dealt, 7.0 us consecutive).
+    // A hub's row is as much work as many others, so rows are dealt to the blocks, eight neighbours at a
+    // time, which share cache lines (dealt one by one, four and eight at a time: BA(200 000, 5) 22.5, 17.9,
+    // 17.3 us, R-MAT of scale 21 119, 108, 108).  Where there are no long rows (four lanes, no row over 64
+    // entries: meshes, sparse random graphs) rows are alike enough that a block takes consecutive ones,
+    // and each XCD's L2 a consecutive eighth of them, since blocks go round the XCDs (97 013-node mesh
+    // 14.9 us dealt, 7.0 us consecutive).  Sparse graphs with hubs are dealt: there the rows that are just short
+    // enough lie side by side in the first blocks (solve of BA(200 000, 2): 2.62 ms consecutive, 2.06 dealt
+    // with sixteen lanes, 1.65 with four; a tree of 189 290 nodes with hubs 123, 107, 85 ms).
     constexpr int kXcds = 8;
+    const bool in_order = kLanes == 4 && max_degree <= kLongRow;
     const int64_t x = b % kXcds, chunk = x * (nb / kXcds) + (x < nb % kXcds ? x : nb % kXcds) + b / kXcds;
     // A row's loads form a chain (bounds, entries, gathers).  The next row's bounds and this
     // row's d and p are loaded before this row's entries, and a lane loads four entries, then
     // their four gathers, before it adds them (in entry order), so fewer latencies follow one
     // another.
     const int64_t ustep = static_cast<int64_t>(kGroups) * nb;
-    int64_t u = kLanes == 4 ? chunk * kGroups + group : (b + (group / 8) * nb) * 8 + group % 8;
+    int64_t u = in_order ? chunk * kGroups + group : (b + (group / 8) * nb) * 8 + group % 8;
     int32_t beg = 0, end = 0;
     if (u < n) {
         beg = row_ptr[u];
@@ -717,7 +722,7 @@ int pivot_solve(const rwc_csr* g, int32_t v, const EstLayout& L, const rwc_solve
         return outcome();
     }
     const bool pair = n <= kPairNodes;
-    const bool few = g->nnz <= 6 * static_cast<int64_t>(n);   // meshes: four lanes per row
+    const bool few = g->nnz <= 6 * static_cast<int64_t>(n);   // short rows on average: four lanes each
     const unsigned nb = std::min<unsigned>(blocks_for(n, kIterBlock), kIterBlocks);
     const unsigned nbs = std::min<unsigned>(blocks_for(static_cast<int64_t>(n) * (few ? 4 : 16), kIterBlock), kIterBlocks);
     const int np = static_cast<int>(nb), nps = static_cast<int>(nbs);

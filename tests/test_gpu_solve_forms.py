@@ -91,3 +91,15 @@ def test_longest_row_at_the_block_limit(degree):
     e = P.estimate_group(Gd, roots, torch.ones(g.n, dtype=torch.int64, device="cuda"), 1)
     want = _hitting_times(g, None, roots)
     np.testing.assert_allclose(e["hit"].cpu().numpy(), want, rtol=1e-9, atol=1e-9 * want.max())
+
+
+@pytest.mark.parametrize("n", [4200, 140000, 200001])
+def test_sparse_graphs_with_hubs(n):
+    """At most three edges a node (four lanes per row) and rows of any length: rows dealt to the blocks, in
+    one step and in several, with pairs and with three launches."""
+    g = G.barabasi_albert(n, 2, 5)
+    Gd = P.Graph(g.n, g.src, g.dst, None)
+    assert 2 * g.m <= 6 * g.n and Gd.csr.max_degree > 64
+    a = P.estimate(Gd, torch.ones(g.n, dtype=torch.int64, device="cuda"), 1)
+    want = _hitting_times(g, None, [Gd.pivot])
+    np.testing.assert_allclose(a["hit"].cpu().numpy(), want, rtol=1e-9, atol=1e-9 * want.max())
