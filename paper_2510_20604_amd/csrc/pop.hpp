@@ -137,17 +137,15 @@ struct PopCounts<false> {
     __device__ void set(uint32_t v, uint32_t c) const { p[v] = c; }
 };
 
-// Grows one tree; returns with the arrows and counts final.  Every thread of the work-group
-// calls; kPerThread * blockDim.x >= n.  counters: two sets of (cycle nodes, active nodes).
 // A round that walks: each changed node follows its path, four steps between two looks, until it is
 // back, meets a node known to lead to the root, or has gone round a cycle it is not on (Brent's
 // algorithm); a lane back at its node lists the cycle's nodes.
-__device__ __forceinline__ void pop_walk(bool all, uint32_t changed, const RWC_LDS uint16_t* old_list, RWC_LDS uint16_t* nx,
+__device__ __forceinline__ void pop_walk(uint32_t changed, const RWC_LDS uint16_t* old_list, RWC_LDS uint16_t* nx,
                                          RWC_LDS uint32_t* bits, RWC_LDS uint16_t* new_list, uint32_t cap,
                                          RWC_LDS uint32_t* found) {
     constexpr uint32_t kNode = kPopDone - 1u;
     for (uint32_t i = threadIdx.x; i < changed; i += blockDim.x) {
-        const uint32_t c = all ? i : old_list[i];
+        const uint32_t c = old_list[i];
         const uint32_t first = nx[c];
         if (first & kPopDone) continue;   // a root
         uint32_t p = first, mark = kPopDone, power = 2, lam = 0;   // (no node is kPopDone)
@@ -178,6 +176,14 @@ __device__ __forceinline__ void pop_walk(bool all, uint32_t changed, const RWC_L
     }
 }
 
+// A round after at most kWalkShare / 64 of the nodes changed walks (where the call's plan says so).  The
+// space of the doubled arrows then holds the list of changed nodes and the one the round makes in
+// its two halves, so a list that is walked must fit one: at most half of the nodes.
+constexpr int32_t kWalkShare = 16;
+static_assert(kWalkShare <= 32, "the changed nodes must fit half of the doubled arrows' space");
+
+// Grows one tree; returns with the arrows and counts final.  Every thread of the work-group
+// calls; kPerThread * blockDim.x >= n.  counters: two sets of (cycle nodes, active nodes).
 template <bool kStrat, bool kLdsCounts, int kPerThread>
 __device__ __forceinline__ void pop_tree(const GraphArgs& G, uint64_t sample, uint64_t seed, int32_t walk_share,
                                          const PopLayout& P,
@@ -212,7 +218,7 @@ __device__ __forceinline__ void pop_tree(const GraphArgs& G, uint64_t sample, ui
         if (static_cast<uint64_t>(popped) * 64u <= static_cast<uint64_t>(walk_share) * n) {
             const uint32_t from = at_list;
             at_list = half - at_list;
-            pop_walk(rounds == 0 && popped == n, popped, jump + from, nx, bits, jump + at_list, half, &found[0]);
+            pop_walk(popped, jump + from, nx, bits, jump + at_list, half, &found[0]);
             __syncthreads();
             popped = found[0];
             scan = popped > half;

@@ -896,7 +896,7 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
                         // Following only the changed nodes' paths pays where a thread would double many
                         // nodes' arrows (BA(20 000, 5), 2000 trees: 4.07 -> 2.40 ms; BA(8000, 5):
                         // 1.21 -> 1.12 ms, but ER(8000, 8), whose paths are long: 7.7 -> 8.6 ms).
-                        const int32_t walk_share = pc.nmax > kPopLdsCounts ? 16 : 0;
+                        const int32_t walk_share = pc.nmax > kPopLdsCounts ? kWalkShare : 0;
                         const PopArgs args{L.graphs, L.items + pc.first, pc.graphs, L.queue + 2 + c, p->sample_begin,
                                            l, p->seed, L.node_off, L.pop_slots, pc.slot_words,
                                            plan.pop_sums > 0 ? L.pop_sums : nullptr,
