@@ -89,6 +89,8 @@ typedef struct rwc_csr {
                               id (graphs whose largest degree exceeds four times the mean);
                               0: internal index = input id.  Placement only: no result
                               depends on it                                                 */
+    double weight_ratio;   /* largest over smallest edge weight (1 for unweighted graphs); decides
+                              plans only                                                    */
     int32_t* component;    /* [n] by input id: the smallest input id of the node's
                               connected component                                           */
 } rwc_csr;

@@ -48,7 +48,7 @@ class RwcCsr(ctypes.Structure):
                 ("col", c_vp), ("weight", c_vp), ("edge_id", c_vp), ("cdf", c_vp), ("strength", c_vp),
                 ("rec", c_vp), ("bfs_order", c_vp), ("bfs_depth", c_i32),
                 ("components", c_i32), ("node_id", c_vp), ("node_index", c_vp), ("pivot_index", c_i32),
-                ("internal_order", c_i32), ("component", c_vp)]
+                ("internal_order", c_i32), ("weight_ratio", c_dbl), ("component", c_vp)]
 
 
 class SampleParams(ctypes.Structure):

@@ -41,7 +41,7 @@ struct BuildScalars {
     uint32_t bfs_tail;    // nodes the breadth-first search reached
     int32_t bfs_done;
     int32_t bfs_depth;
-    int32_t reserved;
+    float min_w, max_w;   // smallest and largest edge weight
 };
 
 // ------------------------------------------------------------------ exclusive scan -----
@@ -350,8 +350,16 @@ __device__ __forceinline__ void for_rows(int32_t n, Body body) {
 struct RowPartial {
     uint64_t max_s, vol;
     int32_t arg, max_deg;   // input id of the largest row (smallest id on ties)
+    float min_w, max_w;     // of the entries' weights
     uint32_t err, reserved;
 };
+
+__device__ __forceinline__ RowPartial no_rows() { return RowPartial{0, 0, 0x7FFFFFFF, 0, 65536.0f, 0.5f, 0, 0}; }
+
+__device__ __forceinline__ void take_weight(RowPartial& p, float w) {
+    p.min_w = fminf(p.min_w, w);
+    p.max_w = fmaxf(p.max_w, w);
+}
 
 __device__ __forceinline__ void take_row(RowPartial& p, uint64_t S, int32_t u, int32_t deg) {
     if (S >= (1ull << 53)) p.err |= kErrStrength;
@@ -374,6 +382,8 @@ __device__ __forceinline__ void merge_partial(RowPartial& p, const RowPartial& q
         p.arg = q.arg;
     }
     p.max_deg = q.max_deg > p.max_deg ? q.max_deg : p.max_deg;
+    p.min_w = fminf(p.min_w, q.min_w);
+    p.max_w = fmaxf(p.max_w, q.max_w);
     p.err |= q.err;
 }
 
@@ -386,6 +396,8 @@ __device__ __forceinline__ RowPartial block_merge(RowPartial p, RowPartial* lds)
         q.vol = __shfl_xor(p.vol, off, kWave);
         q.arg = __shfl_xor(p.arg, off, kWave);
         q.max_deg = __shfl_xor(p.max_deg, off, kWave);
+        q.min_w = __shfl_xor(p.min_w, off, kWave);
+        q.max_w = __shfl_xor(p.max_w, off, kWave);
         q.err = __shfl_xor(p.err, off, kWave);
         merge_partial(p, q);
     }
@@ -398,7 +410,8 @@ __device__ __forceinline__ RowPartial block_merge(RowPartial p, RowPartial* lds)
 
 // Weighted degree (fixed point) of every input row, the entries' weights in row order (fill_rows
 // would gather them again: half of them are random lines), the repeated-edge check (equal
-// neighbours in the sorted keys), and per-block partials of vol, the largest row and the largest degree.
+// neighbours in the sorted keys), and per-block partials of vol, the largest row, the largest degree and
+// the range of the weights.
 template <class K>
 __global__ void __launch_bounds__(kBlock)
     row_sums(int32_t n, const K* __restrict__ keys, const int32_t* __restrict__ vals, const float* __restrict__ w,
@@ -411,12 +424,13 @@ __global__ void __launch_bounds__(kBlock)
     if (threadIdx.x == 0) nlong = 0;
     __syncthreads();
     const int sub = threadIdx.x & (kRowLanes - 1);
-    RowPartial p{0, 0, 0x7FFFFFFF, 0, 0, 0};
+    RowPartial p = no_rows();
     auto entry = [&](uint32_t i) -> uint64_t {
         if (i > 0 && keys[i - 1] == keys[i]) p.err |= kErrDupEdge;
         if (!w) return 1ull << 24;
         const float x = w[vals[i] >> 1];
         wrow[i] = x;
+        take_weight(p, x);
         return fixed_weight(x);
     };
     for_rows(n, [&](const int64_t (&u)[kRowsAhead]) {
@@ -443,7 +457,10 @@ __global__ void __launch_bounds__(kBlock)
         for (int q = 0; q < kRowsAhead; ++q) {
             const bool have = sub < end[q] - beg[q];
             const float x = have && w ? w[e[q]] : 1.0f;
-            if (have && w) wrow[beg[q] + sub] = x;
+            if (have && w) {
+                wrow[beg[q] + sub] = x;
+                take_weight(p, x);
+            }
             S[q] = have ? fixed_weight(x) : 0ull;
         }
 #pragma unroll
@@ -492,7 +509,7 @@ __global__ void __launch_bounds__(kBlock)
 
 __global__ void __launch_bounds__(kBlock) row_stats(int nparts, const RowPartial* __restrict__ parts, BuildScalars* sc) {
     __shared__ RowPartial lds[kBlock / kWave];
-    RowPartial p{0, 0, 0x7FFFFFFF, 0, 0, 0};
+    RowPartial p = no_rows();
     for (int i = threadIdx.x; i < nparts; i += kBlock) merge_partial(p, parts[i]);
     p = block_merge(p, lds);
     if (threadIdx.x == 0) {
@@ -500,6 +517,8 @@ __global__ void __launch_bounds__(kBlock) row_stats(int nparts, const RowPartial
         sc->vol_fixed = p.vol;
         sc->max_deg = p.max_deg;
         sc->pivot_id = p.arg;
+        sc->min_w = p.min_w;
+        sc->max_w = p.max_w;
         sc->status |= p.err;
     }
 }
@@ -1373,6 +1392,7 @@ extern "C" int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src, const 
     g.node_index = L.node_index;
     g.pivot_index = pivot_index;
     g.internal_order = by_strength ? 1 : 0;
+    g.weight_ratio = weighted ? static_cast<double>(host.max_w) / static_cast<double>(host.min_w) : 1.0;
     g.components = host.nroots;
     g.component = L.component;
     *out = g;

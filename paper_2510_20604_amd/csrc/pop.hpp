@@ -30,10 +30,11 @@
 // their own (tokens.hpp).
 //
 // What bounds it: the latency of a round (levels of two barriers and two LDS accesses, then a draw) while
-// the device is not full, and the issue of the levels' instructions once it is.  On graphs above
-// kPopLdsCounts a round costs too much that way (100 us for 20 000 nodes) when only few arrows changed: a cycle
-// runs through a node whose arrow changed in the round before, so such a round follows only
-// those nodes' paths (pop_walk).
+// the device is not full, and the issue of the levels' instructions once it is.  On large graphs a round
+// costs too much that way (100 us for 20 000 nodes) when only few arrows changed: a cycle runs through a
+// node whose arrow changed in the round before, so such a round follows only those nodes' paths
+// (pop_walk).  So it does on graphs with hubs, whose paths are short, and where heavy edges make many
+// rounds of few cycles (the rules: follows_changes in sampler.hip).
 //
 // A work-group adds its trees' visits up in the workspace and pop_reduce adds the work-groups' sums
 // (single graphs: an atomic per node and tree bounded large calls, 29 G/s: BA(2000, 4) x 20 000
@@ -67,7 +68,8 @@ struct PopLayout {
 
 struct PopArgs {
     const GraphArgs* graphs;
-    const Item* items;        // one per graph, in the order they are worked through
+    const Item* items;        // one per graph, in the order they are worked through; slot0 1: rounds of cycle_pop that
+                              // changed few arrows follow those nodes only
     int32_t ngraphs;
     uint32_t* queue;
     int64_t sample_begin, l;
@@ -81,7 +83,6 @@ struct PopArgs {
     int32_t* parents;
     uint64_t *tree_hash, *total_steps;
     uint32_t* status;
-    int32_t walk_share;       // rounds after at most walk_share / 64 n changed arrows follow those nodes only
 };
 
 __device__ __forceinline__ uint32_t lds_or(RWC_LDS uint32_t* p, uint32_t v) {
@@ -139,8 +140,10 @@ struct PopCounts<false> {
 
 // A round that walks: each changed node follows its path, four steps between two looks, until it is
 // back, meets a node known to lead to the root, or has gone round a cycle it is not on (Brent's
-// algorithm); a lane back at its node lists the cycle's nodes.
-__device__ __forceinline__ void pop_walk(uint32_t changed, const RWC_LDS uint16_t* old_list, RWC_LDS uint16_t* nx,
+// algorithm); a lane back at its node lists the cycle's nodes.  A call of its own: inlined, its registers and
+// place in the loop cost the rounds that double (ER(1000, 8), 2000 trees 664 and 679 us; BA(20 000, 5) 1966
+// and 1994).
+__device__ __attribute__((noinline)) void pop_walk(uint32_t changed, const RWC_LDS uint16_t* old_list, RWC_LDS uint16_t* nx,
                                          RWC_LDS uint32_t* bits, RWC_LDS uint16_t* new_list, uint32_t cap,
                                          RWC_LDS uint32_t* found) {
     constexpr uint32_t kNode = kPopDone - 1u;
@@ -176,7 +179,7 @@ __device__ __forceinline__ void pop_walk(uint32_t changed, const RWC_LDS uint16_
     }
 }
 
-// A round after at most kWalkShare / 64 of the nodes changed walks (where the call's plan says so).  The
+// A round after at most kWalkShare / 64 of the nodes changed walks (on graphs that the plan says so of).  The
 // space of the doubled arrows then holds the list of changed nodes and the one the round makes in
 // its two halves, so a list that is walked must fit one: at most half of the nodes.
 constexpr int32_t kWalkShare = 16;
@@ -186,8 +189,7 @@ static_assert(kWalkShare <= 32, "the changed nodes must fit half of the doubled 
 // calls; kPerThread * blockDim.x >= n.  counters: two sets of (cycle nodes, active nodes).
 template <bool kStrat, bool kLdsCounts, int kPerThread>
 __device__ __forceinline__ void pop_tree(const GraphArgs& G, uint64_t sample, uint64_t seed, int32_t walk_share,
-                                         const PopLayout& P,
-                                         RWC_LDS uint32_t* lds, PopCounts<kLdsCounts> cnt, RWC_LDS uint32_t* counters,
+                                         const PopLayout& P, RWC_LDS uint32_t* lds, PopCounts<kLdsCounts> cnt, RWC_LDS uint32_t* counters,
                                          RWC_LDS uint32_t* err) {
     RWC_LDS uint16_t* const nx = (RWC_LDS uint16_t*)lds;
     RWC_LDS uint16_t* const jump = (RWC_LDS uint16_t*)(lds + P.arrows);
@@ -367,8 +369,8 @@ __device__ __forceinline__ void finish_tree(const PopArgs& A, const DumpArgs& du
 
 template <bool kStrat, bool kLdsCounts, int kPerThread>
 __device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps, const GraphArgs& G, int32_t graph,
-                                         int64_t rel, bool first, RWC_LDS uint32_t* lds, RWC_LDS uint32_t* counters,
-                                         RWC_LDS uint32_t* err, RWC_LDS uint64_t* red) {
+                                         int64_t rel, int32_t walk_share, bool first, RWC_LDS uint32_t* lds,
+                                         RWC_LDS uint32_t* counters, RWC_LDS uint32_t* err, RWC_LDS uint64_t* red) {
     const PopLayout P(G.n);
     RWC_LDS uint16_t* const nx = (RWC_LDS uint16_t*)lds;
     PopCounts<kLdsCounts> cnt;
@@ -377,7 +379,7 @@ __device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps
     else
         cnt.p = global_ptr(A.slots + static_cast<int64_t>(blockIdx.x) * A.slot_stride);
     if (threadIdx.x == 0) *err = 0;
-    pop_tree<kStrat, kLdsCounts, kPerThread>(G, static_cast<uint64_t>(A.sample_begin + rel), A.seed, A.walk_share, P, lds,
+    pop_tree<kStrat, kLdsCounts, kPerThread>(G, static_cast<uint64_t>(A.sample_begin + rel), A.seed, walk_share, P, lds,
                                              cnt, counters, err);
     finish_tree(
         A, dumps, G, graph, rel, first, [&](int32_t x) { return cnt.get(x); },
@@ -385,7 +387,7 @@ __device__ __forceinline__ void pop_item(const PopArgs& A, const DumpArgs& dumps
 }
 
 // Persistent: work-groups pop trees, graph by graph, from `queue`, and hand them to
-// grow(graph, arguments, sample, first of this work-group, error word, scratch).
+// grow(item, arguments, sample, first of this work-group, error word, scratch).
 template <class Grow>
 __device__ __forceinline__ void pop_items(const PopArgs& A, Grow grow) {
     __shared__ uint32_t err, next_item, bad;
@@ -402,9 +404,9 @@ __device__ __forceinline__ void pop_items(const PopArgs& A, Grow grow) {
         const int64_t idx = next_item;
         __syncthreads();
         if (idx >= total) break;
-        const int32_t graph = A.items[idx / A.l].graph;
-        const GraphArgs G = A.graphs[graph];
-        grow(graph, G, idx % A.l, first, (RWC_LDS uint32_t*)&err, (RWC_LDS uint64_t*)red);
+        const Item it = A.items[idx / A.l];
+        const GraphArgs G = A.graphs[it.graph];
+        grow(it, G, idx % A.l, first, (RWC_LDS uint32_t*)&err, (RWC_LDS uint64_t*)red);
         first = false;
     }
     if (A.sums && first)   // no tree for this work-group
@@ -415,12 +417,15 @@ __device__ __forceinline__ void pop_items(const PopArgs& A, Grow grow) {
 template <bool kStrat, int kPerThread>
 __device__ __forceinline__ void pop_graphs(const PopArgs& A, const DumpArgs& dumps, RWC_LDS uint32_t* lds) {
     __shared__ uint32_t counters[4];
-    pop_items(A, [&](int32_t graph, const GraphArgs& G, int64_t rel, bool first, RWC_LDS uint32_t* err,
+    pop_items(A, [&](const Item& it, const GraphArgs& G, int64_t rel, bool first, RWC_LDS uint32_t* err,
                      RWC_LDS uint64_t* red) {
+        const int32_t walk_share = __builtin_amdgcn_readfirstlane(it.slot0) ? kWalkShare : 0;
         if (G.n <= kPopLdsCounts)
-            pop_item<kStrat, true, kPerThread>(A, dumps, G, graph, rel, first, lds, (RWC_LDS uint32_t*)counters, err, red);
+            pop_item<kStrat, true, kPerThread>(A, dumps, G, it.graph, rel, walk_share, first, lds,
+                                               (RWC_LDS uint32_t*)counters, err, red);
         else
-            pop_item<kStrat, false, kPerThread>(A, dumps, G, graph, rel, first, lds, (RWC_LDS uint32_t*)counters, err, red);
+            pop_item<kStrat, false, kPerThread>(A, dumps, G, it.graph, rel, walk_share, first, lds,
+                                                (RWC_LDS uint32_t*)counters, err, red);
     });
 }
 

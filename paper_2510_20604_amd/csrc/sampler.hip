@@ -277,6 +277,13 @@ int auto_walkers(int64_t n) {
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+// Nodes in all trees of a call.
+int64_t nodes_in_trees(const rwc_csr* graphs, int32_t G, int64_t l) {
+    int64_t n = 0;
+    for (int32_t g = 0; g < G; ++g) n += graphs[g].n;
+    return l > 0 && n > INT64_MAX / l ? INT64_MAX : n * l;
+}
+
 int pop_class(const rwc_csr& g) {
     if (g.bfs_depth <= kLongWalkDepth) return kPopWorld;
     return g.n > kTokenLdsNodes     ? kPopWide
@@ -290,29 +297,58 @@ int pop_class(const rwc_csr& g) {
 //
 // Small-world graphs (cycle_pop), measured against walker teams (walk and reduction): 1.2 to 5 times
 // faster (ER(300, 8) x 2000 trees 0.93 -> 0.24 ms, ER(1000, 8) x 2000 2.03 -> 0.67, BA(2000, 4)
-// x 500 0.45 -> 0.13, BA(20 000, 5) x 2000 3.76 -> 1.81, x 20 000 28.4 -> 15.7).  Above
-// kPopLdsCounts nodes a graph without hubs (largest degree under sqrt n) has long arrow paths and
-// many rounds, which only pays while a compute unit has few trees (ER(12 000, 8) x 500 trees
-// 14.4 -> 8.3 ms, but x 2000 16.4 -> 17.4 and x 20 000 50.7 -> 120).
+// x 500 0.45 -> 0.13, BA(20 000, 5) x 2000 3.76 -> 1.81, x 20 000 28.4 -> 15.7).  A graph without hubs
+// (largest degree under sqrt n) has long arrow paths and many rounds: above kPopLdsCounts nodes that only pays
+// while a compute unit has few trees (ER(12 000, 8) x 500 trees 14.4 -> 8.3 ms, but x 2000 16.4 -> 17.4 and
+// x 20 000 50.7 -> 120), and above kPopTeamNodes, where the teams' trees leave the LDS and more of them
+// are in flight, while it has some (ER(8000, 8) x 4000 trees 14.3 -> 11.4, x 20 000 32.5 -> 43.6).
+//
+// Weights: a round pops a pair of nodes joined by a heavy edge once, and a walker goes back and forth
+// over it as often, so wide weights slow both down, the rounds by their latency (one edge of 65535
+// among weights of 1: BA(20 000, 5) x 1000 trees 110 -> 66 ms, but x 4000 128 -> 161 and x 20 000 255 -> 621;
+// BA(4000, 2) x 20 000 68 -> 57).  So above kPopTeamNodes very wide weights pay up to kPopWideWork nodes in all
+// trees.  Between a ratio of kPopWideRatio and that, the rounds win once they follow the changed nodes only
+// (follows_changes).
 //
 // Meshes (mesh_pop): a tree takes about 20 sqrt n rounds, and as many trees run at once as the LDS
 // holds; walker teams take about 10 us a node for a tree (twice and more on unit weights), but
 // run 10 G steps/s, about 14 n steps a tree, once they fill the device.  So the rounds win while a
 // call has few trees of its large meshes, and always below 2048 nodes.
+constexpr int32_t kPopTeamNodes = kLdsStateBytes / 8;
+constexpr double kPopWideRatio = 64.0, kPopHeavyRatio = 4096.0;   // of the largest to the smallest weight
+constexpr int64_t kPopWideWork = 64000000;
+
+bool has_hubs(const rwc_csr& g) { return static_cast<int64_t>(g.max_degree) * g.max_degree >= g.n; }
+
+// Whether rounds of cycle_pop that changed few arrows follow those nodes' paths only (pop_walk): on graphs
+// whose counts are in the workspace (BA(20 000, 5), 2000 trees: 4.07 -> 2.40 ms); on those with hubs, whose
+// paths are short (BA(8000, 5) x 4000 trees 1.67 -> 1.25, x 1000 0.51 -> 0.37; up to 4096 nodes in calls of many
+// trees: BA(4000, 2) x 20 000 4.4 -> 3.0, but BA(4000, 5) x 1000 0.35 -> 0.38); and for wide weights, under
+// which most rounds change few arrows, above 4096 nodes and in calls of many trees (ER(8000, 8), weights
+// of 1 and 2 % of 100, x 1000 trees 19.1 -> 10.3 ms, teams 18.6; ER(4000, 8) x 20 000 65 -> 44, teams 55; but
+// x 1000 on weights from 0.5 to 64 2.5 -> 3.4).  Not otherwise: paths are long (ER(4000, 8), unit weights,
+// x 4000 trees 4.0 -> 7.0 ms, teams 7.0).  `nodes`: in all trees of the call.
+bool follows_changes(const rwc_csr& g, int64_t nodes) {
+    if (g.n > kPopLdsCounts) return true;
+    if (has_hubs(g) && (g.n > 4096 || (g.n > 2048 && nodes > 8000000))) return true;
+    return g.weight_ratio > kPopWideRatio && (g.n > 4096 || nodes > 20000000);
+}
+
 bool pops_cycles(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) {
     if (p->walkers_per_tree != 0 || p->walkers_per_graph || p->trees_in_flight > 0) return false;
     if (p->flags & (RWC_SAMPLE_NO_LDS_STATE | RWC_SAMPLE_PATH_RING)) return false;
     if (p->num_samples > kLdsMaxSamples || p->num_samples * G > (int64_t{1} << 30)) return false;
     const double cus = device_cu_count(), l = static_cast<double>(p->num_samples);
-    const bool few = p->num_samples * G <= 4 * device_cu_count();
+    const int64_t trees = p->num_samples * G, nodes = nodes_in_trees(graphs, G, p->num_samples);
     double rounds_us = 0.0, latest_us = 0.0, steps_us = 0.0;
     for (int32_t g = 0; g < G; ++g) {
         const int64_t n = graphs[g].n;
         const int c = pop_class(graphs[g]);
         if (n > (c == kPopWorld ? kPopMaxNodes : kTokenMaxNodes)) return false;
         if (c == kPopWorld) {
-            const bool hubs = static_cast<int64_t>(graphs[g].max_degree) * graphs[g].max_degree >= n;
-            if (n > kPopLdsCounts && !hubs && !few) return false;
+            if (n > kPopLdsCounts && !has_hubs(graphs[g]) && trees > 4 * device_cu_count()) return false;
+            if (n > kPopTeamNodes && !has_hubs(graphs[g]) && trees > 16 * device_cu_count()) return false;
+            if (n > kPopTeamNodes && graphs[g].weight_ratio > kPopHeavyRatio && nodes > kPopWideWork) return false;
         } else if (c != kPopSmall) {
             const double tree_us = 20.0 * std::sqrt(static_cast<double>(n)) * (c == kPopWide ? 25.0 : 5.0);
             rounds_us += tree_us * l / (cus * (c == kPopLarge ? 1.0 : 2.0));
@@ -661,9 +697,10 @@ int make_setup(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, voi
         if (!plan.lds[g])
             for (int32_t s0 = 0; s0 < plan.T[g]; s0 += plan.S[g]) S->items.push_back(Item{g, s0});
     S->nit_hbm = static_cast<int32_t>(S->items.size());
+    const int64_t in_trees = nodes_in_trees(graphs, G, l);
     for (int c = 0; c < static_cast<int>(plan.classes.size()); ++c)
         for (int32_t g : order)
-            if (pop_class(graphs[g]) == c) S->items.push_back(Item{g, 0});
+            if (pop_class(graphs[g]) == c) S->items.push_back(Item{g, follows_changes(graphs[g], in_trees) ? 1 : 0});
     for (int32_t g : order)
         if (plan.lds[g] && !plan.pop)
             for (int64_t s0 = 0; s0 < l; s0 += plan.S[g]) S->items.push_back(Item{g, static_cast<int32_t>(s0)});
@@ -893,15 +930,11 @@ extern "C" int rwc_sample_forests(const rwc_csr* graphs, int32_t G, const rwc_sa
                     for (int c = 0; c < kPopClasses; ++c) {
                         const PopClass& pc = plan.classes[c];
                         if (pc.graphs == 0) continue;
-                        // Following only the changed nodes' paths pays where a thread would double many
-                        // nodes' arrows (BA(20 000, 5), 2000 trees: 4.07 -> 2.40 ms; BA(8000, 5):
-                        // 1.21 -> 1.12 ms, but ER(8000, 8), whose paths are long: 7.7 -> 8.6 ms).
-                        const int32_t walk_share = pc.nmax > kPopLdsCounts ? kWalkShare : 0;
                         const PopArgs args{L.graphs, L.items + pc.first, pc.graphs, L.queue + 2 + c, p->sample_begin,
                                            l, p->seed, L.node_off, L.pop_slots, pc.slot_words,
                                            plan.pop_sums > 0 ? L.pop_sums : nullptr,
                                            plan.pop_sums > 0 ? plan.stride[0] : int64_t{0}, out->counts, out->counts_sq,
-                                           out->parents, out->tree_hash, out->total_steps, status, walk_share};
+                                           out->parents, out->tree_hash, out->total_steps, status};
                         hipLaunchKernelGGL(pop_kernel(c, pc, p->strata >= 2), dim3(static_cast<unsigned>(pc.grid)),
                                            dim3(pc.threads), static_cast<size_t>(pc.lds_words) * 4, ls, args, ldumps);
                         if (plan.pop_sums > 0)

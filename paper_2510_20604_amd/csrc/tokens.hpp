@@ -322,12 +322,12 @@ __device__ __forceinline__ void token_item(const PopArgs& A, const DumpArgs& dum
 template <bool kStrat>
 __device__ __forceinline__ void token_graphs(const PopArgs& A, const DumpArgs& dumps, RWC_LDS uint32_t* lds) {
     __shared__ uint32_t ctl[5];
-    pop_items(A, [&](int32_t graph, const GraphArgs& G, int64_t rel, bool first, RWC_LDS uint32_t* err,
+    pop_items(A, [&](const Item& it, const GraphArgs& G, int64_t rel, bool first, RWC_LDS uint32_t* err,
                      RWC_LDS uint64_t* red) {
         if (G.n <= kTokenLdsNodes)
-            token_item<kStrat, false>(A, dumps, G, graph, rel, first, lds, (RWC_LDS uint32_t*)ctl, err, red);
+            token_item<kStrat, false>(A, dumps, G, it.graph, rel, first, lds, (RWC_LDS uint32_t*)ctl, err, red);
         else
-            token_item<kStrat, true>(A, dumps, G, graph, rel, first, lds, (RWC_LDS uint32_t*)ctl, err, red);
+            token_item<kStrat, true>(A, dumps, G, it.graph, rel, first, lds, (RWC_LDS uint32_t*)ctl, err, red);
     });
 }
 

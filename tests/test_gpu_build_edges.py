@@ -184,3 +184,14 @@ def test_largest_entry_count():
     # once an iteration, by as much as a product with a matrix of norm 2 max(deg) rounds
     bound = 1e-12 * float(deg.double().norm()) + 2.0 ** -52 * float((deg * h).norm()) * (64 + 4 * e["iters"])
     assert float(r.norm()) <= bound
+
+
+@pytest.mark.parametrize("leaves,at", [(15, 14), (17, 16), (200, 199), (256, 255), (257, 0), (2000, 1777)])
+def test_weight_ratio(leaves, at):
+    """The largest over the smallest weight, wherever in a row they are: among the first sixteen entries, past
+    them, and in rows taken by a whole block."""
+    w = np.full(leaves, 2.0, np.float32)
+    w[at], w[leaves // 2] = 60000.0, 0.75
+    g = rwcgen.star_graph(leaves + 1)
+    assert P.Graph(g.n, g.src, g.dst, w).csr.weight_ratio == 80000.0
+    assert P.Graph(g.n, g.src, g.dst).csr.weight_ratio == 1.0

@@ -5,6 +5,7 @@ edge), root sets, stratified entries, batches, the same for the kernel of the me
 that keep the walker teams."""
 import numpy as np
 import pytest
+import torch
 
 import rwcgen as G
 from oracle import wilson as W
@@ -154,3 +155,33 @@ def test_calls_that_keep_the_walker_teams():
     with pytest.raises(P.RWCError) as ei:      # a faulty root set leaves trees without a root: reported, none grown
         P.sample_forests(P.Graph(small.n, small.src, small.dst), 40, 4, roots=[small.n, small.n + 1])
     assert ei.value.status == -2
+
+
+# rounds that follow the changed nodes only: hubs from 2049 nodes on in calls of many trees, wide weights above
+# 4096 nodes and in calls of many trees (er4097 and er4098 have one node less); a heavy edge makes hundreds of rounds of one cycle
+@pytest.mark.parametrize("name,l,heavy,strata", [("ba2048", 4000, 1.0, 0), ("ba2049", 4000, 1.0, 4096), ("er4098", 12, 2000.0, 0),
+                                                 ("er4097", 12, 2000.0, 0), ("ba8192", 12, 2000.0, 32), ("er1000", 20500, 200.0, 0)])
+def test_cycle_pop_with_heavy_edges_is_bit_exact(name, l, heavy, strata):
+    g = _graph(name)
+    w = np.where(np.random.default_rng(3).random(g.m) < 0.01, heavy, 1.0).astype(np.float32)
+    Gd = P.Graph(g.n, g.src, g.dst, w)
+    assert Gd.csr.weight_ratio == heavy
+    o = W.OracleCSR(g.n, g.src, g.dst, w)
+    ref = W.fastwalk_sample(o, o.pivot, 4001, 0, 2, l, want_parents=True, threads=8, strata=strata)
+    s = P.sample_forests(Gd, l, 4001, sample_begin=2, dump=[2, l + 1], strata=strata)
+    assert s["walk_kernel"] == ("cycle_pop_strata" if strata else "cycle_pop")
+    _check(s, ref, l)
+
+
+def test_many_trees_that_keep_the_walker_teams():
+    er = G.erdos_renyi_lcc(7000, 8, 2)     # no hubs, above the teams' LDS limit
+    ba = G.barabasi_albert(7000, 3, 2)
+    w = np.ones(ba.m, np.float32)
+    w[ba.m // 2] = 5000.0                  # one heavy edge, in many trees
+    most = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    for g, wt, few, many in ((er, None, most, most + 1), (ba, w, 9142, 9143)):
+        Gd = P.Graph(g.n, g.src, g.dst, wt)
+        a, b = (P.sample_forests(Gd, l, 3, want_hash=False) for l in (few, many))
+        assert a["walk_kernel"] == "cycle_pop" and b["walk_kernel"].startswith("wilson_team")
+        one = P.sample_forests(Gd, 1, 3, sample_begin=few, want_hash=False)
+        assert torch.equal(a["counts"] + one["counts"], b["counts"])

@@ -38,6 +38,9 @@ struct GraphArgs {
     int64_t stride;
 };
 struct DumpArgs {};
+struct Item {
+    int32_t graph, slot0;
+};
 struct PopArgs {
     uint32_t* slots;
     int64_t slot_stride, sample_begin;
