@@ -871,11 +871,15 @@ __global__ void __launch_bounds__(kPanelBlock) fc_panel(FcArgs A, int32_t p, int
 // The last kRing columns are also kept in LDS, up to kRingLen entries each, and a column with a window
 // of at most kRingWindow and at most kInvEntries distinct rows stays in LDS altogether: its rows are
 // found in a hash table while it waits, the sums are kept there, and the two orders (by magnitude, by row) are
-// ranks counted against all entries: 4.7 us a level (32.1 -> 10.4 ms; BA(20 000, 5) 18.6 -> 5.9). Eight
-// waves instead of sixteen: BA(5000, 5)'s call 17.9 instead of 18.2 ms, BA(20 000, 5)'s 105 instead of 102.  The others have a dense accumulator, stamps and a touched list
-// (a slice of N of each per wave) in the workspace, and order a column in LDS when it has at
-// most kInvLds nonzeros, else in their own kSortCap-entry slice of it (14 us a level).
+// ranks counted against all entries: 4.7 us a level (32.1 -> 10.4 ms; BA(20 000, 5) 18.6 -> 5.9).  Eight
+// waves instead of sixteen: BA(5000, 5)'s call 17.9 instead of 18.2 ms, BA(20 000, 5)'s 105 instead of 102.
+// The others have a dense accumulator, stamps and a touched list (a slice of N of each per wave) in the
+// workspace, and order a column in LDS when it has at most kInvLds nonzeros, else in their own
+// kSortCap-entry slice of it (14 us a level).  Windows over twice kRingWindow throughout make columns of
+// hundreds of entries, which eight waves do faster (BA(2000, 5), 128 columns: 402 ms, sixteen 412, held up
+// for slots in LDS that nothing reads 419); over kRingWindow sixteen (a 4000-node mesh, 33 columns: 96, 106).
 constexpr int kInvWaves = 16;
+constexpr int kInvWidestWaves = 8;
 constexpr int kInvLds = 512;
 constexpr int64_t kInvSpinLimit = int64_t{1} << 26;
 constexpr int kRing = 64;          // columns, a power of two
@@ -1189,9 +1193,10 @@ __device__ InvResult ring_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t 
     return kInvDone;
 }
 
-// Column u by the dense accumulator, the window's entries [c0 + 1, c1) of any number.
+// Column u by the dense accumulator, the window's entries [c0 + 1, c1) of any number.  ring: some column
+// may read it from LDS.
 __device__ InvResult general_column(const FcArgs& A, RWC_LDS InvShared* S, int32_t u, int64_t c0, int64_t c1, double ruu,
-                                    int64_t w) {
+                                    int64_t w, bool ring) {
     const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     const int64_t N = A.N;
     double* acc = A.acc + static_cast<int64_t>(wave) * N;
@@ -1354,6 +1359,7 @@ __device__ InvResult general_column(const FcArgs& A, RWC_LDS InvShared* S, int32
         A.tau[node_of_column(u, A.v)] = t2;
     }
     // the columns kept in LDS, then the table empty again
+    if (!ring) return kInvDone;
     if (!wait_for_slot(S, u)) return kInvStop;
     const int32_t slot = u & (kRing - 1);
     if (lane < keep && keep <= kRingLen) {
@@ -1383,7 +1389,11 @@ __global__ void __launch_bounds__(kInvWaves * kWave) fc_inverse(FcArgs A) {
     if (lane == 0) S->current[wave] = N;
     __syncthreads();
     const double dmax = *A.dmax;
-    while (shared_load(&S->abort_all) == 0) {
+    // with windows over kRingWindow columns throughout none is read from LDS, so none is held up until its slot
+    // there is free; with twice that, fewer accumulators and sort buffers share the caches better
+    const bool ring = A.ws < kRingWindow + 1 || N <= kRingWindow;
+    const int waves = ring || A.ws <= 2 * kRingWindow ? kInvWaves : kInvWidestWaves;
+    while (wave < waves && shared_load(&S->abort_all) == 0) {
         int32_t t = 0;
         if (lane == 0) t = __hip_atomic_fetch_add(&S->next_col, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         t = __builtin_amdgcn_readfirstlane(t);
@@ -1410,7 +1420,7 @@ __global__ void __launch_bounds__(kInvWaves * kWave) fc_inverse(FcArgs A) {
             }
             result = ring_column(A, S, u, ruu, i, coef, static_cast<int>(__popcll(__ballot(i >= 0))));
         }
-        if (result == kInvGeneral) result = general_column(A, S, u, c0, c1, ruu, w);
+        if (result == kInvGeneral) result = general_column(A, S, u, c0, c1, ruu, w, ring);
         if (result == kInvStop) {
             if (shared_load(&S->abort_all) == 0) inv_fail(A, S, static_cast<uint32_t>(kErrWait));   // a wait ran out (not expected)
             break;
