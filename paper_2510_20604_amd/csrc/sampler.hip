@@ -313,7 +313,12 @@ int pop_class(const rwc_csr& g) {
 // Meshes (mesh_pop): a tree takes about 20 sqrt n rounds, and as many trees run at once as the LDS
 // holds; walker teams take about 10 us a node for a tree (twice and more on unit weights), but
 // run 10 G steps/s, about 14 n steps a tree, once they fill the device.  So the rounds win while a
-// call has few trees of its large meshes, and always below 2048 nodes.
+// call has few trees of its large meshes, and always below 2048 nodes.  Wide meshes are counted as two
+// trees a compute unit; above 139 264 nodes the lists and bitmaps leave room for one, and the line
+// drawn for two still lies where the rounds win, since teams are far from 10 G steps/s there (160 000
+// nodes, weighted, x 2600 trees: rounds 2.40 s, teams 3.67; unit weights 4.45 and 7.45; 447 x 447
+// nodes, unit weights, x 3000 7.5 and 18.7).  Weights to 65535 change neither side's lead (grids of 700
+// to 60 000 nodes: the rounds 2 to 7 times faster wherever they are taken).
 constexpr int32_t kPopTeamNodes = kLdsStateBytes / 8;
 constexpr double kPopWideRatio = 64.0, kPopHeavyRatio = 4096.0;   // of the largest to the smallest weight
 constexpr int64_t kPopWideWork = 64000000;
