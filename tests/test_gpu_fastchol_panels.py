@@ -30,20 +30,31 @@ def test_panel_edges_match_the_oracle(columns, droptol):
 
 @pytest.mark.parametrize("name,window,zeta,eps_p", [
     ("ba", 16.0, 12, 1e-3), ("ba", 16.5, 12, 1e-3), ("ba", 33.0, 12, 1e-3),   # windows to 32 columns, to 33, all above
-    ("ba", 32.9, 12, 1e-3), ("ba", 64.0, 20, 1e-3), ("ba", 64.5, 20, 1e-3), ("ba", 150.0, 40, 1e-3),   # and far above
-    ("few", 32.0, 3, 1e-3), ("few", 40.0, 3, 1e-3), ("few", 100.0, 3, 1e-3),   # no more columns than LDS windows hold
-    ("some", 40.0, 3, 1e-3), ("some", 100.0, 3, 1e-3),                         # one more
     ("ba", 16.0, 63, 1e-3), ("ba", 16.0, 64, 1e-9), ("ba", 16.0, 70, 1e-3),   # columns of 64 entries and more
     ("ba", 16.0, 126, 0.0), ("ba", 16.0, 200, 0.0),                           # 128 distinct rows and more
     ("clique", 16.0, 10, 1e-3), ("cycle", 16.0, 0, 0.5), ("star", 16.0, 2, 1e-3)])   # equal magnitudes
 def test_inverse_columns_match_the_oracle(name, window, zeta, eps_p):
     """The inverse's columns in LDS and in the workspace, and both in one run, bit for bit."""
     g = {"ba": lambda: G.barabasi_albert(700, 4, 3), "clique": lambda: G.complete_graph(90),
-         "few": lambda: G.complete_graph(33), "some": lambda: G.complete_graph(34), "cycle": lambda: G.cycle_graph(200), "star": lambda: G.star_graph(300)}[name]()
+         "cycle": lambda: G.cycle_graph(200), "star": lambda: G.star_graph(300)}[name]()
     if name == "ba":
         g = g.with_weights(G.uniform_weights(g.m, 0.5, 2.0, 5))
     Gd = P.Graph(g.n, g.src, g.dst, g.w)
     tau, fnz, snz = _oracle(g, Gd.pivot, 1e-4, window, zeta, eps_p)
     r = P.fastchol(Gd, droptol=1e-4, window=window, zeta=zeta, eps_p=eps_p, factor_capacity=fnz, inverse_capacity=snz)
+    assert (r["factor_entries"], r["inverse_entries"]) == (fnz, snz)
+    np.testing.assert_array_equal(r["tau"].cpu().numpy(), tau)
+
+
+@pytest.mark.parametrize("columns", [32, 33, 699])
+@pytest.mark.parametrize("window,zeta", [(32.0, 3), (32.9, 12), (33.0, 12), (64.0, 20), (64.5, 20), (150.0, 40)])
+def test_long_windows_match_the_oracle(columns, window, zeta):
+    """Windows that no column in LDS serves (33 and more), the longest (over 64), and matrices of no more
+    columns than the windows in LDS hold, where they still do."""
+    g = G.complete_graph(columns + 1) if columns < 100 else G.barabasi_albert(columns + 1, 4, 3)
+    g = g.with_weights(G.uniform_weights(g.m, 0.5, 2.0, 5))
+    Gd = P.Graph(g.n, g.src, g.dst, g.w)
+    tau, fnz, snz = _oracle(g, Gd.pivot, 1e-4, window, zeta, 1e-3)
+    r = P.fastchol(Gd, droptol=1e-4, window=window, zeta=zeta, eps_p=1e-3, factor_capacity=fnz, inverse_capacity=snz)
     assert (r["factor_entries"], r["inverse_entries"]) == (fnz, snz)
     np.testing.assert_array_equal(r["tau"].cpu().numpy(), tau)
