@@ -178,6 +178,11 @@ int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src_dev, const int32_t
                                         most 2^24 samples) grows its trees in LDS instead:
                                         no HBM tree slots, LDS accesses for every state read
                                         and write (same forest)                            */
+#define RWC_SAMPLE_POP_CYCLES 1024u  /* pop the trees' cycles in rounds wherever a call that
+                                        leaves the plan open would, although this one also
+                                        asks for walkers, trees in flight, a path ring or
+                                        HBM state; those serve the calls that would not
+                                        (same forest)                                      */
 
 typedef struct rwc_sample_params {
     uint64_t seed;               /* Philox key (seed mod 2^32, seed >> 32)                 */
@@ -327,20 +332,22 @@ int rwc_sample_trap_walks(const rwc_csr* g, const rwc_trap_params* p, uint64_t* 
                           void* stream);
 
 typedef struct rwc_tune_result {
-    int32_t walkers_per_tree;    /* the winning walkers per tree                            */
-    int32_t trees_in_flight;     /* the winning trees in flight                              */
+    int32_t walkers_per_tree;    /* the fastest plan of walkers: walkers per tree           */
+    int32_t trees_in_flight;     /* and trees in flight                                      */
     double steps_per_s;          /* walk steps per second of the winning probe               */
-    int32_t candidates;          /* probes run (0 when served from the cache)                */
+    int32_t candidates;          /* plans of walkers probed (0 when served from the cache)   */
     int32_t cached;              /* 1 if the result came from the per-process cache          */
-    uint32_t flags;              /* schedule flags of the winner: for walker teams one of
+    uint32_t flags;              /* RWC_SAMPLE_POP_CYCLES alone when the open plan (cycles
+                                    popped in rounds) won; else the schedule flags of the
+                                    fastest plan of walkers: for teams one of
                                     each pair PATH_RING / NO_PATH_RING, SHARED_STARTS /
                                     SPREAD_STARTS, ID_STARTS / BFS_STARTS, or 0 when the
                                     automatic schedule won; 0 for one walker per tree       */
     int32_t reserved;
 } rwc_tune_result;
 
-/* Workspace for rwc_autotune_sampler: room for the largest candidate whose slot state fits
- * `budget_bytes`, plus one graph's counts. */
+/* Workspace for rwc_autotune_sampler: room for the largest candidate whose slot state (for the
+ * open plan, its workspace) fits `budget_bytes`, plus one graph's counts. */
 int rwc_autotune_workspace(const rwc_csr* g, const rwc_sample_params* p, int64_t budget_bytes,
                            size_t* bytes);
 
@@ -348,7 +355,9 @@ int rwc_autotune_workspace(const rwc_csr* g, const rwc_sample_params* p, int64_t
  * parameters `p` by timing one batch of each candidate on the real sample range: first 1, 8,
  * 16, 32 or 64 walkers per tree with one or two device-fulls of resident waves or all trees in
  * flight (slot state within budget_bytes) under the automatic schedule, then, for a winning
- * team, all eight combinations of path ring, start sharing and start order.  Caches the winner
+ * team, all eight combinations of path ring, start sharing and start order.  Where a call that
+ * leaves the plan open pops its cycles in rounds, that is timed too, on all num_samples trees.
+ * Use the result with p->walkers_per_tree, p->trees_in_flight and p->flags |= flags.  Caches the winner
  * per graph class (log2 n, mean degree, weighted, log2 l) for the process.  The forest does not
  * depend on the choice, only the speed.  Synchronises `stream`. */
 int rwc_autotune_sampler(const rwc_csr* g, const rwc_sample_params* p, int64_t budget_bytes,
@@ -360,8 +369,9 @@ typedef struct rwc_batch_tune_result {
     int32_t walkers_other;       /* walkers per tree for the other graphs                    */
     uint32_t flags;              /* the winner's schedule flags: one of each pair PATH_RING /
                                     NO_PATH_RING, ID_STARTS / BFS_STARTS, and NO_LDS_STATE or
-                                    0 (LDS-resident trees where they fit)                     */
-    int32_t candidates;          /* probes run (0 when served from the cache)                */
+                                    0 (LDS-resident trees where they fit); POP_CYCLES alone
+                                    when the open plan (cycles popped in rounds) won          */
+    int32_t candidates;          /* plans of walkers probed (0 when served from the cache)   */
     double steps_per_s;          /* walk steps per second of the winning probe               */
     int32_t probe_samples;       /* trees per graph in each probe                            */
     int32_t cached;              /* 1 if the result came from the per-process cache          */
@@ -376,7 +386,8 @@ int rwc_autotune_batch_workspace(const rwc_csr* graphs, int32_t num_graphs, cons
  * call's sample range: first the walkers per tree of the mesh-like graphs and of the others
  * (16, 32 or 64 each, nine probes) under the automatic schedule, then, for the winning pair,
  * the path ring on or off, ascending or breadth-first start order, and LDS-resident trees on
- * or off (eight probes).  Use the result with p->walkers_per_graph (mesh-like graphs, pivot
+ * or off (eight probes); and the open plan, where the probe's and the call's cycles are popped in
+ * rounds.  Use the result with p->walkers_per_graph (mesh-like graphs, pivot
  * eccentricity above 32, take walkers_mesh) and p->flags |= flags.  Cached per (number of
  * graphs, their total nodes and entries, probe size) for the process.  The forest does not
  * depend on the choice, only the speed.  Synchronises `stream`. */

@@ -27,6 +27,7 @@ RWC_SAMPLE_PATH_RING = 64
 RWC_SAMPLE_NO_PATH_RING = 128
 RWC_SAMPLE_ID_STARTS = 256
 RWC_SAMPLE_NO_LDS_STATE = 512
+RWC_SAMPLE_POP_CYCLES = 1024
 
 RWC_FASTCHOL_AUTO = 0   # rwc_fastchol_params.method
 RWC_FASTCHOL_CHAIN = 1

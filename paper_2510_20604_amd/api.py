@@ -148,6 +148,8 @@ def _sample_setup(gl, num_samples, seed, sample_begin, root, trees_in_flight, wa
         flags |= _lib.RWC_SAMPLE_PATH_RING if path_ring else _lib.RWC_SAMPLE_NO_PATH_RING
     if lds_state is False:
         flags |= _lib.RWC_SAMPLE_NO_LDS_STATE
+    elif lds_state == "pop":
+        flags |= _lib.RWC_SAMPLE_POP_CYCLES
     p = SampleParams(seed=seed, sample_begin=sample_begin, num_samples=num_samples, root=root, flags=flags,
                      trees_in_flight=trees_in_flight, walkers_per_tree=walkers_per_tree,
                      max_steps_per_tree=max_steps_per_tree, graph_index_base=graph_index_base,
@@ -186,7 +188,9 @@ def sample_forests(graphs: Graph | Sequence[Graph], num_samples: int, seed: int,
     `starts` ("auto", "shared", "spread"), `bfs_starts` (None = automatic, True =
     breadth-first from the root, False = ascending ids) and `path_ring` (None = automatic) pick
     how walker teams schedule their walks, and lds_state=False keeps every tree's state in HBM
-    (by default small graphs grow their trees in LDS, by popping cycles where the plan is open); the forest does not depend on them.  `roots` (ids,
+    (by default small graphs grow their trees in LDS, by popping cycles where the plan is open;
+    "pop", as the autotuners return it, pops them also where walkers, trees in flight or a path
+    ring are given, for the calls in which it pays); the forest does not depend on them.  `roots` (ids,
     single graph) samples spanning forests rooted at that set instead of trees rooted at one
     node.  `out` (a dict returned by an earlier call) reuses its output tensors, so that a
     repeated call with capture=True replays the library's cached hipGraph.  The call is
@@ -328,9 +332,10 @@ def sample_trap_walks(graph: Graph, num_walks: int, seed: int, walk_begin: int =
 def autotune(graph: Graph, num_samples: int, seed: int, sample_begin: int = 0,
              budget_bytes: int = 64 << 30) -> dict:
     """Times one batch of each candidate (walkers per tree and trees in flight, then the team
-    schedule) and returns the fastest (rwc_autotune_sampler); cached per graph class for the
-    process.  `path_ring`, `starts` and `bfs_starts` are the winner's schedule in the form
-    sample_forests takes (None / "auto" when the automatic schedule won)."""
+    schedule, and cycles popped in rounds where an open plan does that) and returns the fastest
+    (rwc_autotune_sampler); cached per graph class for the process.  `path_ring`, `starts`, `bfs_starts`
+    and `lds_state` are the winner's schedule in the form sample_forests takes (None / "auto" when the
+    automatic schedule won; lds_state "pop" when the rounds did, next to the fastest plan of walkers)."""
     L = _lib.lib()
     p = SampleParams(seed=seed, sample_begin=sample_begin, num_samples=num_samples, root=-1)
     size = ctypes.c_size_t()
@@ -347,13 +352,20 @@ def autotune(graph: Graph, num_samples: int, seed: int, sample_begin: int = 0,
             "path_ring": pick(_lib.RWC_SAMPLE_PATH_RING, _lib.RWC_SAMPLE_NO_PATH_RING, True, False, None),
             "starts": pick(_lib.RWC_SAMPLE_SPREAD_STARTS, _lib.RWC_SAMPLE_SHARED_STARTS, "spread", "shared", "auto"),
             "bfs_starts": pick(_lib.RWC_SAMPLE_BFS_STARTS, _lib.RWC_SAMPLE_ID_STARTS, True, False, None),
-            "lds_state": False if r.flags & _lib.RWC_SAMPLE_NO_LDS_STATE else None}
+            "lds_state": _lds_state(r.flags)}
+
+
+def _lds_state(flags: int):
+    if flags & _lib.RWC_SAMPLE_POP_CYCLES:
+        return "pop"
+    return False if flags & _lib.RWC_SAMPLE_NO_LDS_STATE else None
 
 
 def autotune_batch(graphs: Sequence[Graph], num_samples: int, seed: int, sample_begin: int = 0) -> dict:
     """rwc_autotune_batch: walkers per tree for the mesh-like graphs and for the others, then the
-    schedule, timed on probes of the whole batch.  Returns the choice in the form sample_forests
-    takes (walkers_per_graph, path_ring, bfs_starts, lds_state) plus the probe statistics."""
+    schedule, and cycles popped in rounds where an open plan does that, timed on probes of the whole
+    batch.  Returns the choice in the form sample_forests takes (walkers_per_graph, path_ring,
+    bfs_starts, lds_state; "pop" and an automatic schedule when the rounds won) plus the probe statistics."""
     L = _lib.lib()
     gl = list(graphs)
     arr = (RwcCsr * len(gl))(*[g.csr for g in gl])
@@ -367,11 +379,12 @@ def autotune_batch(graphs: Sequence[Graph], num_samples: int, seed: int, sample_
     check(L.rwc_autotune_batch(arr, len(gl), ctypes.byref(p), ctypes.byref(r), _ptr(ws), ws.numel(), _stream()),
           "rwc_autotune_batch")
     del ws
+    pop = bool(r.flags & _lib.RWC_SAMPLE_POP_CYCLES)
     wpg = [r.walkers_mesh if int(g.csr.bfs_depth) > 32 else r.walkers_other for g in gl]
     return {"walkers_mesh": r.walkers_mesh, "walkers_other": r.walkers_other, "walkers_per_graph": wpg,
-            "path_ring": bool(r.flags & _lib.RWC_SAMPLE_PATH_RING),
-            "bfs_starts": bool(r.flags & _lib.RWC_SAMPLE_BFS_STARTS),
-            "lds_state": False if r.flags & _lib.RWC_SAMPLE_NO_LDS_STATE else None,
+            "path_ring": None if pop else bool(r.flags & _lib.RWC_SAMPLE_PATH_RING),
+            "bfs_starts": None if pop else bool(r.flags & _lib.RWC_SAMPLE_BFS_STARTS),
+            "lds_state": _lds_state(r.flags),
             "flags": int(r.flags), "candidates": r.candidates, "steps_per_s": r.steps_per_s,
             "probe_samples": r.probe_samples, "cached": bool(r.cached)}
 

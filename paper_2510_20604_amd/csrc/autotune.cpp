@@ -1,7 +1,8 @@
 // rwc_autotune_sampler: picks walkers per tree, trees in flight and (for walker teams) the
 // schedule -- LDS path ring, shared or spread starts, ascending or breadth-first start order --
 // for a graph by timing short probes of the real sampler, and caches the winner per graph class
-// for the process.
+// for the process.  Where a call that leaves the plan open pops its trees' cycles in rounds, which no
+// plan of walkers does, that is a candidate too.
 //
 // The sampler's outputs are a fixed function of (graph, seed, sample index), so the choice
 // only changes speed.  Throughput depends on the number of concurrent walkers, on the state
@@ -88,6 +89,17 @@ bool lds_fits(const rwc_csr* g, int W, int64_t l) {
     return W > 1 && (64 / W) * round_up(g->n, 8) * 8 <= 48 * 1024 && l <= (int64_t{1} << 24);
 }
 
+// The call with its plan left open, in *q; true where it pops its cycles in rounds (anything else is
+// among the plans of walkers).
+bool open_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, rwc_sample_params* q) {
+    *q = *p;
+    q->walkers_per_tree = 0;
+    q->trees_in_flight = 0;
+    q->walkers_per_graph = nullptr;
+    q->flags = p->flags & RWC_SAMPLE_PERSISTENT;
+    return pops_cycles(graphs, G, q);
+}
+
 struct TuneLayout {
     uint64_t* counts;
     uint64_t* steps;
@@ -124,6 +136,18 @@ int max_sample_bytes(const rwc_csr* g, const rwc_sample_params* p, const std::ve
     return RWC_OK;
 }
 
+// Whether the open plan is a candidate for one graph: *q, within the budget (*bytes is raised to its need).
+int open_candidate(const rwc_csr* g, const rwc_sample_params* p, int64_t budget_bytes, rwc_sample_params* q, bool* use,
+                   size_t* bytes) {
+    *use = false;
+    if (!open_plan(g, 1, p, q)) return RWC_OK;
+    size_t b = 0;
+    RWC_CHECK(rwc_sample_forests_workspace(g, 1, q, &b));
+    *use = b <= static_cast<size_t>(budget_bytes);
+    if (*use && b > *bytes) *bytes = b;
+    return RWC_OK;
+}
+
 }  // namespace
 }  // namespace rwc
 
@@ -138,6 +162,9 @@ extern "C" int rwc_autotune_workspace(const rwc_csr* g, const rwc_sample_params*
     if (cand.empty()) return fail(RWC_ERR_WORKSPACE, "no candidate fits the state budget");
     size_t sb = 0;
     RWC_CHECK(max_sample_bytes(g, p, cand, &sb));
+    rwc_sample_params open{};
+    bool use_open = false;
+    RWC_CHECK(open_candidate(g, p, budget_bytes, &open, &use_open, &sb));
     *bytes = carve_tune(nullptr, g, sb).total;
     return RWC_OK;
 }
@@ -162,17 +189,15 @@ extern "C" int rwc_autotune_sampler(const rwc_csr* g, const rwc_sample_params* p
     if (cand.empty()) return fail(RWC_ERR_WORKSPACE, "no candidate fits the state budget");
     size_t sb = 0;
     RWC_CHECK(max_sample_bytes(g, p, cand, &sb));
+    rwc_sample_params open{};
+    bool use_open = false;
+    RWC_CHECK(open_candidate(g, p, budget_bytes, &open, &use_open, &sb));
     RWC_CHECK(check_workspace(ws, ws_bytes, carve_tune(nullptr, g, sb).total));
     TuneLayout L = carve_tune(ws, g, sb);
     rwc_tune_result best{};
     best.steps_per_s = -1.0;
     Candidate best_c = cand.front();
-    auto probe = [&](const Candidate& c) -> int {
-        rwc_sample_params q = *p;
-        q.walkers_per_tree = c.W;
-        q.trees_in_flight = static_cast<int32_t>(c.T);
-        q.num_samples = c.T;        // one full batch of the real sample range
-        q.flags = c.flags;
+    auto run = [&](const rwc_sample_params& q, double* rate) -> int {
         float ms[2] = {0.f, 0.f};
         rwc_sample_outputs o{};
         o.counts = L.counts;
@@ -181,7 +206,17 @@ extern "C" int rwc_autotune_sampler(const rwc_csr* g, const rwc_sample_params* p
         RWC_CHECK(rwc_sample_forests(g, 1, &q, &o, L.sample_ws, L.sample_bytes, stream));
         uint64_t steps = 0;
         RWC_HIP(hipMemcpy(&steps, L.steps, sizeof(steps), hipMemcpyDeviceToHost));
-        const double rate = static_cast<double>(steps) / (1e-3 * (ms[0] + ms[1]));
+        *rate = static_cast<double>(steps) / (1e-3 * (ms[0] + ms[1]));
+        return RWC_OK;
+    };
+    auto probe = [&](const Candidate& c) -> int {
+        rwc_sample_params q = *p;
+        q.walkers_per_tree = c.W;
+        q.trees_in_flight = static_cast<int32_t>(c.T);
+        q.num_samples = c.T;        // one full batch of the real sample range
+        q.flags = c.flags;
+        double rate = 0.0;
+        RWC_CHECK(run(q, &rate));
         ++best.candidates;
         if (rate > best.steps_per_s) {
             best.steps_per_s = rate;
@@ -194,6 +229,14 @@ extern "C" int rwc_autotune_sampler(const rwc_csr* g, const rwc_sample_params* p
     };
     for (const Candidate& c : cand) RWC_CHECK(probe(c));
     for (const Candidate& c : schedules(best_c, lds_fits(g, best_c.W, best_c.T))) RWC_CHECK(probe(c));
+    if (use_open) {
+        double rate = 0.0;
+        RWC_CHECK(run(open, &rate));
+        if (rate > best.steps_per_s) {
+            best.steps_per_s = rate;
+            best.flags = RWC_SAMPLE_POP_CYCLES;
+        }
+    }
     best.cached = 0;
     {
         std::lock_guard<std::mutex> lock(g_mu);
@@ -275,8 +318,19 @@ rwc_sample_params batch_probe_params(const rwc_csr* graphs, int32_t G, const rwc
     return q;
 }
 
+// The open plan's probe; true where both it and the call itself pop their cycles in rounds.
+bool batch_open_probe(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, rwc_sample_params* q) {
+    rwc_sample_params r = *p;
+    r.flags |= RWC_SAMPLE_PERSISTENT;
+    if (!open_plan(graphs, G, &r, q)) return false;
+    q->num_samples = probe_samples(p->num_samples);
+    return pops_cycles(graphs, G, q);
+}
+
 int batch_sample_bytes(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, size_t* bytes) {
     size_t best = 0;
+    rwc_sample_params open{};
+    if (batch_open_probe(graphs, G, p, &open)) RWC_CHECK(rwc_sample_forests_workspace(graphs, G, &open, &best));
     std::vector<int32_t> walkers;
     std::vector<BatchCandidate> all = batch_stage1();
     for (const BatchCandidate& c : batch_stage1())
@@ -339,8 +393,7 @@ extern "C" int rwc_autotune_batch(const rwc_csr* graphs, int32_t G, const rwc_sa
     BatchCandidate best_c = batch_stage1().front();
     std::vector<int32_t> walkers;
     std::vector<uint64_t> steps(G);
-    auto probe = [&](const BatchCandidate& c) -> int {
-        rwc_sample_params q = batch_probe_params(graphs, G, p, c, walkers);
+    auto run = [&](const rwc_sample_params& q, double* rate) -> int {
         float ms[2] = {0.f, 0.f};
         rwc_sample_outputs o{};
         o.counts = L.counts;
@@ -350,7 +403,13 @@ extern "C" int rwc_autotune_batch(const rwc_csr* graphs, int32_t G, const rwc_sa
         RWC_HIP(hipMemcpy(steps.data(), L.steps, sizeof(uint64_t) * G, hipMemcpyDeviceToHost));
         uint64_t total = 0;
         for (uint64_t x : steps) total += x;
-        const double rate = static_cast<double>(total) / (1e-3 * (ms[0] + ms[1]));
+        *rate = static_cast<double>(total) / (1e-3 * (ms[0] + ms[1]));
+        return RWC_OK;
+    };
+    auto probe = [&](const BatchCandidate& c) -> int {
+        const rwc_sample_params q = batch_probe_params(graphs, G, p, c, walkers);
+        double rate = 0.0;
+        RWC_CHECK(run(q, &rate));
         ++best.candidates;
         if (rate > best.steps_per_s) {
             best.steps_per_s = rate;
@@ -363,6 +422,15 @@ extern "C" int rwc_autotune_batch(const rwc_csr* graphs, int32_t G, const rwc_sa
     };
     for (const BatchCandidate& c : batch_stage1()) RWC_CHECK(probe(c));
     for (const BatchCandidate& c : batch_stage2(best_c)) RWC_CHECK(probe(c));
+    rwc_sample_params open{};
+    if (batch_open_probe(graphs, G, p, &open)) {
+        double rate = 0.0;
+        RWC_CHECK(run(open, &rate));
+        if (rate > best.steps_per_s) {
+            best.steps_per_s = rate;
+            best.flags = RWC_SAMPLE_POP_CYCLES;
+        }
+    }
     best.cached = 0;
     {
         std::lock_guard<std::mutex> lock(g_mu);

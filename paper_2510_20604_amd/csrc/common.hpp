@@ -122,5 +122,7 @@ int device_cu_count();
 // Waves of the walker-team kernel (with or without the LDS path ring) resident on the whole
 // device at once (occupancy x compute units); defined with the kernels.
 int team_resident_waves(bool ring);
+// Whether a call with these graphs and parameters pops its trees' cycles in rounds.
+bool pops_cycles(const rwc_csr* graphs, int32_t num_graphs, const rwc_sample_params* p);
 
 }  // namespace rwc

@@ -293,7 +293,8 @@ int pop_class(const rwc_csr& g) {
 }
 
 // Whether the call's trees are grown by popping cycles in rounds: an automatic plan (no walkers,
-// trees in flight or path ring asked for, and LDS state allowed), and graphs on which it pays.
+// trees in flight or path ring asked for, and LDS state allowed) or RWC_SAMPLE_POP_CYCLES, and graphs on
+// which it pays.
 //
 // Small-world graphs (cycle_pop), measured against walker teams (walk and reduction): 1.2 to 5 times
 // faster (ER(300, 8) x 2000 trees 0.93 -> 0.24 ms, ER(1000, 8) x 2000 2.03 -> 0.67, BA(2000, 4)
@@ -339,9 +340,11 @@ bool follows_changes(const rwc_csr& g, int64_t nodes) {
     return g.weight_ratio > kPopWideRatio && (g.n > 4096 || nodes > 20000000);
 }
 
-bool pops_cycles(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) {
-    if (p->walkers_per_tree != 0 || p->walkers_per_graph || p->trees_in_flight > 0) return false;
-    if (p->flags & (RWC_SAMPLE_NO_LDS_STATE | RWC_SAMPLE_PATH_RING)) return false;
+bool rounds_pay(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) {
+    if (!(p->flags & RWC_SAMPLE_POP_CYCLES)) {
+        if (p->walkers_per_tree != 0 || p->walkers_per_graph || p->trees_in_flight > 0) return false;
+        if (p->flags & (RWC_SAMPLE_NO_LDS_STATE | RWC_SAMPLE_PATH_RING)) return false;
+    }
     if (p->num_samples > kLdsMaxSamples || p->num_samples * G > (int64_t{1} << 30)) return false;
     const double cus = device_cu_count(), l = static_cast<double>(p->num_samples);
     const int64_t trees = p->num_samples * G, nodes = nodes_in_trees(graphs, G, p->num_samples);
@@ -396,7 +399,7 @@ int make_plan(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p, Plan
     // also holds larger graphs the two launches cannot overlap and the LDS launch's tail idles
     // the device (256 mixed graphs: the batch autotuner picks HBM state), so a call uses LDS
     // state only when every graph's trees fit.
-    plan->pop = pops_cycles(graphs, G, p);
+    plan->pop = rounds_pay(graphs, G, p);
     plan->classes.assign(plan->pop ? kPopClasses : 0, PopClass{});
     bool all_fit = plan->pop || (!(p->flags & RWC_SAMPLE_NO_LDS_STATE) && l <= kLdsMaxSamples);
     for (int32_t g = 0; g < G && all_fit && !plan->pop; ++g) {
@@ -819,6 +822,8 @@ void destroy_exec(CachedExec& e) {   // teardown: failures here have nobody to r
 }  // namespace rwc
 
 using namespace rwc;
+
+bool rwc::pops_cycles(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) { return rounds_pay(graphs, G, p); }
 
 extern "C" int rwc_sample_forests_workspace(const rwc_csr* graphs, int32_t num_graphs, const rwc_sample_params* p,
                                             size_t* bytes) {

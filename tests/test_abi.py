@@ -259,3 +259,26 @@ def test_build_flags_are_checked_before_device_work():
     names = [f[0] for f in _lib.RwcCsr._fields_]
     assert names.index("components") == names.index("bfs_depth") + 1
     assert names[-1] == "component"
+
+
+def test_pop_cycles_flag_opens_a_closed_plan():
+    """RWC_SAMPLE_POP_CYCLES: the plan (here seen by its workspace) of a call that leaves it open, whatever else
+    is asked for; on a graph too large for it, the plan asked for.  The autotuners' workspaces hold it."""
+    from paper_2510_20604_amd import _lib
+    lib = _lib.load()
+
+    def ws(n, **kw):
+        g = _lib.RwcCsr(n=n, pivot=0, m=4 * n, nnz=8 * n, weighted=0, max_degree=n - 1, row_ptr=8, col=8, rec=8, bfs_order=8)
+        p = _lib.SampleParams(seed=1, num_samples=500, root=-1, **kw)
+        size = ctypes.c_size_t()
+        assert lib.rwc_sample_forests_workspace(ctypes.byref(g), 1, ctypes.byref(p), ctypes.byref(size)) == 0
+        tune = ctypes.c_size_t()
+        assert lib.rwc_autotune_workspace(ctypes.byref(g), ctypes.byref(p), 1 << 32, ctypes.byref(tune)) == 0
+        assert tune.value > size.value or kw
+        return size.value
+
+    asked = dict(walkers_per_tree=16, trees_in_flight=64)
+    for flags in (0, _lib.RWC_SAMPLE_NO_LDS_STATE, _lib.RWC_SAMPLE_PATH_RING):
+        opened = dict(asked, flags=flags | _lib.RWC_SAMPLE_POP_CYCLES)
+        assert ws(9000, **opened) == ws(9000) != ws(9000, flags=flags, **asked)
+        assert ws(31000, **opened) == ws(31000, flags=flags, **asked)
