@@ -307,9 +307,17 @@ int pop_class(const rwc_csr& g) {
 // Weights: a round pops a pair of nodes joined by a heavy edge once, and a walker goes back and forth
 // over it as often, so wide weights slow both down, the rounds by their latency (one edge of 65535
 // among weights of 1: BA(20 000, 5) x 1000 trees 110 -> 66 ms, but x 4000 128 -> 161 and x 20 000 255 -> 621;
-// BA(4000, 2) x 20 000 68 -> 57).  So above kPopTeamNodes very wide weights pay up to kPopWideWork nodes in all
+// BA(4000, 2) x 20 000 68 -> 57).  So above kPopTeamNodes very wide weights pay up to kPopLongWork nodes in all
 // trees.  Between a ratio of kPopWideRatio and that, the rounds win once they follow the changed nodes only
 // (follows_changes).
+//
+// Roots: a walk finds the pivot, or one of many roots, soon; a single other root or a few may be hard to find,
+// and make as many rounds (one root of least degree: BA(12 000, 3) x 1000 trees 146 -> 82 ms, but x 4000
+// 150 -> 175 and x 20 000 232 -> 757; sixteen: x 4000 14.6 and 14.5, x 20 000 29 -> 53; 64: 20 -> 16).  The
+// same line, and for one root from 2049 nodes on (BA(4000, 5) x 20 000 110 -> 130, BA(2000, 4) 53 and 54).
+//
+// Stratified entries double a draw's arithmetic, and graphs without hubs draw most (ER(6000, 8) x 8000
+// trees 22.2 -> 24.0).
 //
 // Meshes (mesh_pop): a tree takes about 20 sqrt n rounds, and as many trees run at once as the LDS
 // holds; walker teams take about 10 us a node for a tree (twice and more on unit weights), but
@@ -322,7 +330,7 @@ int pop_class(const rwc_csr& g) {
 // to 60 000 nodes: the rounds 2 to 7 times faster wherever they are taken).
 constexpr int32_t kPopTeamNodes = kLdsStateBytes / 8;
 constexpr double kPopWideRatio = 64.0, kPopHeavyRatio = 4096.0;   // of the largest to the smallest weight
-constexpr int64_t kPopWideWork = 64000000;
+constexpr int64_t kPopLongWork = 40000000;
 
 bool has_hubs(const rwc_csr& g) { return static_cast<int64_t>(g.max_degree) * g.max_degree >= g.n; }
 
@@ -355,8 +363,12 @@ bool rounds_pay(const rwc_csr* graphs, int32_t G, const rwc_sample_params* p) {
         if (n > (c == kPopWorld ? kPopMaxNodes : kTokenMaxNodes)) return false;
         if (c == kPopWorld) {
             if (n > kPopLdsCounts && !has_hubs(graphs[g]) && trees > 4 * device_cu_count()) return false;
-            if (n > kPopTeamNodes && !has_hubs(graphs[g]) && trees > 16 * device_cu_count()) return false;
-            if (n > kPopTeamNodes && graphs[g].weight_ratio > kPopHeavyRatio && nodes > kPopWideWork) return false;
+            if (n > (p->strata >= 2 ? 5000 : kPopTeamNodes) && !has_hubs(graphs[g]) && trees > 16 * device_cu_count())
+                return false;
+            const bool other_root = p->num_roots > 0 ? p->num_roots == 1 : p->root >= 0 && p->root != graphs[g].pivot;
+            const bool few_roots = p->num_roots > 0 && p->num_roots < n / 256;
+            const bool long_chains = n > kPopTeamNodes && (graphs[g].weight_ratio > kPopHeavyRatio || few_roots);
+            if (nodes > kPopLongWork && (long_chains || (other_root && n > 2048))) return false;
         } else if (c != kPopSmall) {
             const double tree_us = 20.0 * std::sqrt(static_cast<double>(n)) * (c == kPopWide ? 25.0 : 5.0);
             rounds_us += tree_us * l / (cus * (c == kPopLarge ? 1.0 : 2.0));

@@ -179,7 +179,7 @@ def test_many_trees_that_keep_the_walker_teams():
     w = np.ones(ba.m, np.float32)
     w[ba.m // 2] = 5000.0                  # one heavy edge, in many trees
     most = 16 * torch.cuda.get_device_properties(0).multi_processor_count
-    for g, wt, few, many in ((er, None, most, most + 1), (ba, w, 9142, 9143)):
+    for g, wt, few, many in ((er, None, most, most + 1), (ba, w, 5714, 5715)):
         Gd = P.Graph(g.n, g.src, g.dst, wt)
         a, b = (P.sample_forests(Gd, l, 3, want_hash=False) for l in (few, many))
         assert a["walk_kernel"] == "cycle_pop" and b["walk_kernel"].startswith("wilson_team")
@@ -191,3 +191,23 @@ def test_many_trees_that_keep_the_walker_teams():
 def test_mesh_pop_on_its_largest_meshes(name):
     """Two work-groups a compute unit up to 139 264 nodes, one up to the last size."""
     test_mesh_pop_is_bit_exact(name, 2, name != "340x410", 0)
+
+
+@pytest.mark.parametrize("n,roots,kernel", [(2048, 1, "cycle_pop"), (2049, 1, "wilson_team"), (6144, 23, "cycle_pop"),
+                                            (6400, 24, "wilson_team"), (6400, 25, "cycle_pop")])
+def test_many_trees_with_few_roots(n, roots, kernel):
+    """One root that is not the pivot, or a few, in calls of more than 40 million tree nodes."""
+    g = G.barabasi_albert(n, 3, 2)
+    l = 40000000 // n + 1
+    Gd = P.Graph(g.n, g.src, g.dst)
+    S = [n - 1 - i for i in range(roots)]
+    s = P.sample_forests(Gd, l, 3, roots=S, want_hash=False)
+    assert s["walk_kernel"].startswith(kernel)
+    a = P.sample_forests(Gd, l - 5, 3, roots=S, want_hash=False)
+    assert a["walk_kernel"] == "cycle_pop"
+    a = P.sample_forests(Gd, 5, 3, sample_begin=l - 5, roots=S, want_hash=False, accumulate=a)
+    assert torch.equal(a["counts"], s["counts"]) and torch.equal(a["counts_sq"], s["counts_sq"])
+    if roots == 1:
+        one = P.sample_forests(Gd, l, 3, root=S[0], want_hash=False)
+        assert one["walk_kernel"].startswith(kernel) and torch.equal(one["counts"], s["counts"])
+        assert P.sample_forests(Gd, l, 3, root=Gd.pivot, want_hash=False)["walk_kernel"] == "cycle_pop"
