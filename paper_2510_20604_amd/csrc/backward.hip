@@ -422,7 +422,10 @@ __global__ void bpcg_spmm(int32_t n, int32_t v, int32_t R, int32_t nnz, int32_t 
                 for (int j = 0; j < kColPass; ++j) {
                     // columns c0 + 64 j .. lie in block blk (uniform); each row's base is uniform
                     // and the lane adds its own offset
-                    const int32_t blk = (c0 + j * kWave) / kWave;
+                    // (where there is none, the last block: past it is not P any more; a branch
+                    // instead costs the gradient with R = 66 five percent)
+                    const int32_t at = (c0 + j * kWave) / kWave, last = (R - 1) / kWave;
+                    const int32_t blk = at < last ? at : last;
                     const int64_t stride = p_block_width(blk, R);
                     const float* __restrict__ Pb = P32 + p_block_base(blk, n);
                     // lanes past column R - 1 read the row's first entry (their sums are never
