@@ -174,7 +174,7 @@ struct Direction<true> {
 
 // y = L_v p on the grounded system (row and column v removed, p_v kept at zero), with p^T y.  kLanes
 // lanes share a short row (strided over its entries, then a shuffle reduction; four on graphs of at
-// most three edges a node, sixteen otherwise); which block takes it is said below.  Rows longer than
+// most three edges a node, a wave above 80, sixteen otherwise); which block takes it is said below.  Rows longer than
 // 16 kLanes are left out of that pass and then taken one at a time, in order, by the whole block:
 // block b takes those among b, b + nb, b + 2 nb, ... (nb blocks), so that hub rows, which cluster at
 // small indices in power-law graphs, land in different blocks.
@@ -724,9 +724,16 @@ int pivot_solve(const rwc_csr* g, int32_t v, const EstLayout& L, const rwc_solve
     const bool pair = n <= kPairNodes;
     const bool few = g->nnz <= 6 * static_cast<int64_t>(n);   // short rows on average: four lanes each
     const unsigned nb = std::min<unsigned>(blocks_for(n, kIterBlock), kIterBlocks);
-    const unsigned nbs = std::min<unsigned>(blocks_for(static_cast<int64_t>(n) * (few ? 4 : 16), kIterBlock), kIterBlocks);
+    const bool dense = g->nnz > 160 * static_cast<int64_t>(n);   // a wave each (ER(10 000, 300): solve 0.68 -> 0.37 ms)
+    // a group of lanes per row, and on dense graphs, whose long rows are taken one after the other by whole
+    // blocks, a block for every four of its threads' loads (complete graph of 2000 nodes, 32 -> 512 blocks:
+    // 1.10 -> 0.26 ms)
+    const int64_t by_rows = blocks_for(static_cast<int64_t>(n) * (few ? 4 : dense ? 64 : 16), kIterBlock);
+    const unsigned nbs = static_cast<unsigned>(
+        std::min<int64_t>(std::max<int64_t>(by_rows, blocks_for(g->nnz, 4 * kIterBlock)), kIterBlocks));
     const int np = static_cast<int>(nb), nps = static_cast<int>(nbs);
-    auto product = pair ? (few ? spmv_dot<true, 4> : spmv_dot<true, 16>) : (few ? spmv_dot<false, 4> : spmv_dot<false, 16>);
+    auto product = pair ? (few ? spmv_dot<true, 4> : dense ? spmv_dot<true, 64> : spmv_dot<true, 16>)
+                        : (few ? spmv_dot<false, 4> : dense ? spmv_dot<false, 64> : spmv_dot<false, 16>);
     auto update = pair ? update_xr<true> : update_xr<false>;
     hipLaunchKernelGGL(pcg_init, dim3(nb), dim3(kIterBlock), 0, s, n, v, L.gmask, g->strength, L.x, L.r, L.z, L.p,
                        L.zp[0], L.part, L.sc);

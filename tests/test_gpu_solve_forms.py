@@ -103,3 +103,15 @@ def test_sparse_graphs_with_hubs(n):
     a = P.estimate(Gd, torch.ones(g.n, dtype=torch.int64, device="cuda"), 1)
     want = _hitting_times(g, None, [Gd.pivot])
     np.testing.assert_allclose(a["hit"].cpu().numpy(), want, rtol=1e-9, atol=1e-9 * want.max())
+
+
+@pytest.mark.parametrize("a,b", [(300, 4000), (2000, 2200), (20, 40000)])
+def test_dense_graphs(a, b):
+    """Complete bipartite graphs: rows taken by blocks on one side or both, by more blocks than the rows' own
+    lanes fill."""
+    g = G.graphs.EdgeList(a + b, np.repeat(np.arange(a), b).astype(np.int32), (a + np.tile(np.arange(b), a)).astype(np.int32), None)
+    w = G.uniform_weights(g.m, 0.5, 2.0, 3)
+    Gd = P.Graph(g.n, g.src, g.dst, w)
+    e = P.estimate(Gd, torch.ones(g.n, dtype=torch.int64, device="cuda"), 1)
+    want = _hitting_times(g, w, [Gd.pivot])
+    np.testing.assert_allclose(e["hit"].cpu().numpy(), want, rtol=1e-9, atol=1e-9 * want.max())
