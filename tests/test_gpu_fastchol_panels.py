@@ -58,3 +58,20 @@ def test_long_windows_match_the_oracle(columns, window, zeta):
     r = P.fastchol(Gd, droptol=1e-4, window=window, zeta=zeta, eps_p=1e-3, factor_capacity=fnz, inverse_capacity=snz)
     assert (r["factor_entries"], r["inverse_entries"]) == (fnz, snz)
     np.testing.assert_array_equal(r["tau"].cpu().numpy(), tau)
+
+
+def test_columns_over_the_lds_limit_with_short_windows():
+    """A ring of cliques: columns of the inverse of up to a thousand rows in windows of 12, from which on half
+    of the waves take no more."""
+    a, b = np.triu_indices(16, 1)
+    c = np.arange(70)
+    src = np.concatenate([(a[None] + 16 * c[:, None]).ravel(), 16 * c])
+    dst = np.concatenate([(b[None] + 16 * c[:, None]).ravel(), 16 * ((c + 1) % 70) + 1])
+    g = G.graphs.EdgeList(16 * 70, src.astype(np.int32), dst.astype(np.int32), None)
+    g = g.with_weights(G.uniform_weights(g.m, 0.5, 2.0, 5))
+    Gd = P.Graph(g.n, g.src, g.dst, g.w)
+    tau, fnz, snz = _oracle(g, Gd.pivot, 1e-4, 12.0, 12, 1e-6)
+    assert snz > 400 * g.n      # columns of hundreds of entries
+    r = P.fastchol(Gd, droptol=1e-4, window=12.0, zeta=12, eps_p=1e-6, factor_capacity=fnz, inverse_capacity=snz)
+    assert (r["factor_entries"], r["inverse_entries"]) == (fnz, snz)
+    np.testing.assert_array_equal(r["tau"].cpu().numpy(), tau)
