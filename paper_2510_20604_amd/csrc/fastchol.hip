@@ -878,8 +878,8 @@ __global__ void __launch_bounds__(kPanelBlock) fc_panel(FcArgs A, int32_t p, int
 // kSortCap-entry slice of it (14 us a level).  Windows over twice kRingWindow throughout make columns of
 // hundreds of entries, which eight waves do faster (BA(2000, 5), 128 columns: 402 ms, sixteen 412, held up
 // for slots in LDS that nothing reads 419); over kRingWindow sixteen (a 4000-node mesh, 33 columns: 96, 106).
-// So do other columns that pass kInvLds rows: from the first on, the upper eight waves take no more (ring of 100
-// cliques of 20, windows of 12: 677 ms, 710 with all sixteen, 671 with eight throughout).
+// (Shorter windows can make such columns too: ring of 100 cliques of 20, windows of 12, 671 with eight and 710 with
+// sixteen; letting the upper waves leave at the first such column cost the columns in LDS 1 to 2 %, taken back.)
 constexpr int kInvWaves = 16;
 constexpr int kInvWidestWaves = 8;
 constexpr int kInvLds = 512;
@@ -909,7 +909,7 @@ struct InvShared {
     int32_t len[kRing];             // -1: not kept here
     int32_t column[kRing];          // which column a slot holds, once it is published
     int32_t current[kInvWaves];     // the column each wave is at
-    int32_t next_col, abort_all, large;   // large: a column did not fit kInvLds entries
+    int32_t next_col, abort_all;
     unsigned long long pool;
 };
 static_assert(sizeof(InvShared) <= 160 * 1024);
@@ -1272,7 +1272,6 @@ __device__ InvResult general_column(const FcArgs& A, RWC_LDS InvShared* S, int32
     wave_order();
     // the nonzeros of S*(:, u), in LDS when they fit, else in this wave's global scratch
     const bool small = nt <= static_cast<uint32_t>(kInvLds);
-    if (!small && lane == 0) shared_store(&S->large, 1);
     double* const lds = (double*)(&S->wave[wave]);
     double* val = small ? lds : A.inv_val + static_cast<int64_t>(wave) * kSortCap;
     int32_t* row = small ? reinterpret_cast<int32_t*>(lds + kInvLds) : A.inv_row + static_cast<int64_t>(wave) * kSortCap;
@@ -1385,19 +1384,17 @@ __global__ void __launch_bounds__(kInvWaves * kWave) fc_inverse(FcArgs A) {
     if (threadIdx.x == 0) {
         S->next_col = 0;
         S->pool = 0;
-        S->large = 0;
         S->abort_all = A.header->status != 0 ? 1 : 0;   // the factor is incomplete
     }
-    for (int k = threadIdx.x; k < kRing; k += kInvWaves * kWave) S->column[k] = -1;
+    for (int k = threadIdx.x; k < kRing; k += blockDim.x) S->column[k] = -1;
+    if (threadIdx.x < kInvWaves) S->current[threadIdx.x] = static_cast<int>(threadIdx.x) * kWave < static_cast<int>(blockDim.x) ? N : -1;
     for (int k = lane; k < kInvTable; k += kWave) S->wave[wave].key[k] = -1;
-    if (lane == 0) S->current[wave] = N;
     __syncthreads();
     const double dmax = *A.dmax;
     // with windows over kRingWindow columns throughout none is read from LDS, so none is held up until its slot
-    // there is free; with twice that, fewer accumulators and sort buffers share the caches better
+    // there is free
     const bool ring = A.ws < kRingWindow + 1 || N <= kRingWindow;
-    const int waves = ring || A.ws <= 2 * kRingWindow ? kInvWaves : kInvWidestWaves;
-    while (wave < waves && (wave < kInvWidestWaves || shared_load(&S->large) == 0) && shared_load(&S->abort_all) == 0) {
+    while (shared_load(&S->abort_all) == 0) {
         int32_t t = 0;
         if (lane == 0) t = __hip_atomic_fetch_add(&S->next_col, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         t = __builtin_amdgcn_readfirstlane(t);
@@ -1624,7 +1621,9 @@ extern "C" int rwc_fastchol(const rwc_csr* g, const rwc_fastchol_params* p, doub
         clear_stamps();
         hipLaunchKernelGGL(fc_ichol, dim3(1), dim3(kWave), 0, s, A);
     }
-    hipLaunchKernelGGL(fc_inverse, dim3(1), dim3(kInvWaves * kWave), sizeof(InvShared), s, A);
+    // the longest windows on fewer waves, whose accumulators and sort buffers share the caches better
+    const int waves = p->window <= 2 * kRingWindow ? kInvWaves : kInvWidestWaves;
+    hipLaunchKernelGGL(fc_inverse, dim3(1), dim3(waves * kWave), sizeof(InvShared), s, A);
     RWC_HIP(hipGetLastError());
     return RWC_OK;
 }

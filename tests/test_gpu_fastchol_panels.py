@@ -61,8 +61,7 @@ def test_long_windows_match_the_oracle(columns, window, zeta):
 
 
 def test_columns_over_the_lds_limit_with_short_windows():
-    """A ring of cliques: columns of the inverse of up to a thousand rows in windows of 12, from which on half
-    of the waves take no more."""
+    """A ring of cliques: columns of the inverse of up to a thousand rows in windows of 12."""
     a, b = np.triu_indices(16, 1)
     c = np.arange(70)
     src = np.concatenate([(a[None] + 16 * c[:, None]).ravel(), 16 * c])
