@@ -172,7 +172,10 @@ int rwc_build_csr_ex(int32_t n, int64_t m, const int32_t* src_dev, const int32_t
                                         of at most 30 000 nodes and pivot eccentricity up to
                                         32 (state in LDS) and on meshes (a larger
                                         eccentricity) of at most 200 000 nodes (above 20 500
-                                        in the workspace) while that is the faster; else,
+                                        in the workspace) while that is the faster by the
+                                        sizes, trees, weights' ratio, hubs and roots (the
+                                        rule and its measurements: rounds_pay in
+                                        csrc/sampler.hip); else,
                                         a call whose graphs all use walker teams and all fit
                                         (64 / W trees of n 8-byte words in 48 KB of LDS; at
                                         most 2^24 samples) grows its trees in LDS instead:
@@ -196,7 +199,9 @@ typedef struct rwc_sample_params {
     int32_t walkers_per_tree;    /* 0 = automatic (teams of 64, fewer for graphs under
                                     1024 nodes); 1 = one walker per tree; else a power of
                                     two up to 64                                          */
-    uint64_t max_steps_per_tree; /* guard; 0 = 2^20 + 4096 n                              */
+    uint64_t max_steps_per_tree; /* guard; 0 = 2^20 + 4096 n.  Walker teams and popped cycles
+                                    hold 8 times it + 8 n + 1024 against a tree's iterations,
+                                    or its rounds and its departures / 64                  */
     uint32_t graph_index_base;   /* Philox graph word of graphs[0]; graph g uses base + g */
     uint32_t strata;             /* 0 or 1: independent draws.  L >= 2 (at most 2^31):
                                     stratified stack entries, a variance reduction at equal
@@ -521,13 +526,14 @@ int rwc_backward(const rwc_csr* g, const double* grad_rwc_dev, const rwc_backwar
  *    column of more than zeta nonzeros cut to the shortest prefix, by decreasing magnitude,
  *    whose dropped tail has 1-norm <= eps_p times the column's (Algorithm 2's sparsification);
  *    tau~_u = ||S~(:, u)||^2 (Section 4: (calL_v^{-1})_uu ~ ||R^{-1} e_u||^2).
- * Both are chains of dependent columns; one wave runs each, column by column, in the serial
- * algorithm's order of floating-point operations.  Feed tau~ to rwc_estimate_diag for RWC.
+ * Both are chains of dependent columns, each column's floating-point operations in the serial
+ * algorithm's order.  The dense factor is formed 32 columns a launch, the inverse by the waves of
+ * one workgroup, a column each.  Feed tau~ to rwc_estimate_diag for RWC.
  * ------------------------------------------------------------------------------------- */
 /* How rwc_fastchol factors calL_v; both give the same factor bit for bit.
  *   RWC_FASTCHOL_DENSE: right-looking on the packed lower triangle of the (n-1) x (n-1) matrix
- *     ((n-1) n / 2 doubles) in the workspace, one
- *     launch per column, the column's updates spread over the GPU (n - 1 <= 2^20);
+ *     ((n-1) n / 2 doubles) in the workspace, one launch per 32 columns, their updates spread
+ *     over the GPU (n - 1 <= 2^20);
  *   RWC_FASTCHOL_CHAIN: left-looking on one wave, sparse throughout (any n; a column may reach
  *     at most 4096 kept entries);
  *   RWC_FASTCHOL_AUTO: DENSE while that triangle is at most 32 GiB ((n-1) <= 92681), else CHAIN. */
@@ -549,7 +555,7 @@ typedef struct rwc_fastchol_params {
 int rwc_fastchol_workspace(const rwc_csr* g, const rwc_fastchol_params* p, size_t* bytes);
 
 /* tau_dev: double [n] output by input id (0 at the pivot).  Stream-ordered: the call enqueues
- * its kernels (five for CHAIN, n + 6 for DENSE; the inverse is one workgroup) and returns;
+ * its kernels (five for CHAIN, ceil((n - 1) / 32) + 7 for DENSE; the inverse is one workgroup) and returns;
  * rwc_workspace_status reports RWC_ERR_TOO_LARGE (a pool, or a column's 4096-entry ordering
  * buffer, was too small) or RWC_ERR_BREAKDOWN (a non-positive pivot), after which tau_dev is
  * meaningless.  RWC_ERR_INVALID_ARG for an unknown method, RWC_ERR_TOO_LARGE for DENSE past
